@@ -988,23 +988,16 @@ gsr_status gsr_dssim(gsr_ctx* c, void* stream, const gsr_camera* cams, int32_t n
     if (!c) return GSR_ERR_INVALID_ARG;
     if (!cams || n_views < 1 || !rgb || !target) return fail(c, GSR_ERR_INVALID_ARG, "d-ssim: null argument");
     if (!std::isfinite(weight)) return fail(c, GSR_ERR_INVALID_ARG, "d-ssim: weight not finite");
-    int64_t maxM = 0;
-    for (int v = 0; v < n_views; ++v) {
+    for (int v = 0; v < n_views; ++v)
         if (cams[v].width < 1 || cams[v].height < 1 || cams[v].width > 32767 || cams[v].height > 32767)
             return fail(c, GSR_ERR_INVALID_ARG, "d-ssim: camera size out of range");
-        maxM = std::max<int64_t>(maxM, (int64_t)cams[v].width * cams[v].height);
-    }
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
-    gsr_status s = grow(c, c->ssim_tmp, ssim_tmp_bytes(maxM));
+    static_assert(sizeof(gsr_camera) % sizeof(int32_t) == 0, "camera sizes are read at a word stride");
+    const SsimSizes z{ &cams[0].width, &cams[0].height, sizeof(gsr_camera) / sizeof(int32_t), n_views };
+    gsr_status s = grow(c, c->ssim_tmp, ssim_tmp_bytes(z, grad_rgb != nullptr));
     if (s) return s;
-    int64_t off = 0;
-    for (int v = 0; v < n_views; ++v) {             // views in order, one after another (they share the scratch)
-        const int W = cams[v].width, H = cams[v].height;
-        HIP_TRY(c, launch_dssim(rgb + 3 * off, target + 3 * off, W, H, weight, grad_rgb ? grad_rgb + 3 * off : nullptr,
-                                loss ? loss + v : nullptr, c->ssim_tmp.p, st));
-        off += (int64_t)W * H;
-    }
+    HIP_TRY(c, launch_dssim(rgb, target, z, weight, grad_rgb, loss, c->ssim_tmp.p, st));
     return GSR_OK;
 }
 

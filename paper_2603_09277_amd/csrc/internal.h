@@ -242,11 +242,19 @@ hipError_t launch_opacity_reg(const float* opac, int64_t n, float w, float* grad
 // L_O = w / n * sum of the n_partial FP64 partial sums, in a fixed order -> *loss
 hipError_t launch_opacity_reg_reduce(const double* partial, uint32_t n_partial, int64_t n, float w, float* loss,
                                      hipStream_t s);
-// D-SSIM of one view: loss (device, may be null) = weight (1 - SSIM(x, y)); grad (may be null)
-// += dloss/dx; x, y, grad [W*H][3]; tmp holds ssim_tmp_bytes(W*H) bytes
-size_t ssim_tmp_bytes(int64_t M);
-hipError_t launch_dssim(const float* x, const float* y, int W, int H, float weight, float* grad, float* loss, void* tmp,
-                        hipStream_t s);
+// D-SSIM of packed views: loss[v] (device, may be null) = weight (1 - SSIM(x, y)); grad
+// (may be null) += dloss/dx; x, y, grad [pixels][3]; tmp holds ssim_tmp_bytes bytes
+struct SsimSizes {
+    const int32_t* w0;                    // view v's width and height: w0[v * stride], h0[v * stride]
+    const int32_t* h0;
+    size_t stride;
+    int n;
+    int32_t w(int v) const { return w0[(size_t)v * stride]; }
+    int32_t h(int v) const { return h0[(size_t)v * stride]; }
+};
+size_t ssim_tmp_bytes(const SsimSizes& z, bool with_grad);
+hipError_t launch_dssim(const float* x, const float* y, const SsimSizes& z, float weight, float* grad, float* loss,
+                        void* tmp, hipStream_t s);
 // one bias-corrected Adam step on raw parameters (kind 0 identity, 1 exp, 2 sigmoid activation)
 hipError_t launch_adam(float* raw, float* m, float* v, float* act, const float* grad_act, int64_t n, int kind,
                        float lr, float b1, float b2, float eps, int64_t step, hipStream_t s);

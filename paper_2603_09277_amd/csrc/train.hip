@@ -5,7 +5,7 @@
 // statistics over an 11x11 Gaussian window (sigma 1.5, normalised; zero outside
 // the image), C1 = 0.01^2, C2 = 0.03^2,
 //   S = (2 mx my + C1)(2 sxy + C2) / ((mx^2 + my^2 + C1)(sx^2 + sy^2 + C2)).
-// The window is separable, so the five statistics take a horizontal and a
+// The window is separable, so the statistics take a horizontal and a
 // vertical 11-tap pass; the gradient runs the same two passes over the three
 // per-pixel partials (dS/dmx, dS/dE[x^2], dS/dE[xy]) -- the window is symmetric,
 // so the adjoint of each pass is the pass itself -- and combines them as
@@ -21,8 +21,6 @@ constexpr int kTaps = 11;
 constexpr int kHalf = 5;
 constexpr int kThr = 256;
 
-__constant__ float c_win[kTaps];
-
 __device__ __forceinline__ double block_sum_f64(double x)
 {
     __shared__ double s[kThr];
@@ -35,125 +33,259 @@ __device__ __forceinline__ double block_sum_f64(double x)
     return s[0];
 }
 
-// horizontal pass of x, y, x^2, y^2, xy: st[p][15] = per channel (5 values)
-__global__ __launch_bounds__(kThr) void ssim_rows_kernel(const float* x, const float* y, int W, int H, float* st)
+// D-SSIM.  One launch covers every view, forward and gradient.  A workgroup owns a band
+// of 64 pixel columns (192 floats: the interleaved channels are just a tap stride of
+// 3) over a segment of rows and marches down it 8 rows at a time, so that the only
+// traffic beyond the images, the gradient and their halos is LDS: per 8 rows
+//   1. the rows' x and y (band + 10 pixels either side), loaded one step ahead, into LDS;
+//   2. horizontal window sums of x, y, x^2 + y^2 and xy (the map needs the two variances
+//      only as their sum), a thread per (row, channel, 8-pixel strip): 18 values read
+//      for 8 outputs of 11 taps;
+//   3. vertical sums, a thread per float column, the 10 rows before the new ones kept in
+//      registers; the SSIM map's terms and its three partials, zero outside the image;
+//   4. horizontal sums of the partials, as 2;  5. vertical sums, as 3, and the gradient.
+// Bound by its FMAs and LDS reads, not by memory.  The separable passes over whole
+// images that this replaces (5 launches a view, 33 floats a pixel of scratch, every tap
+// of an array of structures from L2) took 1.58 ms on 8 views of 9.76 Mpixel together and
+// 0.23 ms on one 1296x840 image; this takes 0.42 ms (1.1 TB/s of images and gradient) and
+// 0.077 ms.  VALU issue is 0.56 of its rate at three workgroups a CU (0.46 at two).
+constexpr int kStep = 8;                       // rows a step
+constexpr int kBandPx = 64;                    // output pixels across a band
+constexpr int kOutF = 3 * kBandPx;             // its float columns
+constexpr int kRS2 = kOutF + 3;                // row strides in LDS, 3 more than a multiple of 8: the lanes of a
+                                               // strip pass read at 24 strip + channel + stride row
+struct SsimView {
+    int32_t W, H;
+    uint32_t wg_base, bands;                   // first workgroup of the view; bands across
+    int64_t off;                               // first float of the view
+    float scale;                               // dloss/dSSIM-sum
+};
+constexpr int kSsimViews = 32;                 // views a launch
+struct SsimArgs {
+    SsimView v[kSsimViews];
+    int32_t n_views, seg;                      // seg: output rows a workgroup
+    float w[kHalf + 1];                        // the symmetric window: taps k and 10 - k are w[k]
+};
+
+// 8 outputs of the 11-tap window over 18 consecutive inputs
+__device__ __forceinline__ void window8(const float* w, const float (&v)[kStep + 2 * kHalf], float (&o)[kStep])
 {
-    const int64_t p = (int64_t)blockIdx.x * kThr + threadIdx.x;
-    if (p >= (int64_t)W * H) return;
-    const int px = (int)(p % W);
-    float acc[15];
 #pragma unroll
-    for (int k = 0; k < 15; ++k) acc[k] = 0.f;
-    for (int b = -kHalf; b <= kHalf; ++b) {
-        const int qx = px + b;
-        if (qx < 0 || qx >= W) continue;
-        const float w = c_win[b + kHalf];
-        const int64_t q = p + b;
+    for (int j = 0; j < kStep; ++j) {
+        float s = w[0] * v[j];
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            const float xv = x[3 * q + ch], yv = y[3 * q + ch];
-            acc[5 * ch + 0] = fmaf(w, xv, acc[5 * ch + 0]);
-            acc[5 * ch + 1] = fmaf(w, yv, acc[5 * ch + 1]);
-            acc[5 * ch + 2] = fmaf(w, xv * xv, acc[5 * ch + 2]);
-            acc[5 * ch + 3] = fmaf(w, yv * yv, acc[5 * ch + 3]);
-            acc[5 * ch + 4] = fmaf(w, xv * yv, acc[5 * ch + 4]);
-        }
+        for (int k = 1; k < kTaps; ++k) s = fmaf(w[k <= kHalf ? k : 2 * kHalf - k], v[j + k], s);
+        o[j] = s;
     }
-#pragma unroll
-    for (int k = 0; k < 15; ++k) st[15 * p + k] = acc[k];
 }
 
-// vertical pass, S and its partials; block sums of S (FP64)
-__global__ __launch_bounds__(kThr) void ssim_map_kernel(const float* st, int W, int H, float* part, double* block_sum)
+template <bool GRAD>
+__global__ __launch_bounds__(kThr, 3) void ssim_kernel(const float* x, const float* y, SsimArgs a, float* grad,
+                                                    double* block_sum)
 {
-    const int64_t p = (int64_t)blockIdx.x * kThr + threadIdx.x;
-    const int64_t M = (int64_t)W * H;
+    constexpr int kIn = kStep + 2 * kHalf;     // inputs of 8 outputs
+    constexpr int kHalo1 = GRAD ? kHalf : 0;   // the map is needed this far around the outputs
+    constexpr int kMapF = kOutF + 6 * kHalo1;  // its float columns
+    constexpr int kInF = kMapF + 6 * kHalf;    // input float columns
+    static_assert(kInF <= kThr, "one thread an input column");
+    constexpr int kStrips1 = (kMapF + 23) / 24;
+    constexpr int kRSin = GRAD ? 275 : 227, kRSh = GRAD ? 243 : 195, kRSp = 227;
+    static_assert(24 * kStrips1 + 30 <= kRSin && 24 * kStrips1 <= kRSh && kOutF + 30 <= kRSp, "strips stay in a row");
+    static_assert(3 * kRS2 <= 4 * kRSh, "the second horizontal pass reuses the first one's rows");
+    // the input rows and the partials' rows take turns in one array (three workgroups a CU)
+    constexpr int kInWords = 2 * kStep * kRSin, kPWords = GRAD ? 3 * kStep * kRSp : 0;
+    __shared__ float s_io[kInWords > kPWords ? kInWords : kPWords];
+    __shared__ float s_h[4 * kStep * kRSh];
+    __shared__ double s_sum[kThr / 64];
+    const int t = (int)threadIdx.x;
+    int v = 0;
+    while (v + 1 < a.n_views && a.v[v + 1].wg_base <= blockIdx.x) ++v;
+    const SsimView& vw = a.v[v];
+    const int W = vw.W, H = vw.H;
+    const uint32_t local = blockIdx.x - vw.wg_base;
+    const int px0 = (int)(local % vw.bands) * kBandPx, r0 = (int)(local / vw.bands) * a.seg;
+    const int r1 = r0 + a.seg < H ? r0 + a.seg : H;
+    x += vw.off;
+    y += vw.off;
+    if (GRAD) grad += vw.off;
+    const int64_t stride = 3 * (int64_t)W;
+    // input column of this thread; map / output column (t < kMapF, t < kOutF)
+    const int in_px = px0 - kHalo1 - kHalf + t / 3;
+    const bool in_ok = t < kInF && in_px >= 0 && in_px < W;
+    const int64_t in_c = 3 * (int64_t)(px0 - kHalo1 - kHalf) + t;
+    const int map_px = px0 - kHalo1 + t / 3;
+    const bool map_ok = t < kMapF && map_px >= 0 && map_px < W;
+    const bool own_px = map_ok && map_px >= px0 && map_px < px0 + kBandPx;
+    const int64_t out_c = 3 * (int64_t)px0 + t;
+    const bool out_ok = t < kOutF && px0 + t / 3 < W;
+    // strips: (row, strip, channel), the channel fastest
+    const int h1_row = t / (3 * kStrips1), h1_rem = t % (3 * kStrips1), h1_c = 24 * (h1_rem / 3) + h1_rem % 3;
+    const int h2_row = t / 24, h2_rem = t % 24, h2_c = 24 * (h2_rem / 3) + h2_rem % 3;
+
+    float nx[kStep], ny[kStep];
+    auto fetch = [&](int row) {
+#pragma unroll
+        for (int j = 0; j < kStep; ++j) {
+            const bool ok = in_ok && row + j >= 0 && row + j < H;
+            nx[j] = ok ? x[(row + j) * stride + in_c] : 0.f;
+            ny[j] = ok ? y[(row + j) * stride + in_c] : 0.f;
+        }
+    };
+    auto put = [&]() {
+        if (t < kInF) {
+#pragma unroll
+            for (int j = 0; j < kStep; ++j) {
+                s_io[j * kRSin + t] = nx[j];
+                s_io[(kStep + j) * kRSin + t] = ny[j];
+            }
+        }
+    };
+    float old1[4][2 * kHalf], old2[GRAD ? 3 : 1][2 * kHalf];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int k = 0; k < 2 * kHalf; ++k) old1[q][k] = 0.f;
+#pragma unroll
+    for (int q = 0; q < (GRAD ? 3 : 1); ++q)
+#pragma unroll
+        for (int k = 0; k < 2 * kHalf; ++k) old2[q][k] = 0.f;
     double sacc = 0.0;
-    if (p < M) {
-        const int py = (int)(p / W);
-        float s5[15];
+    int row = r0 - kHalo1 - kHalf;             // the step's first input row
+    fetch(row);
+    put();
+    // the step of input rows [row, row + 8) completes map rows [row - 5, row + 3) and
+    // output rows [row - 10, row - 2)
+    for (; row - kHalf - kHalo1 < r1; row += kStep) {
+        __syncthreads();
+        if (t < 3 * kStrips1 * kStep) {
+            float xv[kIn], yv[kIn], sv[kIn], pv[kIn], o[kStep];
 #pragma unroll
-        for (int k = 0; k < 15; ++k) s5[k] = 0.f;
-        for (int a = -kHalf; a <= kHalf; ++a) {
-            const int qy = py + a;
-            if (qy < 0 || qy >= H) continue;
-            const float w = c_win[a + kHalf];
-            const int64_t q = p + (int64_t)a * W;
+            for (int k = 0; k < kIn; ++k) {
+                xv[k] = s_io[h1_row * kRSin + h1_c + 3 * k];
+                yv[k] = s_io[(kStep + h1_row) * kRSin + h1_c + 3 * k];
+                sv[k] = __fadd_rn(__fmul_rn(xv[k], xv[k]), __fmul_rn(yv[k], yv[k]));
+                pv[k] = xv[k] * yv[k];
+            }
+            float* h = s_h + h1_row * kRSh + h1_c;
+            auto put_row = [&](int q, const float (&in)[kIn]) {
+                window8(a.w, in, o);
 #pragma unroll
-            for (int k = 0; k < 15; ++k) s5[k] = fmaf(w, st[15 * q + k], s5[k]);
+                for (int k = 0; k < kStep; ++k) h[q * kStep * kRSh + 3 * k] = o[k];
+            };
+            put_row(0, xv);
+            put_row(1, yv);
+            put_row(2, sv);
+            put_row(3, pv);
         }
-        const float C1 = 1e-4f, C2 = 9e-4f;
+        fetch(row + kStep);
+        __syncthreads();
+        if (!GRAD) put();                       // (every read of this step's rows is done)
+        if (t < kMapF) {
+            float m[4][kStep];
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            const float mx = s5[5 * ch], my = s5[5 * ch + 1];
-            const float sx = s5[5 * ch + 2] - mx * mx, sy = s5[5 * ch + 3] - my * my, sxy = s5[5 * ch + 4] - mx * my;
-            const float ln = 2.f * mx * my + C1, ld = mx * mx + my * my + C1;
-            const float cn = 2.f * sxy + C2, cd = sx + sy + C2;
-            const float N = ln * cn, D = ld * cd;
-            const float iD = 1.f / D;
-            sacc += (double)(N * iD);
-            const float dN = 2.f * my * (cn - ln), dD = 2.f * mx * (cd - ld);
-            part[9 * p + 3 * ch + 0] = (dN - N * iD * dD) * iD;     // dS/dmx
-            part[9 * p + 3 * ch + 1] = -N * ld * iD * iD;           // dS/dExx
-            part[9 * p + 3 * ch + 2] = 2.f * ln * iD;               // dS/dExy
+            for (int q = 0; q < 4; ++q) {
+                float in[kIn];
+#pragma unroll
+                for (int k = 0; k < 2 * kHalf; ++k) in[k] = old1[q][k];
+#pragma unroll
+                for (int j = 0; j < kStep; ++j) in[2 * kHalf + j] = s_h[(q * kStep + j) * kRSh + t];
+                window8(a.w, in, m[q]);
+#pragma unroll
+                for (int k = 0; k < 2 * kHalf; ++k) old1[q][k] = in[kStep + k];
+            }
+            const float C1 = 1e-4f, C2 = 9e-4f;
+#pragma unroll
+            for (int j = 0; j < kStep; ++j) {
+                const int r = row - kHalf + j;
+                const float mx = m[0][j], my = m[1][j];
+                // products rounded alike on both sides, so that identical images give S = 1
+                const float mxy = __fmul_rn(mx, my), mm = __fadd_rn(__fmul_rn(mx, mx), __fmul_rn(my, my));
+                const float ln = __fadd_rn(2.f * mxy, C1), ld = __fadd_rn(mm, C1);
+                const float cn = __fadd_rn(2.f * __fsub_rn(m[3][j], mxy), C2);
+                const float cd = __fadd_rn(__fsub_rn(m[2][j], mm), C2);
+                const float N = ln * cn, D = ld * cd;
+                const float iD = 1.f / D;
+                if (own_px && r >= r0 && r < r1) sacc += (double)(N * iD);
+                if (GRAD) {
+                    const bool ok = map_ok && r >= 0 && r < H;
+                    const float dN = 2.f * my * (cn - ln), dD = 2.f * mx * (cd - ld);
+                    s_io[(0 * kStep + j) * kRSp + t] = ok ? (dN - N * iD * dD) * iD : 0.f;     // dS/dmx
+                    s_io[(1 * kStep + j) * kRSp + t] = ok ? -N * ld * iD * iD : 0.f;           // dS/dExx
+                    s_io[(2 * kStep + j) * kRSp + t] = ok ? 2.f * ln * iD : 0.f;               // dS/dExy
+                }
+            }
+        }
+        if constexpr (GRAD) {
+            float gx[kStep], gy[kStep], gg[kStep];
+#pragma unroll
+            for (int j = 0; j < kStep; ++j) {   // in flight over the second horizontal pass
+                const int r = row - 2 * kHalf + j;
+                const bool ok = out_ok && r >= r0 && r < r1;
+                gx[j] = ok ? x[r * stride + out_c] : 0.f;
+                gy[j] = ok ? y[r * stride + out_c] : 0.f;
+                gg[j] = ok ? grad[r * stride + out_c] : 0.f;
+            }
+            __syncthreads();
+            if (t < 24 * kStep) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    float in[kIn], o[kStep];
+#pragma unroll
+                    for (int k = 0; k < kIn; ++k) in[k] = s_io[(q * kStep + h2_row) * kRSp + h2_c + 3 * k];
+                    window8(a.w, in, o);
+#pragma unroll
+                    for (int k = 0; k < kStep; ++k) s_h[(q * kStep + h2_row) * kRS2 + h2_c + 3 * k] = o[k];
+                }
+            }
+            __syncthreads();
+            put();                              // (every read of the partials is done)
+            if (t < kOutF) {
+                float m[3][kStep];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    float in[kIn];
+#pragma unroll
+                    for (int k = 0; k < 2 * kHalf; ++k) in[k] = old2[q][k];
+#pragma unroll
+                    for (int j = 0; j < kStep; ++j) in[2 * kHalf + j] = s_h[(q * kStep + j) * kRS2 + t];
+                    window8(a.w, in, m[q]);
+#pragma unroll
+                    for (int k = 0; k < 2 * kHalf; ++k) old2[q][k] = in[kStep + k];
+                }
+#pragma unroll
+                for (int j = 0; j < kStep; ++j) {
+                    const int r = row - 2 * kHalf + j;
+                    if (out_ok && r >= r0 && r < r1) {
+                        const float d = m[0][j] + 2.f * gx[j] * m[1][j] + gy[j] * m[2][j];
+                        grad[r * stride + out_c] = gg[j] + vw.scale * d;
+                    }
+                }
+            }
         }
     }
-    const double tot = block_sum_f64(sacc);
-    if (threadIdx.x == 0) block_sum[blockIdx.x] = tot;
-}
-
-// horizontal pass of the 9 partials
-__global__ __launch_bounds__(kThr) void ssim_back_rows_kernel(const float* part, int W, int H, float* tmp)
-{
-    const int64_t p = (int64_t)blockIdx.x * kThr + threadIdx.x;
-    if (p >= (int64_t)W * H) return;
-    const int px = (int)(p % W);
-    float acc[9];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) acc[k] = 0.f;
-    for (int b = -kHalf; b <= kHalf; ++b) {
-        const int qx = px + b;
-        if (qx < 0 || qx >= W) continue;
-        const float w = c_win[b + kHalf];
+    for (int o = 32; o > 0; o >>= 1) sacc += __shfl_xor(sacc, o, 64);
+    if ((t & 63) == 0) s_sum[t >> 6] = sacc;
+    __syncthreads();
+    if (t == 0) {
+        double tot = 0.0;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) acc[k] = fmaf(w, part[9 * (p + b) + k], acc[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < 9; ++k) tmp[9 * p + k] = acc[k];
-}
-
-// vertical pass and the combination; grad += scale * dSSIM-sum/dx
-__global__ __launch_bounds__(kThr) void ssim_back_cols_kernel(const float* tmp, const float* x, const float* y, int W,
-                                                              int H, float scale, float* grad)
-{
-    const int64_t p = (int64_t)blockIdx.x * kThr + threadIdx.x;
-    if (p >= (int64_t)W * H) return;
-    const int py = (int)(p / W);
-    float acc[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) acc[k] = 0.f;
-    for (int a = -kHalf; a <= kHalf; ++a) {
-        const int qy = py + a;
-        if (qy < 0 || qy >= H) continue;
-        const float w = c_win[a + kHalf];
-        const int64_t q = p + (int64_t)a * W;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) acc[k] = fmaf(w, tmp[9 * q + k], acc[k]);
-    }
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-        const float d = acc[3 * ch] + 2.f * x[3 * p + ch] * acc[3 * ch + 1] + y[3 * p + ch] * acc[3 * ch + 2];
-        grad[3 * p + ch] += scale * d;
+        for (int w = 0; w < kThr / 64; ++w) tot += s_sum[w];
+        block_sum[blockIdx.x] = tot;
     }
 }
 
-__global__ __launch_bounds__(kThr) void ssim_loss_kernel(const double* block_sum, uint32_t n_blocks, int64_t M,
+// one workgroup a view: weight (1 - SSIM) from its workgroups' sums, in a fixed order
+__global__ __launch_bounds__(kThr) void ssim_loss_kernel(const double* block_sum, SsimArgs a, uint32_t n_wg,
                                                          float weight, float* loss)
 {
+    const int v = (int)blockIdx.x;
+    const uint32_t b1 = v + 1 < a.n_views ? a.v[v + 1].wg_base : n_wg;
     double acc = 0.0;
-    for (uint32_t b = threadIdx.x; b < n_blocks; b += kThr) acc += block_sum[b];
+    for (uint32_t b = a.v[v].wg_base + threadIdx.x; b < b1; b += kThr) acc += block_sum[b];
     const double tot = block_sum_f64(acc);
-    if (threadIdx.x == 0) *loss = (float)((double)weight * (1.0 - tot / (3.0 * (double)M)));
+    if (threadIdx.x == 0)
+        loss[v] = (float)((double)weight * (1.0 - tot / (3.0 * (double)((int64_t)a.v[v].W * a.v[v].H))));
 }
 
 // one bias-corrected Adam step on raw parameters; kind 0 identity, 1 exp, 2 sigmoid
@@ -231,48 +363,74 @@ __global__ void __launch_bounds__(256) adam_kernel(float* raw, float* m, float* 
     }
 }
 
-bool g_win_ready[64] = {};
-
-hipError_t upload_window()
+uint32_t ssim_groups(int32_t W, int32_t H, int seg)
 {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev >= 0 && dev < 64 && g_win_ready[dev]) return hipSuccess;
-    float w[kTaps];
-    double s = 0.0, g[kTaps];
-    for (int k = 0; k < kTaps; ++k) { g[k] = std::exp(-(double)((k - kHalf) * (k - kHalf)) / (2.0 * 1.5 * 1.5)); s += g[k]; }
-    for (int k = 0; k < kTaps; ++k) w[k] = (float)(g[k] / s);
-    e = hipMemcpyToSymbol(HIP_SYMBOL(c_win), w, sizeof w, 0, hipMemcpyHostToDevice);
-    if (e == hipSuccess && dev >= 0 && dev < 64) g_win_ready[dev] = true;
-    return e;
+    return (uint32_t)((W + kBandPx - 1) / kBandPx) * (uint32_t)((H + seg - 1) / seg);
+}
+
+// rows a workgroup, of those whose marched rows (the segment and its halo) are whole
+// steps: the one with the least rounds of workgroups (3 a CU, by LDS) times steps
+int ssim_segment(const SsimSizes& z, int v0, int n, bool with_grad, uint64_t* groups)
+{
+    constexpr uint64_t kResident = 768;
+    const int halo = with_grad ? 4 * kHalf : 2 * kHalf;
+    int best = 0;
+    uint64_t best_cost = 0;
+    for (int steps : { 18, 14, 10, 8, 6, 4 }) {
+        const int seg = steps * kStep - halo;
+        uint64_t wgs = 0;
+        for (int v = v0; v < v0 + n; ++v) wgs += ssim_groups(z.w(v), z.h(v), seg);
+        const uint64_t cost = (wgs + kResident - 1) / kResident * (uint64_t)steps;
+        if (best == 0 || cost < best_cost) { best = seg; best_cost = cost; *groups = wgs; }
+    }
+    return best;
 }
 
 }  // namespace
 
-size_t ssim_tmp_bytes(int64_t M) { return (size_t)M * 4 * (15 + 9 + 9) + ((size_t)(M + kThr - 1) / kThr + 1) * 8 + 1024; }
-
-hipError_t launch_dssim(const float* x, const float* y, int W, int H, float weight, float* grad, float* loss, void* tmp,
-                        hipStream_t s)
+size_t ssim_tmp_bytes(const SsimSizes& z, bool with_grad)
 {
-    const int64_t M = (int64_t)W * H;
-    if (M == 0) return hipSuccess;
-    hipError_t e = upload_window();
-    if (e != hipSuccess) return e;
-    char* t = (char*)tmp;
-    float* st = (float*)t;
-    float* part = st + 15 * M;
-    float* back = part + 9 * M;
-    double* bsum = (double*)(((uintptr_t)(back + 9 * M) + 255) & ~(uintptr_t)255);
-    const uint32_t nb = (uint32_t)((M + kThr - 1) / kThr);
-    hipLaunchKernelGGL(ssim_rows_kernel, dim3(nb), dim3(kThr), 0, s, x, y, W, H, st);
-    hipLaunchKernelGGL(ssim_map_kernel, dim3(nb), dim3(kThr), 0, s, st, W, H, part, bsum);
-    if (loss) hipLaunchKernelGGL(ssim_loss_kernel, dim3(1), dim3(kThr), 0, s, bsum, nb, M, weight, loss);
-    if (grad) {
-        hipLaunchKernelGGL(ssim_back_rows_kernel, dim3(nb), dim3(kThr), 0, s, part, W, H, back);
-        // L = weight (1 - SSIM), SSIM = sum S / (3 M)
-        hipLaunchKernelGGL(ssim_back_cols_kernel, dim3(nb), dim3(kThr), 0, s, back, x, y, W, H,
-                           -weight / (3.0f * (float)M), grad);
+    uint64_t most = 1;
+    for (int v0 = 0; v0 < z.n; v0 += kSsimViews) {
+        uint64_t g = 0;
+        (void)ssim_segment(z, v0, z.n - v0 < kSsimViews ? z.n - v0 : kSsimViews, with_grad, &g);
+        most = g > most ? g : most;
+    }
+    return (size_t)most * sizeof(double);
+}
+
+hipError_t launch_dssim(const float* x, const float* y, const SsimSizes& z, float weight, float* grad, float* loss,
+                        void* tmp, hipStream_t s)
+{
+    SsimArgs a;
+    double g[kTaps], gsum = 0.0;
+    for (int k = 0; k < kTaps; ++k) { g[k] = std::exp(-(double)((k - kHalf) * (k - kHalf)) / (2.0 * 1.5 * 1.5)); gsum += g[k]; }
+    for (int k = 0; k <= kHalf; ++k) a.w[k] = (float)(g[k] / gsum);
+    double* bsum = (double*)tmp;
+    int64_t off = 0;
+    for (int v0 = 0; v0 < z.n; v0 += kSsimViews) {
+        const int n = z.n - v0 < kSsimViews ? z.n - v0 : kSsimViews;
+        uint64_t groups = 0;
+        a.n_views = n;
+        a.seg = ssim_segment(z, v0, n, grad != nullptr, &groups);
+        uint32_t wg = 0;
+        for (int v = 0; v < n; ++v) {
+            SsimView& q = a.v[v];
+            q.W = z.w(v0 + v);
+            q.H = z.h(v0 + v);
+            q.wg_base = wg;
+            q.bands = (uint32_t)((q.W + kBandPx - 1) / kBandPx);
+            q.off = 3 * off;
+            // L = weight (1 - SSIM), SSIM = sum S / (3 M)
+            const int64_t M = (int64_t)q.W * q.H;
+            q.scale = -weight / (3.0f * (float)M);
+            wg += ssim_groups(q.W, q.H, a.seg);
+            off += M;
+        }
+        if (grad) hipLaunchKernelGGL(ssim_kernel<true>, dim3(wg), dim3(kThr), 0, s, x, y, a, grad, bsum);
+        else hipLaunchKernelGGL(ssim_kernel<false>, dim3(wg), dim3(kThr), 0, s, x, y, a, grad, bsum);
+        if (loss)
+            hipLaunchKernelGGL(ssim_loss_kernel, dim3(n), dim3(kThr), 0, s, bsum, a, wg, weight, loss + v0);
     }
     return hipGetLastError();
 }

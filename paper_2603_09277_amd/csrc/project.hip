@@ -215,7 +215,7 @@ __device__ __forceinline__ void view_proj(const CamDev& c, const float* mu, cons
 // The forward reads the cameras of a launch from LDS, kCamChunk at a time: read
 // from global memory in its view loop, a camera became vector loads, whose wait
 // (the shared vector-memory counter) also waited for the previous view's stores.
-// The backward stores nothing in its view loop and reads them with scalar loads.
+// The backward's pairs name their views, so its lanes read the cameras from LDS as well.
 constexpr int kCamChunk = 16;
 static_assert(sizeof(CamDev) % 4 == 0, "cameras are copied in 4-byte words");
 
@@ -321,21 +321,145 @@ __global__ __launch_bounds__(256) void project_fwd_kernel(ProjectFwdArgs a)
     }
 }
 
-// ONE: a launch of one view. The view loop then has a constant trip count and the
-// kernel fits three wavefronts a SIMD (168 VGPRs; the compiler spills a few bytes)
-// instead of two.
-template <int DEG, bool BF16, bool ONE>
-__device__ __forceinline__ void project_bwd_one(const ProjectBwdArgs& a, uint32_t i)
+// LDS rows of a wavefront's SH gradients: kWords 32-bit words a Gaussian, one more apart
+// (an odd stride: no bank conflicts)
+template <int K, bool BF16>
+struct ShRows {
+    static constexpr int kBytes = K * 3 * (BF16 ? 2 : 4);
+    static constexpr bool kStaged = kBytes % 16 == 0;
+    static constexpr int kWords = kBytes / 4, kStride = kWords + 1;
+    static constexpr int kLds = kStaged ? 256 * kStride : 1;     // words a workgroup
+};
+
+// what one (view, Gaussian) adds to its Gaussian's gradient: 16 words of LDS, one more apart
+struct PairGrad {
+    float mu[3], S[6], op, col[3], dir[3];
+};
+constexpr int kPairWords = 16, kPairStride = kPairWords + 1;
+static_assert(sizeof(PairGrad) == 4 * kPairWords, "a pair's record is 16 words");
+constexpr int kBwdRound = 8;                   // views a round
+
+// The gradient one view gives Gaussian i: its 2D row back through colour, conic and
+// mean.  False where the view does not project it (nothing to add).
+template <int DEG, bool BF16>
+__device__ __forceinline__ bool project_bwd_pair(const ProjectBwdArgs& a, uint32_t i, int v, const CamDev& c, PairGrad& o)
 {
     constexpr int K = (DEG + 1) * (DEG + 1);
+    float g[kG2];
+#pragma unroll
+    for (int k = 0; k < kG2; ++k) g[k] = a.grad2d[(size_t)kG2 * ((size_t)v * a.n + i) + k];
     float mu[3] = { a.means[3 * (size_t)i], a.means[3 * (size_t)i + 1], a.means[3 * (size_t)i + 2] };
     float s[3] = { a.scales[3 * (size_t)i], a.scales[3 * (size_t)i + 1], a.scales[3 * (size_t)i + 2] };
     float q[4] = { a.quats[4 * (size_t)i], a.quats[4 * (size_t)i + 1], a.quats[4 * (size_t)i + 2], a.quats[4 * (size_t)i + 3] };
-    float op = a.opac[i];
     float sh[K * 3];
     load_sh<K, BF16>(a.sh, i, sh);
     Local L;
-    local_state(mu, s, q, op, sh, K * 3, L);
+    local_state(mu, s, q, a.opac[i], sh, K * 3, L);
+    ViewProj P;
+    view_proj(c, mu, L, a.flags, P);
+    if (!P.ok) return false;
+    const float gmx = g[0], gmy = g[1], gA = g[2], gB = g[3], gC = g[4];
+    o.op = g[5];
+    // ---- colour -> SH coefficients (by the caller, from dir and col) and viewing direction
+    const float dx = mu[0] - c.campos[0], dy = mu[1] - c.campos[1], dz = mu[2] - c.campos[2];
+    const float idn = 1.f / sqrtf(dx * dx + dy * dy + dz * dz);
+    const float d0 = dx * idn, d1 = dy * idn, d2 = dz * idn;
+    o.dir[0] = d0; o.dir[1] = d1; o.dir[2] = d2;
+    float Y[K];
+    sh_basis<DEG>(d0, d1, d2, Y);
+    for (int ch = 0; ch < 3; ++ch) {
+        float acc = 0.f;
+#pragma unroll
+        for (int k = 0; k < K; ++k) acc += Y[k] * sh[3 * k + ch];
+        acc += 0.5f;
+        const bool clamped = (a.flags & F_CCLAMP) && acc < 0.f;
+        o.col[ch] = clamped ? 0.f : g[6 + ch];
+    }
+    float gmu[3] = { 0.f, 0.f, 0.f };
+    if constexpr (DEG > 0) {
+        float wk[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) wk[k] = sh[3 * k] * o.col[0] + sh[3 * k + 1] * o.col[1] + sh[3 * k + 2] * o.col[2];
+        const float3 gd = sh_basis_grad<DEG>(d0, d1, d2, wk);
+        const float dd = d0 * gd.x + d1 * gd.y + d2 * gd.z;
+        gmu[0] = (gd.x - d0 * dd) * idn;
+        gmu[1] = (gd.y - d1 * dd) * idn;
+        gmu[2] = (gd.z - d2 * dd) * idn;
+    }
+    // ---- conic -> 2D covariance (FP64): dL/dSigma' = -Q G Q, G the symmetric gradient of Q
+    const double hB = 0.5 * (double)gB;
+    const double QG00 = P.qA * gA + P.qB * hB, QG01 = P.qA * hB + P.qB * gC;
+    const double QG10 = P.qB * gA + P.qC * hB, QG11 = P.qB * hB + P.qC * gC;
+    const float g00 = (float)(-(QG00 * P.qA + QG01 * P.qB));
+    const float g01 = (float)(-(QG00 * P.qB + QG01 * P.qC));
+    const float g11 = (float)(-(QG10 * P.qB + QG11 * P.qC));
+    // ---- Sigma' = Tm Sigma Tm^T: dL/dSigma += Tm^T GS Tm ; dL/dTm = 2 GS Tm Sigma = 2 GS W
+    const float* T0 = P.Tm;
+    const float* T1 = P.Tm + 3;
+    int idx = 0;
+    for (int k = 0; k < 3; ++k)
+        for (int l = k; l < 3; ++l, ++idx)
+            o.S[idx] = g00 * T0[k] * T0[l] + g01 * (T0[k] * T1[l] + T1[k] * T0[l]) + g11 * T1[k] * T1[l];
+    float gTm[6];
+    for (int j = 0; j < 3; ++j) {
+        gTm[j] = 2.f * (g00 * P.W[j] + g01 * P.W[3 + j]);
+        gTm[3 + j] = 2.f * (g01 * P.W[j] + g11 * P.W[3 + j]);
+    }
+    // dL/dJ = dL/dTm Rc^T (only the four non-zero entries of J matter)
+    const float gJ00 = gTm[0] * c.R[0] + gTm[1] * c.R[1] + gTm[2] * c.R[2];
+    const float gJ02 = gTm[0] * c.R[6] + gTm[1] * c.R[7] + gTm[2] * c.R[8];
+    const float gJ11 = gTm[3] * c.R[3] + gTm[4] * c.R[4] + gTm[5] * c.R[5];
+    const float gJ12 = gTm[3] * c.R[6] + gTm[4] * c.R[7] + gTm[5] * c.R[8];
+    // ---- J and the 2D mean -> camera-space position
+    const float iz = 1.f / P.tz, iz2 = iz * iz;
+    float gtx = 0.f, gty = 0.f, gtz = 0.f;
+    gtz += -(gJ00 * c.fx + gJ11 * c.fy) * iz2;
+    if (!P.clx) { gtx += -gJ02 * c.fx * iz2; gtz += 2.f * gJ02 * c.fx * P.tx * iz2 * iz; }
+    else        { gtz += gJ02 * c.fx * P.uc * iz2; }
+    if (!P.cly) { gty += -gJ12 * c.fy * iz2; gtz += 2.f * gJ12 * c.fy * P.ty * iz2 * iz; }
+    else        { gtz += gJ12 * c.fy * P.vc * iz2; }
+    gtx += gmx * c.fx * iz;
+    gty += gmy * c.fy * iz;
+    gtz -= (gmx * c.fx * P.tx + gmy * c.fy * P.ty) * iz2;
+    for (int k = 0; k < 3; ++k) o.mu[k] = gmu[k] + (c.R[k] * gtx + c.R[3 + k] * gty + c.R[6 + k] * gtz);
+    return true;
+}
+
+// A workgroup owns 256 Gaussians.  Which of their (view, Gaussian) rows are this
+// frame's (the others are zero: no pixel blended the record) is read from the row
+// stamps, 8 views a round; the live pairs of a round are listed in LDS, Gaussian by
+// Gaussian with the views in order, and worked on one a thread, 256 at a time; then each
+// Gaussian's thread adds its pairs in that order.  So lanes are full whichever Gaussians
+// and views are live, and a Gaussian with no live row reads nothing but its stamps: on 8
+// views of 3M Gaussians 12 % of the pairs are live and 64 % of the Gaussians have none,
+// while a thread a Gaussian that looped over the views ran at 0.29 of its lanes and read
+// every parameter.  Bound by HBM, and with several views by the latency of its phases
+// at two workgroups a CU (the 48 SH sums stay in registers over the rounds).  One view of
+// 3.3M FP32 degree-3 Gaussians: 0.41 -> 0.20 ms (4.0 TB/s of what it has to move); 200k:
+// 29 -> 21 us; 8 views of 3M, BF16: 0.53 -> 0.41 ms.
+template <int DEG, bool BF16, bool ONE>
+__global__ __launch_bounds__(256, ONE ? 3 : 2) void project_bwd_kernel(ProjectBwdArgs a)
+{
+    constexpr int K = (DEG + 1) * (DEG + 1);
+    constexpr int kBwdViews = ONE ? 1 : kBwdRound;
+    using RL = ShRows<K, BF16>;
+    constexpr int kPairLds = 256 * kPairStride;
+    // the pairs' records, later the SH gradients' rows
+    __shared__ uint32_t s_mem[kPairLds > RL::kLds ? kPairLds : RL::kLds];
+    __shared__ uint16_t s_list[256 * kBwdViews];             // local Gaussian | view << 8
+    __shared__ uint32_t s_wave[256 / 64];
+    __shared__ CamDev s_cam[kBwdViews];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wid = tid >> 6;
+    const uint32_t base = blockIdx.x * 256u, i = base + tid;
+    const bool active = i < a.n;
+    // the opacity regulariser's loss (Sec. 5.4 ablation): per-wavefront FP64 sums of
+    // exp(-(sigma - 0.5)^2 / 0.05), in a fixed order, for a fixed-order final sum
+    double e = 0.0;
+    if (a.reg_partial && active) {
+        const float d = a.opac[i] - 0.5f;
+        e = (double)expf(-(d * d) * 20.0f);                  // 1 / 0.05 = 20
+    }
+    const uint32_t st = *a.stamp;
 
     float gmu[3] = { 0.f, 0.f, 0.f };
     float gS[6] = { 0.f, 0.f, 0.f, 0.f, 0.f, 0.f };   // symmetric dL/dSigma, upper triangle
@@ -343,115 +467,97 @@ __device__ __forceinline__ void project_bwd_one(const ProjectBwdArgs& a, uint32_
     float gsh[K * 3];
 #pragma unroll
     for (int k = 0; k < K * 3; ++k) gsh[k] = 0.f;
+    bool live = false;
 
-    // this view's row stamp and 2D gradient row: a row whose stamp is not this frame's
-    // is zero (no pixel blended any of its pairs, or the record has no pairs) and is not
-    // read.  Stamps are loaded two views ahead, so that the row of the next view is
-    // loaded (one view ahead) only where its stamp is this frame's.
-    const uint32_t st = *a.stamp;
     const int n_views = ONE ? 1 : a.n_views;
-    uint32_t rs_n = n_views > 0 ? a.rec_stamp[i] : 0u;
-    uint32_t rs_nn = n_views > 1 ? a.rec_stamp[(size_t)a.n + i] : 0u;
-    float g_n[kG2];
+    for (int v0 = 0; v0 < n_views; v0 += kBwdViews) {
+        const int nv = n_views - v0 < kBwdViews ? n_views - v0 : kBwdViews;
+        // this Gaussian's live views (every stamp in flight at once)
+        uint32_t r[kBwdViews], mask = 0u;
 #pragma unroll
-    for (int k = 0; k < kG2; ++k) g_n[k] = 0.f;
-    if (rs_n == st) {
+        for (int k = 0; k < kBwdViews; ++k)
+            r[k] = a.rec_stamp[(size_t)(v0 + (k < nv ? k : nv - 1)) * a.n + (active ? i : a.n - 1u)];
 #pragma unroll
-        for (int k = 0; k < kG2; ++k) g_n[k] = a.grad2d[(size_t)kG2 * i + k];
-    }
-    for (int v = 0; v < n_views; ++v) {
-        const uint32_t rs_v = rs_n;
-        float g[kG2];
+        for (int k = 0; k < kBwdViews; ++k)
+            if (active && k < nv && r[k] == st) mask |= 1u << k;
+        const uint32_t cnt = (uint32_t)__popc(mask);
+        live = live || cnt != 0u;
+        uint32_t inc = cnt;
 #pragma unroll
-        for (int k = 0; k < kG2; ++k) g[k] = g_n[k];
-        rs_n = rs_nn;
-        if (v + 1 < n_views && rs_n == st) {
-            const size_t o = (size_t)(v + 1) * a.n + i;
-#pragma unroll
-            for (int k = 0; k < kG2; ++k) g_n[k] = a.grad2d[(size_t)kG2 * o + k];
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(inc, o, 64);
+            if (lane >= (uint32_t)o) inc += y;
         }
-        if (v + 2 < n_views) rs_nn = a.rec_stamp[(size_t)(v + 2) * a.n + i];
-        if (rs_v != st) continue;                           // zero gradient from this view
-        const CamDev& c = a.cams[v];                        // scalar loads here (unlike the forward)
-        ViewProj P;
-        view_proj(c, mu, L, a.flags, P);
-        if (!P.ok) continue;
-        float gmx = g[0], gmy = g[1], gA = g[2], gB = g[3], gC = g[4];
-        gop += g[5];
-        // ---- colour -> SH coefficients and viewing direction
-        float dx = mu[0] - c.campos[0], dy = mu[1] - c.campos[1], dz = mu[2] - c.campos[2];
-        float dn = sqrtf(dx * dx + dy * dy + dz * dz);
-        float idn = 1.f / dn;
-        float d0 = dx * idn, d1 = dy * idn, d2 = dz * idn;
-        float Y[K];
-        sh_basis<DEG>(d0, d1, d2, Y);
-        float gcol[3];
-        for (int ch = 0; ch < 3; ++ch) {
-            float acc = 0.f;
+        __syncthreads();                                     // (the last round's reads are done)
+        if (lane == 63u) s_wave[wid] = inc;
+        {   // the round's cameras
+            const uint32_t* src = reinterpret_cast<const uint32_t*>(a.cams + v0);
+            for (uint32_t w = tid; w < (uint32_t)nv * (uint32_t)(sizeof(CamDev) / 4); w += 256u)
+                reinterpret_cast<uint32_t*>(s_cam)[w] = src[w];
+        }
+        __syncthreads();
+        uint32_t first = inc - cnt, total = 0u;
 #pragma unroll
-            for (int k = 0; k < K; ++k) acc += Y[k] * sh[3 * k + ch];
-            acc += 0.5f;
-            bool clamped = (a.flags & F_CCLAMP) && acc < 0.f;
-            gcol[ch] = clamped ? 0.f : g[6 + ch];
+        for (uint32_t w = 0; w < 256u / 64u; ++w) {
+            if (w < wid) first += s_wave[w];
+            total += s_wave[w];
         }
-        float wk[K];
+        uint32_t at = first;
+        for (uint32_t m = mask; m; m &= m - 1u) s_list[at++] = (uint16_t)(tid | ((uint32_t)(__ffs(m) - 1) << 8));
+        __syncthreads();
+        for (uint32_t c0 = 0; c0 < (ONE ? 1u : total); c0 += 256u) {
+            if (c0 + tid < total) {
+                const uint32_t e2 = s_list[c0 + tid], v = e2 >> 8;
+                PairGrad o;
+                if (!project_bwd_pair<DEG, BF16>(a, base + (e2 & 0xffu), v0 + (int)v, s_cam[v], o)) {
+                    o = PairGrad{};
+                    o.dir[2] = 1.f;
+                }
+                float* dst = reinterpret_cast<float*>(s_mem) + tid * kPairStride;
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            wk[k] = sh[3 * k] * gcol[0] + sh[3 * k + 1] * gcol[1] + sh[3 * k + 2] * gcol[2];
-            gsh[3 * k + 0] += Y[k] * gcol[0];
-            gsh[3 * k + 1] += Y[k] * gcol[1];
-            gsh[3 * k + 2] += Y[k] * gcol[2];
+                for (int k = 0; k < kPairWords; ++k) dst[k] = reinterpret_cast<const float*>(&o)[k];
+            }
+            __syncthreads();
+            const uint32_t k0 = ONE || first > c0 ? first : c0;
+            const uint32_t k1 = ONE || first + cnt < c0 + 256u ? first + cnt : c0 + 256u;
+            for (uint32_t k = k0; k < k1; ++k) {
+                PairGrad o;
+                const float* src = reinterpret_cast<const float*>(s_mem) + (k - c0) * kPairStride;
+#pragma unroll
+                for (int w = 0; w < kPairWords; ++w) reinterpret_cast<float*>(&o)[w] = src[w];
+#pragma unroll
+                for (int w = 0; w < 3; ++w) gmu[w] += o.mu[w];
+#pragma unroll
+                for (int w = 0; w < 6; ++w) gS[w] += o.S[w];
+                gop += o.op;
+                float Y[K];
+                sh_basis<DEG>(o.dir[0], o.dir[1], o.dir[2], Y);
+#pragma unroll
+                for (int w = 0; w < K; ++w) {
+                    gsh[3 * w + 0] += Y[w] * o.col[0];
+                    gsh[3 * w + 1] += Y[w] * o.col[1];
+                    gsh[3 * w + 2] += Y[w] * o.col[2];
+                }
+            }
+            __syncthreads();
         }
-        if constexpr (DEG > 0) {
-            float3 gd = sh_basis_grad<DEG>(d0, d1, d2, wk);
-            float dd = d0 * gd.x + d1 * gd.y + d2 * gd.z;
-            gmu[0] += (gd.x - d0 * dd) * idn;
-            gmu[1] += (gd.y - d1 * dd) * idn;
-            gmu[2] += (gd.z - d2 * dd) * idn;
-        }
-        // ---- conic -> 2D covariance (FP64): dL/dSigma' = -Q G Q, G the symmetric gradient of Q
-        double hB = 0.5 * (double)gB;
-        double QG00 = P.qA * gA + P.qB * hB, QG01 = P.qA * hB + P.qB * gC;
-        double QG10 = P.qB * gA + P.qC * hB, QG11 = P.qB * hB + P.qC * gC;
-        float g00 = (float)(-(QG00 * P.qA + QG01 * P.qB));
-        float g01 = (float)(-(QG00 * P.qB + QG01 * P.qC));
-        float g11 = (float)(-(QG10 * P.qB + QG11 * P.qC));
-        // ---- Sigma' = Tm Sigma Tm^T: dL/dSigma += Tm^T GS Tm ; dL/dTm = 2 GS Tm Sigma = 2 GS W
-        const float* T0 = P.Tm;
-        const float* T1 = P.Tm + 3;
-        int idx = 0;
-        for (int k = 0; k < 3; ++k)
-            for (int l = k; l < 3; ++l, ++idx)
-                gS[idx] += g00 * T0[k] * T0[l] + g01 * (T0[k] * T1[l] + T1[k] * T0[l]) + g11 * T1[k] * T1[l];
-        float gTm[6];
-        for (int j = 0; j < 3; ++j) {
-            gTm[j] = 2.f * (g00 * P.W[j] + g01 * P.W[3 + j]);
-            gTm[3 + j] = 2.f * (g01 * P.W[j] + g11 * P.W[3 + j]);
-        }
-        // dL/dJ = dL/dTm Rc^T (only the four non-zero entries of J matter)
-        float gJ00 = gTm[0] * c.R[0] + gTm[1] * c.R[1] + gTm[2] * c.R[2];
-        float gJ02 = gTm[0] * c.R[6] + gTm[1] * c.R[7] + gTm[2] * c.R[8];
-        float gJ11 = gTm[3] * c.R[3] + gTm[4] * c.R[4] + gTm[5] * c.R[5];
-        float gJ12 = gTm[3] * c.R[6] + gTm[4] * c.R[7] + gTm[5] * c.R[8];
-        // ---- J and the 2D mean -> camera-space position
-        float iz = 1.f / P.tz, iz2 = iz * iz;
-        float gtx = 0.f, gty = 0.f, gtz = 0.f;
-        gtz += -(gJ00 * c.fx + gJ11 * c.fy) * iz2;
-        if (!P.clx) { gtx += -gJ02 * c.fx * iz2; gtz += 2.f * gJ02 * c.fx * P.tx * iz2 * iz; }
-        else        { gtz += gJ02 * c.fx * P.uc * iz2; }
-        if (!P.cly) { gty += -gJ12 * c.fy * iz2; gtz += 2.f * gJ12 * c.fy * P.ty * iz2 * iz; }
-        else        { gtz += gJ12 * c.fy * P.vc * iz2; }
-        gtx += gmx * c.fx * iz;
-        gty += gmy * c.fy * iz;
-        gtz -= (gmx * c.fx * P.tx + gmy * c.fy * P.ty) * iz2;
-        gmu[0] += c.R[0] * gtx + c.R[3] * gty + c.R[6] * gtz;
-        gmu[1] += c.R[1] * gtx + c.R[4] * gty + c.R[7] * gtz;
-        gmu[2] += c.R[2] * gtx + c.R[5] * gty + c.R[8] * gtz;
     }
 
+    float s[3] = { 0.f, 0.f, 0.f }, q[4] = { 0.f, 0.f, 0.f, 0.f };
+    if (live) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) s[k] = a.scales[3 * (size_t)i + k];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[k] = a.quats[4 * (size_t)i + k];
+    }
+    // a live row's Gaussian was projected, so its inputs are finite and its quaternion not zero
+    const float qnorm = sqrtf(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
+    const float iq = live ? 1.f / qnorm : 0.f;
+    const float w = q[0] * iq, x = q[1] * iq, y = q[2] * iq, z = q[3] * iq;
+    float R[9];
+    quat_to_rot(w, x, y, z, R);
     // ---- Sigma = M M^T with M = R diag(s):  dL/dM = 2 G M
     float G[9] = { gS[0], gS[1], gS[2], gS[1], gS[3], gS[4], gS[2], gS[4], gS[5] };
-    const float* R = L.R;
     float M[9];
     for (int r = 0; r < 3; ++r)
         for (int j = 0; j < 3; ++j) M[3 * r + j] = R[3 * r + j] * s[j];
@@ -463,7 +569,6 @@ __device__ __forceinline__ void project_bwd_one(const ProjectBwdArgs& a, uint32_
             gR[3 * r + j] = gm * s[j];
         }
     // ---- rotation -> normalised quaternion -> raw quaternion
-    float w = L.qn[0], x = L.qn[1], y = L.qn[2], z = L.qn[3];
     float gw = 2.f * (-z * gR[1] + y * gR[2] + z * gR[3] - x * gR[5] - y * gR[6] + x * gR[7]);
     float gx = 2.f * (y * gR[1] + z * gR[2] + y * gR[3] - w * gR[5] + z * gR[6] + w * gR[7]) -
                4.f * x * (gR[4] + gR[8]);
@@ -472,74 +577,67 @@ __device__ __forceinline__ void project_bwd_one(const ProjectBwdArgs& a, uint32_
     float gz = 2.f * (-w * gR[1] + x * gR[2] + w * gR[3] + y * gR[5] + x * gR[6] + y * gR[7]) -
                4.f * z * (gR[0] + gR[4]);
     float qd = w * gw + x * gx + y * gy + z * gz;
-    float iq = L.ok ? 1.f / L.qnorm : 0.f;
 
-    bool any = L.ok;
-    a.g_means[3 * (size_t)i + 0] = any ? gmu[0] : 0.f;
-    a.g_means[3 * (size_t)i + 1] = any ? gmu[1] : 0.f;
-    a.g_means[3 * (size_t)i + 2] = any ? gmu[2] : 0.f;
-    a.g_scales[3 * (size_t)i + 0] = any ? gs[0] : 0.f;
-    a.g_scales[3 * (size_t)i + 1] = any ? gs[1] : 0.f;
-    a.g_scales[3 * (size_t)i + 2] = any ? gs[2] : 0.f;
-    a.g_quats[4 * (size_t)i + 0] = any ? (gw - w * qd) * iq : 0.f;
-    a.g_quats[4 * (size_t)i + 1] = any ? (gx - x * qd) * iq : 0.f;
-    a.g_quats[4 * (size_t)i + 2] = any ? (gy - y * qd) * iq : 0.f;
-    a.g_quats[4 * (size_t)i + 3] = any ? (gz - z * qd) * iq : 0.f;
-    {
-        float go = any ? gop : 0.f;
+    // Every lane stores: a Gaussian without a live row its zeros, with its neighbours'
+    // gradients (stored apart, the lines they share went to memory twice: 0.53 -> 0.81 ms
+    // on 8 views).
+    if (active) {
+        a.g_means[3 * (size_t)i + 0] = live ? gmu[0] : 0.f;
+        a.g_means[3 * (size_t)i + 1] = live ? gmu[1] : 0.f;
+        a.g_means[3 * (size_t)i + 2] = live ? gmu[2] : 0.f;
+        a.g_scales[3 * (size_t)i + 0] = live ? gs[0] : 0.f;
+        a.g_scales[3 * (size_t)i + 1] = live ? gs[1] : 0.f;
+        a.g_scales[3 * (size_t)i + 2] = live ? gs[2] : 0.f;
+        a.g_quats[4 * (size_t)i + 0] = live ? (gw - w * qd) * iq : 0.f;
+        a.g_quats[4 * (size_t)i + 1] = live ? (gx - x * qd) * iq : 0.f;
+        a.g_quats[4 * (size_t)i + 2] = live ? (gy - y * qd) * iq : 0.f;
+        a.g_quats[4 * (size_t)i + 3] = live ? (gz - z * qd) * iq : 0.f;
+        float go = live ? gop : 0.f;
         if (a.reg_w != 0.f) {                                // + dL_O/dsigma, as a separate pass would add it
-            const float d = op - 0.5f;
-            const float e = expf(-(d * d) * 20.0f);
-            go += (a.reg_w / (float)a.n) * e * (-40.0f * d);
+            const float d = a.opac[i] - 0.5f;
+            const float ex = expf(-(d * d) * 20.0f);
+            go += (a.reg_w / (float)a.n) * ex * (-40.0f * d);
         }
         a.g_opac[i] = go;
     }
-    if constexpr (BF16) {
-        uint16_t* p = reinterpret_cast<uint16_t*>(a.g_sh) + (size_t)i * (K * 3);
-        if constexpr ((K * 3) % 8 == 0) {                    // eight values a 16-byte store
-            uint32_t w[K * 3 / 2];
+    // SH gradients: through LDS, so that the workgroup stores its Gaussians' range as
+    // consecutive 16-byte words (from the lanes' own rows, 16 bytes each at a stride of a
+    // row, every store touched 64 lines in part: 0.35 instead of 0.27 ms at 3.3M, one view)
+    const bool staged = RL::kStaged && (reinterpret_cast<uintptr_t>(a.g_sh) & 15u) == 0u;
+    if (staged) {
+        uint32_t* row = s_mem + tid * RL::kStride;
 #pragma unroll
-            for (int k = 0; k < K * 3; k += 2)
-                w[k / 2] = (uint32_t)f32_to_bf16_rne(any ? gsh[k] : 0.f) |
-                           ((uint32_t)f32_to_bf16_rne(any ? gsh[k + 1] : 0.f) << 16);
-            if ((reinterpret_cast<uintptr_t>(a.g_sh) & 15u) == 0u) {
-                uint4* p4 = reinterpret_cast<uint4*>(p);
-#pragma unroll
-                for (int k = 0; k < K * 3 / 8; ++k)
-                    p4[k] = make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
-            } else {
-#pragma unroll
-                for (int k = 0; k < K * 3; ++k) p[k] = (uint16_t)(w[k / 2] >> (16 * (k & 1)));
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < K * 3; ++k) p[k] = f32_to_bf16_rne(any ? gsh[k] : 0.f);
+        for (int k = 0; k < RL::kWords; ++k) {
+            if constexpr (BF16)
+                row[k] = (uint32_t)f32_to_bf16_rne(gsh[2 * k]) | ((uint32_t)f32_to_bf16_rne(gsh[2 * k + 1]) << 16);
+            else
+                row[k] = __float_as_uint(gsh[k]);
         }
-    } else {
-        float* p = reinterpret_cast<float*>(a.g_sh) + (size_t)i * (K * 3);
+        __syncthreads();
+        const uint32_t n_own = base < a.n ? (a.n - base < 256u ? a.n - base : 256u) : 0u;
+        constexpr uint32_t kQ = RL::kWords / 4 > 0 ? RL::kWords / 4 : 1;         // 16-byte words a Gaussian
+        uint4* dst = reinterpret_cast<uint4*>(a.g_sh) + (size_t)base * kQ;
 #pragma unroll
-        for (int k = 0; k < K * 3; ++k) p[k] = any ? gsh[k] : 0.f;
+        for (uint32_t r = 0; r < kQ; ++r) {
+            const uint32_t f = r * 256u + tid, g = f / kQ;
+            const uint32_t* src = s_mem + g * RL::kStride + 4u * (f - g * kQ);
+            if (g < n_own) dst[f] = make_uint4(src[0], src[1], src[2], src[3]);
+        }
+    } else if (active) {
+        if constexpr (BF16) {
+            uint16_t* p = reinterpret_cast<uint16_t*>(a.g_sh) + (size_t)i * (K * 3);
+#pragma unroll
+            for (int k = 0; k < K * 3; ++k) p[k] = f32_to_bf16_rne(gsh[k]);
+        } else {
+            float* p = reinterpret_cast<float*>(a.g_sh) + (size_t)i * (K * 3);
+#pragma unroll
+            for (int k = 0; k < K * 3; ++k) p[k] = gsh[k];
+        }
     }
-}
-
-template <int DEG, bool BF16, bool ONE>
-__global__ __launch_bounds__(256, ONE ? 3 : 1) void project_bwd_kernel(ProjectBwdArgs a)
-{
-    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-    // the opacity regulariser's loss (Sec. 5.4 ablation): per-wavefront FP64 sums of
-    // exp(-(sigma - 0.5)^2 / 0.05), in a fixed order, for a fixed-order final sum; stored
-    // after the gradients (with a store ahead of the view loop, some camera fields in it
-    // became vector loads that waited on memory: 0.52 -> 0.62 ms on the 8-view workload)
-    double e = 0.0;
-    if (a.reg_partial && i < a.n) {
-        const float d = a.opac[i] - 0.5f;
-        e = (double)expf(-(d * d) * 20.0f);                  // 1 / 0.05 = 20
-    }
-    if (i < a.n) project_bwd_one<DEG, BF16, ONE>(a, i);
     if (a.reg_partial) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o, 64);
-        if ((threadIdx.x & 63u) == 0u) a.reg_partial[4u * blockIdx.x + (threadIdx.x >> 6)] = e;
+        if (lane == 0u) a.reg_partial[4u * blockIdx.x + wid] = e;
     }
 }
 

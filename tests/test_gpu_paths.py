@@ -45,3 +45,49 @@ def test_dssim_bands_and_segments(R, sizes, with_grad):
             g = grad[at:at + w * h].cpu().numpy().reshape(h, w, 3).astype(np.float64)
             assert np.linalg.norm(g + 0.2 * gs) <= 1e-4 * np.linalg.norm(0.2 * gs), (v, w, h)
         at += w * h
+
+
+ATTRS = ("means", "scales", "quats", "opacities", "sh")
+
+
+def _small_scene(n, deg, seed=5):
+    scene = scenes.gmm_scene(seed, n, sh_degree=deg, n_clusters=4, box=3.0)
+    return scene, {k: v for k, v in to_dev(scene).items()}
+
+
+# Projection backward: 256 Gaussians a workgroup, 8 views a round, 256 live pairs a pass, the SH
+# gradients stored as 16-byte words where they are aligned.  A launch of all views against the sum
+# of one-view launches: the same FP32 terms in another order (relative L2 1e-5; SH in BF16: one
+# rounding of the sum against a sum of rounded terms, 2^-8 a term).
+@pytest.mark.parametrize("n,deg,bf16", [(255, 0, False), (257, 1, False), (300, 1, True), (256, 2, False), (700, 3, False),
+                                        (515, 3, True)])
+@pytest.mark.parametrize("views,shift", [(2, 0), (9, 0), (17, 1)])
+def test_projection_backward_rounds(n, deg, bf16, views, shift):
+    scene, t = _small_scene(n, deg)
+    if bf16:
+        t["sh"] = t["sh"].to(torch.bfloat16)
+    opts = gsr.RasterOptions(sh_degree=deg, sh_bf16=bf16)
+    cams = scenes.orbit_cameras(np.random.default_rng(views), [(61 + v, 43) for v in range(views)])
+    p = [t[k] for k in ATTRS]
+    r = gsr.Rasterizer(max_views=views)
+    npix = [c.width * c.height for c in cams]
+    g_rgb = torch.randn(sum(npix), 3, device=DEV, generator=torch.Generator(DEV).manual_seed(1))
+    g_em = torch.full((views,), 0.3, device=DEV)
+    grads = {k: torch.full_like(v, 7.0) for k, v in zip(ATTRS, p)}
+    # (shift: SH gradients 4 bytes off a 16-byte boundary)
+    pad = 4 // t["sh"].element_size() * shift
+    grads["sh"] = torch.full((t["sh"].numel() + pad,), 7.0, device=DEV, dtype=t["sh"].dtype)[pad:].view_as(t["sh"])
+    out = r.forward(*p, cams, opts)
+    got = r.backward(*p, cams, opts, out, g_rgb, None, g_em, grads)
+    want = {k: torch.zeros(v.shape, device=DEV, dtype=torch.float64) for k, v in zip(ATTRS, p)}
+    at = 0
+    for v, cam in enumerate(cams):
+        o1 = r.forward(*p, [cam], opts)
+        g1 = r.backward(*p, [cam], opts, o1, g_rgb[at:at + npix[v]].contiguous(), None, g_em[v:v + 1])
+        at += npix[v]
+        for k in ATTRS:
+            want[k] += g1[k].double()
+    for k in ATTRS:
+        d, w = (got[k].double() - want[k]).norm().item(), want[k].norm().item()
+        assert w > 0 and d <= (2.0 ** -8 if bf16 and k == "sh" else 1e-5) * w, (k, d / w)
+    r.close()

@@ -80,6 +80,12 @@ struct ProjectFwdArgs {
     uint32_t* tiles_touched;              // [V*n]
     int32_t* radius;                      // [V*n]
     float* depth;                         // [V*n]
+    // pair counting (count null: none): the sum of tiles touched of view v -> count_total[v], by
+    // way of project_count_words(n, n_views) words at count; only views from store_from on are
+    // stored, at the records of views 0, 1, ...
+    uint64_t* count;
+    uint64_t* count_total;
+    int32_t store_from;
 };
 
 struct ProjectBwdArgs {
@@ -173,6 +179,7 @@ struct InvArgs {
 
 // ---- launchers (return hipError_t of the launch) ----
 hipError_t launch_project_fwd(const ProjectFwdArgs& a, int sh_degree, bool sh_bf16, hipStream_t s);
+inline size_t project_count_words(uint32_t n, int n_views) { return 4 * (size_t)((n + 255u) / 256u) * (size_t)n_views; }
 hipError_t launch_project_bwd(const ProjectBwdArgs& a, int sh_degree, bool sh_bf16, hipStream_t s);
 
 // exclusive scan of vals[order[i]] for i < n  ->  out[i]; total -> *total (uint32),
@@ -220,8 +227,6 @@ hipError_t launch_grad_reduce(const float* pair_grad, const uint32_t* pair_stamp
 hipError_t launch_frame_begin(uint32_t* counters, uint32_t* ranges, uint32_t n_tiles, uint32_t n_words,
                               hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t count, hipStream_t s);
-// p[i] = i
-hipError_t launch_iota_u32(uint32_t* p, uint32_t count, hipStream_t s);
 // order[n_tiles]: the tiles by decreasing list length (16 classes per octave);
 // hist: 512 words, zeroed (bucket counts, then bucket fill counters)
 constexpr uint32_t kTileHistWords = 512;

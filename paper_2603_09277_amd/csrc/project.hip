@@ -230,8 +230,11 @@ __device__ __forceinline__ void stage_cams(CamDev* s_cam, const CamDev* cams, in
     __syncthreads();
 }
 
-// ONE: a launch of one view (a constant view count; fewer registers)
-template <int DEG, bool BF16, bool ONE>
+// ONE: a launch of one view (a constant view count; fewer registers).  COUNT: every
+// workgroup also leaves its tile count of each view in a.count, and only views from
+// a.store_from on are stored (as if the launch had only them): the pair counts of several
+// cameras from one read of the parameters.
+template <int DEG, bool BF16, bool ONE, bool COUNT>
 __global__ __launch_bounds__(256) void project_fwd_kernel(ProjectFwdArgs a)
 {
     constexpr int K = (DEG + 1) * (DEG + 1);
@@ -252,10 +255,11 @@ __global__ __launch_bounds__(256) void project_fwd_kernel(ProjectFwdArgs a)
     for (int v0 = 0; v0 < n_views; v0 += kCamChunk) {
     const int nv = n_views - v0 < kCamChunk ? n_views - v0 : kCamChunk;
     stage_cams(s_cam, a.cams, v0, nv);
-    if (!active) continue;
+    if (!COUNT && !active) continue;
     for (int v = v0; v < v0 + nv; ++v) {
         const CamDev& c = s_cam[v - v0];
-        size_t o = (size_t)v * a.n + i;
+        const bool store = !COUNT || (active && v >= a.store_from);
+        size_t o = (size_t)(COUNT ? v - a.store_from : v) * a.n + i;
         ViewProj P;
         view_proj(c, mu, L, a.flags, P);
         uint32_t tt = 0;
@@ -283,6 +287,7 @@ __global__ __launch_bounds__(256) void project_fwd_kernel(ProjectFwdArgs a)
                 rc = make_uint2((uint32_t)x0 | ((uint32_t)x1 << 16), (uint32_t)y0 | ((uint32_t)y1 << 16));
             }
             // colour along the viewing direction
+            if (store) {
             float dx = mu[0] - c.campos[0], dy = mu[1] - c.campos[1], dz = mu[2] - c.campos[2];
             float idn = 1.f / sqrtf(dx * dx + dy * dy + dz * dz);
             float Y[K];
@@ -308,6 +313,15 @@ __global__ __launch_bounds__(256) void project_fwd_kernel(ProjectFwdArgs a)
             const float kr = (float)(-(double)B2 / (2.0 * (double)C2));
             const float kc = (float)(-(double)B2 / (2.0 * (double)A2));
             r2 = make_float4(col[2], (float)Lc, kr, kc);
+            }
+        }
+        if (COUNT) {
+            uint64_t sum = active ? tt : 0u;
+#pragma unroll
+            for (int w = 32; w > 0; w >>= 1) sum += __shfl_xor(sum, w, 64);
+            if ((threadIdx.x & 63u) == 0u)
+                a.count[(size_t)v * 4u * gridDim.x + 4u * blockIdx.x + (threadIdx.x >> 6)] = sum;
+            if (!store) continue;
         }
         a.rec[3 * o + 0] = r0;
         a.rec[3 * o + 1] = r1;
@@ -641,12 +655,36 @@ __global__ __launch_bounds__(256, ONE ? 3 : 2) void project_bwd_kernel(ProjectBw
     }
 }
 
+// one workgroup a view: the sum of its n counts
+__global__ __launch_bounds__(256) void count_reduce_kernel(const uint64_t* count, uint32_t n, uint64_t* total)
+{
+    __shared__ uint64_t s_w[256 / 64];
+    const uint64_t* c = count + (size_t)blockIdx.x * n;
+    uint64_t sum = 0;
+    for (uint32_t b0 = threadIdx.x; b0 < n; b0 += 8u * 256u) {
+        uint64_t v[8];
+#pragma unroll
+        for (uint32_t k = 0; k < 8u; ++k) v[k] = b0 + k * 256u < n ? c[b0 + k * 256u] : 0u;
+#pragma unroll
+        for (uint32_t k = 0; k < 8u; ++k) sum += v[k];
+    }
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) sum += __shfl_xor(sum, w, 64);
+    if ((threadIdx.x & 63u) == 0u) s_w[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) total[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+}
+
 template <int DEG, bool BF16>
 hipError_t fwd_dispatch(const ProjectFwdArgs& a, hipStream_t s)
 {
     dim3 grid((a.n + 255u) / 256u);
-    if (a.n_views == 1) hipLaunchKernelGGL((project_fwd_kernel<DEG, BF16, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((project_fwd_kernel<DEG, BF16, false>), grid, dim3(256), 0, s, a);
+    if (a.count) {
+        hipLaunchKernelGGL((project_fwd_kernel<DEG, BF16, false, true>), grid, dim3(256), 0, s, a);
+        hipLaunchKernelGGL(count_reduce_kernel, dim3((unsigned)a.n_views), dim3(256), 0, s, a.count, 4u * grid.x,
+                           a.count_total);
+    } else if (a.n_views == 1) hipLaunchKernelGGL((project_fwd_kernel<DEG, BF16, true, false>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((project_fwd_kernel<DEG, BF16, false, false>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

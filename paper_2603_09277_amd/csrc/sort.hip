@@ -921,12 +921,6 @@ __global__ __launch_bounds__(kThreads) void seg_fixup_kernel(const SegCarry* car
 }
 
 
-__global__ void iota_u32_kernel(uint32_t* p, uint32_t count)
-{
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = i;
-}
-
 // a frame's first kernel: pair count and overflow cleared, the row stamp advanced,
 // and the tile ranges (plus the tile-order class counts behind them) cleared
 __global__ void frame_begin_kernel(uint32_t* counters, uint32_t* ranges, uint32_t n_tiles, uint32_t n_words)
@@ -1076,14 +1070,6 @@ hipError_t launch_grad_reduce(const float* pair_grad, const uint32_t* pair_stamp
                        reinterpret_cast<const SegCarry*>(carry), total, cap, stamp, grad2d, rec_stamp);
     return hipGetLastError();
 }
-
-hipError_t launch_iota_u32(uint32_t* p, uint32_t count, hipStream_t s)
-{
-    if (count == 0) return hipSuccess;
-    hipLaunchKernelGGL(iota_u32_kernel, dim3((count + 255) / 256), dim3(256), 0, s, p, count);
-    return hipGetLastError();
-}
-
 
 hipError_t launch_frame_begin(uint32_t* counters, uint32_t* ranges, uint32_t n_tiles, uint32_t n_words, hipStream_t s)
 {

@@ -91,3 +91,25 @@ def test_projection_backward_rounds(n, deg, bf16, views, shift):
         d, w = (got[k].double() - want[k]).norm().item(), want[k].norm().item()
         assert w > 0 and d <= (2.0 ** -8 if bf16 and k == "sh" else 1e-5) * w, (k, d / w)
     r.close()
+
+
+@pytest.mark.parametrize("n", [1, 255, 1025])
+def test_pair_counts_of_several_cameras(n):
+    scene, t = _small_scene(n, 1)
+    opts = gsr.RasterOptions(sh_degree=1)
+    cams = scenes.orbit_cameras(np.random.default_rng(3), [(200, 120), (33, 17), (640, 480)])
+    p = [t[k] for k in ATTRS]
+    r = gsr.Rasterizer(max_views=3)
+    r.forward(*p, cams, opts)
+    want, tt = r.stats(3)["pairs_per_view"], r.inspect(gsr.BUF_TILES_TOUCHED)
+    assert r.pair_counts(*p, cams, opts) == want
+    assert np.array_equal(r.inspect(gsr.BUF_TILES_TOUCHED), tt)      # the records of every view
+    # r_max: each factor's mean list length, and the last factor's records
+    _, means = r.select_rmax(*p, cams[2], opts, 5, 1e-9)
+    last = r.inspect(gsr.BUF_TILES_TOUCHED)
+    for k in range(1, 6):
+        cam = gsr.scaled_camera(cams[2], k)
+        (cnt,) = r.pair_counts(*p, [cam], opts)
+        assert means[k - 1] == cnt / (-(-cam.width // 16) * -(-cam.height // 16))
+    assert np.array_equal(last, r.inspect(gsr.BUF_TILES_TOUCHED))
+    r.close()

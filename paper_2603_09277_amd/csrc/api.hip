@@ -462,6 +462,7 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
         ba.shared_batches = (L.n_tiles > 0 && p_est >= kSharedBatchMeanLen * (double)L.n_tiles) ? 1 : 0;
         c->long_lists = ba.shared_batches != 0;
     }
+    ba.slotted = slotted_blend(L.n_blocks, vn) ? 1 : 0;
     {
         StageTimer tm(c, st, GSR_STAGE_BLEND_FWD, !c->capturing);
         HIP_TRY(c, launch_blend_fwd(ba, o->lds_batch == 0 ? 64 : o->lds_batch, st));
@@ -509,6 +510,7 @@ gsr_status enqueue_backward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, 
     bb.queues = persist ? (uint32_t*)c->queues.p + kQueues * kQueueStride : nullptr;
     bb.tile_order = persist ? nullptr : (const uint32_t*)c->tile_order.p;
     bb.block_cnt = (uint4*)c->block_cnt.p;
+    bb.slotted = slotted_blend(L.n_blocks, vn) ? 1 : 0;
     if (persist) HIP_TRY(c, launch_fill_u32(bb.queues, 0u, kQueues * kQueueStride, st));
     // backward window: at most 128 entries; on long lists 64, whose smaller per-window LDS
     // (records and per-wavefront sums) lets more wavefronts stay resident (the walk of a long

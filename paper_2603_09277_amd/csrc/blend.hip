@@ -589,6 +589,305 @@ __global__ __launch_bounds__(256) void blend_fwd_shared_kernel(BlendFwdArgs a)
     }
 }
 
+// ---------------------------------------------------------------------------
+// The slotted forms, forward and backward: four list entries a step.
+//
+// A launch of few tiles ends with its longest list's walk, one entry after another, on
+// a chip that is mostly idle by then.  Here a wavefront owns a 4x4 pixel block and the
+// four lanes of a quad take four consecutive surviving entries of one pixel: everything
+// that does not depend on the entries before runs four entries wide, and the walk's serial
+// part (the transmittance, backward also Q) is four multiply steps over the quad by DPP,
+// in list order, with the arithmetic of the plain forms: alphas, transmittances, stops
+// and n_contrib are bit-identical to theirs, and so are colour and entropy (a quad's lanes
+// accumulate one channel each, the fourth the entropy, in list order).  The 16 wavefronts of a 16x16 / 32x8 tile
+// (4 of an 8x8 tile) share the staged records.  A step of 4 entries at 16 pixels costs 1.3
+// times the instructions of one entry at 64 pixels and its latency is about that of
+// one; the finer cull gives most of the throughput back.  Bound by the latency of the
+// longest list's steps (LDS reads, exp, the quad's chain), forward / backward at 16x16
+// tiles, plain -> slotted: 2k Gaussians at 128x128, 27 -> 13 / 52 -> 25 us; 200k at 256x160,
+// 718 -> 170 / 955 -> 425 us; 200k at 640x416, 207 -> 79 / 347 -> 167 us; 150k at 801x533 in
+// 8x8 tiles, 118 -> 55 / 187 -> 79 us.
+// ---------------------------------------------------------------------------
+constexpr int kSlotBatch = 256;          // entries a forward batch
+
+// value of quad lane I in every lane of the quad
+template <int I>
+__device__ __forceinline__ float quad_f(float v)
+{
+    return dpp_f<0x55 * I, 0xf>(v);
+}
+
+template <int I>
+__device__ __forceinline__ int32_t quad_i(int32_t v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, 0x55 * I, 0xf, 0xf, true);
+}
+
+// v[slot], slot = this lane's place in its quad
+__device__ __forceinline__ float by_slot(uint32_t slot, float v0, float v1, float v2, float v3)
+{
+    const float lo = slot & 1u ? v1 : v0, hi = slot & 1u ? v3 : v2;
+    return slot & 2u ? hi : lo;
+}
+
+// Geometry of a wavefront's 4x4 block: quarter wid % 4 of 8x8 block wb.  g8: the 8x8 block
+// (its rectangle); g: the 4x4 block's rectangle and this lane's pixel.
+__device__ __forceinline__ void slot_geom(const CamDev* cams, int n_views, uint32_t wb, uint32_t wid, uint32_t lane,
+                                          int tsx, int tsy, int spt, BlockGeom& g8, BlockGeom& g)
+{
+    const uint32_t q = wid & 3u, p = lane >> 2;
+    g8 = block_geom(cams, n_views, wb, 0u, tsx, tsy, spt);
+    const CamDev& c = cams[g8.view];
+    g = g8;
+    const int x0 = g8.px + 4 * (int)(q & 1u), y0 = g8.py + 4 * (int)(q >> 1);
+    g.px = x0 + (int)(p & 3u);
+    g.py = y0 + (int)(p >> 2);
+    g.inside = g.px < c.W && g.py < c.H;
+    g.pix = c.pix_base + (int64_t)g.py * c.W + g.px;
+    g.cx0 = (float)x0 + 0.5f;
+    g.cy0 = (float)y0 + 0.5f;
+    g.cx1 = (float)min(x0 + 3, c.W - 1) + 0.5f;
+    g.cy1 = (float)min(y0 + 3, c.H - 1) + 0.5f;
+}
+
+constexpr uint64_t kSlot0 = 0x1111111111111111ull;          // the first lane of every quad
+
+// the entries of a slotted walk whose colours are not finite: taken by the lanes that
+// blend them only (a zero weight times infinity must not reach the others)
+__device__ __forceinline__ bool odd_colour(float r, float g, float b)
+{
+    return !(fabsf(r) + fabsf(g) + fabsf(b) < __builtin_inff());
+}
+
+// Forward: a workgroup of 4 wavefronts an 8x8 block, also where a tile has 4 of them (each
+// stages the tile's list for itself: the blocks of a tile need not wait for each other, and
+// five workgroups a CU hide more than one of 16 wavefronts did: 200k Gaussians at 640x416,
+// 79 against 104 us)
+template <bool RENDER>
+__global__ __launch_bounds__(256) void blend_fwd_slot_kernel(BlendFwdArgs a)
+{
+    constexpr int B = kSlotBatch, NW = 4;
+    constexpr int kPart = B + 1;                             // records a part: the last is empty (opacity 0)
+    constexpr int kEmptyOff = 16 * B;
+    __shared__ float4 s_rec[2][3 * kPart];
+    // each wavefront's surviving entries (byte offsets in a part), in list order, and up to 8
+    // empty ones (read a step ahead)
+    __shared__ int32_t s_idx[NW][B + 8];
+    __shared__ uint64_t s_keep[NW];                          // the 8x8 block's survivors, entries 64 w ..
+    __shared__ uint32_t s_open[NW];
+    __shared__ uint32_t s_cnt[NW][4];
+    __shared__ float s_h[64];                                // entropy of the 8x8 block's pixels
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wid = tid >> 6, slot = lane & 3u;
+    const uint32_t item = blockIdx.x / (uint32_t)a.spt;      // longest tiles first
+    const uint32_t wb = (a.tile_order ? a.tile_order[item] : item) * (uint32_t)a.spt + blockIdx.x % (uint32_t)a.spt;
+    BlockGeom g8, g;
+    slot_geom(a.cams, a.n_views, wb, wid, lane, a.tile_shift_x, a.tile_shift_y, a.spt, g8, g);
+    const uint2 rg = a.ranges[g8.tile];
+    const float fpx = (float)g.px + 0.5f, fpy = (float)g.py + 0.5f;
+    const uint64_t lt_mask = (1ull << lane) - 1ull;
+    if (tid < 6u) s_rec[tid / 3u][(tid % 3u) * kPart + B] = make_float4(0.f, 0.f, 0.f, 0.f);
+    // byte offset, from an entry's first part, of the colour channel this lane accumulates
+    const int32_t ch_off = slot == 0u ? 16 * kPart + 8 : (slot == 1u ? 16 * kPart + 12 : 32 * kPart);
+    float T = 1.f, C = 0.f;                                  // C: channel `slot`, of slot 3 the entropy (log2 units)
+    int32_t last = 0, stop_pos = g.inside ? -1 : 0;
+    uint64_t open = __builtin_amdgcn_ballot_w64(g.inside);
+    uint32_t tested = 0u, blended = 0u;
+    // records one batch ahead in registers, record indices two
+    uint32_t pv = 0;
+    float4 n0 = make_float4(0.f, 0.f, 0.f, 0.f), n1 = n0, n2 = n0;
+    if (tid < (uint32_t)B && rg.x + tid < rg.y) {
+        pv = a.emit_vg[a.pair_vals[rg.x + tid]];
+        const float4* r = a.rec + (size_t)kRecF4 * pv;
+        n0 = r[0];
+        n1 = r[1];
+        n2 = r[2];
+    }
+    if (tid < (uint32_t)B && rg.x + B + tid < rg.y) pv = a.emit_vg[a.pair_vals[rg.x + B + tid]];
+    uint32_t buf = 0u;
+    for (uint32_t bs = rg.x; bs < rg.y; bs += B, buf ^= 1u) {
+        const uint32_t cnt = (rg.y - bs) < (uint32_t)B ? (rg.y - bs) : (uint32_t)B;
+        float4* rec = s_rec[buf];
+        if (tid < cnt) {
+            rec[tid] = n0;
+            rec[kPart + tid] = n1;
+            rec[2 * kPart + tid] = n2;
+        }
+        __syncthreads();
+        if (tid < (uint32_t)B && bs + B + tid < rg.y) {
+            const float4* r = a.rec + (size_t)kRecF4 * pv;
+            n0 = r[0];
+            n1 = r[1];
+            n2 = r[2];
+        }
+        if (tid < (uint32_t)B && bs + 2 * B + tid < rg.y) pv = a.emit_vg[a.pair_vals[bs + 2 * B + tid]];
+        // a quarter of the batch against this wavefront's 8x8 block
+        {
+            const uint32_t j = tid;
+            const bool keep = j < cnt && !culled(g8, rec[j], rec[kPart + j].x, rec[2 * kPart + j]);
+            const uint64_t bal = __builtin_amdgcn_ballot_w64(keep);
+            if (lane == 0u) {
+                s_keep[wid] = bal;
+                s_open[wid] = open != 0ull ? 1u : 0u;
+            }
+        }
+        __syncthreads();
+        if ((s_open[0] | s_open[1] | s_open[2] | s_open[3]) == 0u) break;          // every pixel has stopped
+        if (open == 0ull) continue;
+        // the batch's entries that can reach the 4x4 block
+        uint32_t m = 0, m8 = 0;
+        bool odd = false;
+#pragma unroll
+        for (uint32_t h = 0; h < (uint32_t)B / 64u; ++h) {
+            const uint64_t k8 = s_keep[h];
+            const uint32_t j = 64u * h + lane;
+            bool keep = (k8 >> lane) & 1ull;
+            if (keep) {
+                const float4 r1 = rec[kPart + j], r2 = rec[2 * kPart + j];
+                keep = !culled(g, rec[j], r1.x, r2);
+                odd |= keep && odd_colour(r1.z, r1.w, r2.x);
+            }
+            const uint64_t bal = __builtin_amdgcn_ballot_w64(keep);
+            if (keep) s_idx[wid][m + (uint32_t)__popcll(bal & lt_mask)] = (int32_t)(16u * j);
+            m += (uint32_t)__popcll(bal);
+            m8 += (uint32_t)__popcll(k8);
+        }
+        if (lane < 8u) s_idx[wid][m + lane] = kEmptyOff;
+        wave_lds_sync();
+        m = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+        const bool any_odd = __builtin_amdgcn_ballot_w64(odd) != 0ull;
+        const char* base = reinterpret_cast<const char*>(rec);
+        const int32_t pos0 = (int32_t)(bs - rg.x) + 1;
+        // a step's operands, loaded a step ahead
+        int32_t off = s_idx[wid][slot];
+        float4 e0 = *reinterpret_cast<const float4*>(base + off);
+        float2 e1 = *reinterpret_cast<const float2*>(base + off + 16 * kPart);
+        float c0 = *reinterpret_cast<const float*>(base + quad_i<0>(off) + ch_off);
+        float c1 = *reinterpret_cast<const float*>(base + quad_i<1>(off) + ch_off);
+        float c2 = *reinterpret_cast<const float*>(base + quad_i<2>(off) + ch_off);
+        float c3 = *reinterpret_cast<const float*>(base + quad_i<3>(off) + ch_off);
+        for (uint32_t k = 0; k < m; k += 4u) {
+            const int32_t noff = s_idx[wid][k + 4u + slot];
+            const float p = gauss_p2(e0.z, e0.w, e1.x, e0.x - fpx, e0.y - fpy);
+            const float alpha = fminf(kAlphaMax, e1.y * __builtin_amdgcn_exp2f(p));
+            const uint64_t hit = open & __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin);
+            float al = __builtin_amdgcn_inverse_ballot_w64(hit) ? alpha : 0.f;
+            const float4 f0 = *reinterpret_cast<const float4*>(base + noff);
+            const float2 f1 = *reinterpret_cast<const float2*>(base + noff + 16 * kPart);
+            const float d0 = *reinterpret_cast<const float*>(base + quad_i<0>(noff) + ch_off);
+            const float d1 = *reinterpret_cast<const float*>(base + quad_i<1>(noff) + ch_off);
+            const float d2 = *reinterpret_cast<const float*>(base + quad_i<2>(noff) + ch_off);
+            const float d3 = *reinterpret_cast<const float*>(base + quad_i<3>(noff) + ch_off);
+            // the transmittance before and after each of the four entries, in list order
+            float om = 1.f - al;
+            float t1 = T * quad_f<0>(om), t2 = t1 * quad_f<1>(om), t3 = t2 * quad_f<2>(om), t4 = t3 * quad_f<3>(om);
+            uint64_t blend = hit;
+            const int32_t pos1 = pos0 + (off >> 4);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(t4 < kTStop) != 0ull, 0)) {
+                // some pixel stops at one of them: the first hit that would take T below the
+                // threshold, and nothing after it, blends
+                const uint64_t low = __builtin_amdgcn_ballot_w64(by_slot(slot, t1, t2, t3, t4) < kTStop);
+                blend = hit & ~low;
+                uint64_t stop = hit & low;                   // the stopping entry and hits after it
+                al = __builtin_amdgcn_inverse_ballot_w64(blend) ? alpha : 0.f;
+                om = 1.f - al;
+                t1 = T * quad_f<0>(om);
+                t2 = t1 * quad_f<1>(om);
+                t3 = t2 * quad_f<2>(om);
+                t4 = t3 * quad_f<3>(om);
+                const uint32_t mine = (uint32_t)(stop >> (lane & ~3u)) & 0xfu;   // this quad's
+                if (mine != 0u) {
+                    const int first = __ffs((int)mine) - 1;
+                    const int32_t so = first == 0 ? quad_i<0>(off) : first == 1 ? quad_i<1>(off)
+                                       : first == 2 ? quad_i<2>(off) : quad_i<3>(off);
+                    const int32_t j = so >> 4;
+                    stop_pos = pos0 + j - 1;
+                    // the 8x8 block's survivors up to and including the stopping entry
+                    uint32_t t = 0u;
+#pragma unroll
+                    for (int h = 0; h < B / 64; ++h) {
+                        const uint64_t k8 = s_keep[h];
+                        const int32_t r = j - 64 * h;
+                        if (r >= 0) t += (uint32_t)__popcll(r >= 63 ? k8 : k8 & ((2ull << r) - 1ull));
+                    }
+                    if (slot == 0u) tested += t;
+                }
+                open &= ~__builtin_amdgcn_ballot_w64(mine != 0u);
+            }
+            const float w = al * by_slot(slot, T, t1, t2, t3);
+            if (!RENDER) {                                   // -w log2 w (Eq. 10): slot 3's "channel"
+                const float lw = -__builtin_amdgcn_logf(fmaxf(w, 1e-30f));
+                // (moved before the choice: a lane move reads only lanes that execute it)
+                const float l0 = quad_f<0>(lw), l1 = quad_f<1>(lw), l2 = quad_f<2>(lw), l3 = quad_f<3>(lw);
+                c0 = slot == 3u ? l0 : c0;
+                c1 = slot == 3u ? l1 : c1;
+                c2 = slot == 3u ? l2 : c2;
+                c3 = slot == 3u ? l3 : c3;
+            }
+            const float w0 = quad_f<0>(w), w1 = quad_f<1>(w), w2 = quad_f<2>(w), w3 = quad_f<3>(w);
+            if (__builtin_expect(any_odd, 0)) {              // (a zero weight takes no part)
+                if (w0 != 0.f) C = fmaf(w0, c0, C);
+                if (w1 != 0.f) C = fmaf(w1, c1, C);
+                if (w2 != 0.f) C = fmaf(w2, c2, C);
+                if (w3 != 0.f) C = fmaf(w3, c3, C);
+            } else {
+                C = fmaf(w0, c0, C);
+                C = fmaf(w1, c1, C);
+                C = fmaf(w2, c2, C);
+                C = fmaf(w3, c3, C);
+            }
+            if (__builtin_amdgcn_inverse_ballot_w64(blend)) last = pos1;
+            blended += (uint32_t)__popcll(blend);
+            T = t4;
+            off = noff;
+            e0 = f0;
+            e1 = f1;
+            c0 = d0; c1 = d1; c2 = d2; c3 = d3;
+        }
+        // pixels still open tested every survivor of the 8x8 block
+        if (slot == 0u && __builtin_amdgcn_inverse_ballot_w64(open)) tested += m8;
+        wave_lds_sync();
+    }
+    // the quad's entropy and last position
+    const float H = RENDER ? 0.f : kLn2 * fmaf(-T, __builtin_amdgcn_logf(T), quad_f<3>(C));
+    last = max(last, __builtin_amdgcn_update_dpp(0, last, 0xb1, 0xf, 0xf, true));
+    last = max(last, __builtin_amdgcn_update_dpp(0, last, 0x4e, 0xf, 0xf, true));
+    if (g.inside) {
+        if (slot < 3u) a.out_rgb[3 * g.pix + slot] = C;
+        else if (!RENDER) {
+            a.out_H[g.pix] = H;
+            a.out_T[g.pix] = T;
+            a.out_nc[g.pix] = last;
+        }
+    }
+    // the 8x8 block's work counts, and its entropy, summed as the plain forms sum it
+    const bool count = slot == 0u && g.inside;
+    const int32_t n_eval = !count ? 0 : (stop_pos >= 0 ? stop_pos + 1 : (int32_t)(rg.y - rg.x));
+    const uint32_t ne = (uint32_t)wave_sum_all_i(n_eval), nc = (uint32_t)wave_sum_all_i(count ? last : 0);
+    const uint32_t tf = (uint32_t)wave_sum_all_i((int32_t)tested);
+    if (!RENDER && slot == 0u)
+        s_h[8 * (g.py & 7) + (g.px & 7)] = g.inside ? H : 0.f;
+    if (lane == 0u) {
+        s_cnt[wid][0] = ne;
+        s_cnt[wid][1] = nc;
+        s_cnt[wid][2] = blended;
+        s_cnt[wid][3] = tf;
+    }
+    __syncthreads();
+    if (wid == 0u) {
+        const float h = RENDER ? 0.f : wave_sum_all(s_h[lane]);
+        if (lane == 0u) {
+            uint32_t s[4] = { 0u, 0u, 0u, 0u };
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s[k] += s_cnt[w][k];
+            if (!RENDER) a.block_H[wb] = h;
+            a.block_cnt[2 * wb] = make_uint4(s[0], s[1], s[2], 0u);
+            a.block_cnt[2 * wb + 1] = make_uint4(s[3], 0u, 0u, 0u);
+        }
+    }
+}
+
 // Per-lane state of the backward walk of one pixel.  The per-pixel sums the
 // backward needs, S_{i+1} = sum_{k>i} w_k c_k (colour, Eq. 13-14) and Alg. 1's
 // R_{i+1} = sum_{k>i} (ln w_k + 1) w_k + (ln T + 1) T (entropy, Eq. 15), only
@@ -975,6 +1274,231 @@ __global__ __launch_bounds__(256, (SHARED && B <= 64 && !PERSIST) ? 8 : 1) void 
     }
 }
 
+// The slotted backward: windows of 64 entries from the back, the slots of a quad in walk
+// order.  T and Q pass from slot to slot by DPP (T with the plain form's arithmetic); the 9
+// terms of the four entries are summed over the 16 pixels together, by lane swaps and row
+// rotations, into one row of LDS an entry and wavefront.
+// DENSE: held to 64 VGPRs (a few bytes spill), so that two workgroups of 16 wavefronts
+// share a CU.
+template <int SPT, bool DENSE>
+__global__ __launch_bounds__(256 * SPT, DENSE ? 8 : 1) void blend_bwd_slot_kernel(BlendBwdArgs a)
+{
+    constexpr int B = 64, NW = 4 * SPT;
+    constexpr int kPart = B + 1;                             // records a part: the last is empty (opacity 0)
+    constexpr int kEmptyOff = 16 * B;
+    __shared__ float4 s_rec[3 * kPart];                      // two buffers, as two arrays (see blend_bwd_kernel)
+    __shared__ float4 s_rec2[3 * kPart];
+    __shared__ uint32_t s_e[B], s_e2[B];
+    __shared__ float s_acc[NW][(B + 4) * kG2];               // each wavefront's sums of its surviving entries
+    __shared__ int32_t s_idx[NW][B + 8];                     // their byte offsets, last first, and empty ones
+    __shared__ uint64_t s_keep[NW], s_hit[NW];               // surviving entries; of those, the blended ones
+    __shared__ uint64_t s_keep8[SPT];                        // the 8x8 blocks' survivors (work counts)
+    __shared__ int32_t s_max[NW];
+    __shared__ uint32_t s_tested[NW];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wid = tid >> 6, slot = lane & 3u;
+    const uint32_t stamp = *a.stamp;
+    const uint32_t tile = a.tile_order ? a.tile_order[blockIdx.x] : blockIdx.x;
+    BlockGeom g8, g;
+    slot_geom(a.cams, a.n_views, tile * SPT + (SPT == 4 ? wid >> 2 : 0u), wid, lane, a.tile_shift_x, a.tile_shift_y, SPT,
+              g8, g);
+    const uint2 rg = a.ranges[tile];
+    BwdPix q;
+    bwd_init(a, g, (int32_t)(rg.y - rg.x), q);
+    const int32_t wave_n = __builtin_amdgcn_readfirstlane(wave_max_i32(q.n));
+    if (lane == 0u) s_max[wid] = wave_n;
+    if (tid < 3u) s_rec[tid * kPart + B] = s_rec2[tid * kPart + B] = make_float4(0.f, 0.f, 0.f, 0.f);
+    __syncthreads();
+    const int32_t maxn = __builtin_amdgcn_readfirstlane(wave_max_i32(s_max[lane % NW]));
+    uint32_t tested = 0u;
+
+    const int32_t nwin = (maxn + B - 1) / B;
+    auto win_lo = [&](int32_t x) { const int32_t l = maxn - (x + 1) * B; return l > 0 ? l : 0; };
+    auto win_cnt = [&](int32_t x) { const int32_t c = maxn - x * B; return c < B ? c : B; };
+    // the first wavefront fetches the windows, as in blend_bwd_kernel
+    uint32_t e1 = 0u, v1 = 0u, e2 = 0u;
+    const int32_t t = (int32_t)tid;
+    auto load_window = [&](float4* rec_b, uint32_t* e_b, int32_t x) {
+        if (t < win_cnt(x)) {
+            const float4* r = a.rec + (size_t)kRecF4 * v1;
+#pragma unroll
+            for (int k = 0; k < kRecF4; ++k) lds_direct_load16(r + k, &rec_b[k * kPart]);
+            e_b[t] = e1;
+        }
+    };
+    auto window = [&](float4* rec_w, uint32_t* e_w, float4* rec_n, uint32_t* e_n, int32_t w) {
+        const int32_t lo = win_lo(w), cnt = win_cnt(w);
+        if (w + 1 < nwin) load_window(rec_n, e_n, w + 1);
+        if (w + 2 < nwin && t < win_cnt(w + 2)) {
+            v1 = a.emit_vg[e2];
+            e1 = e2;
+        }
+        if (w + 3 < nwin && t < win_cnt(w + 3)) e2 = a.pair_vals[rg.x + (uint32_t)(win_lo(w + 3) + t)];
+        // this wavefront's surviving entries, last first; each 8x8 block's by one of its wavefronts in turn
+        const int32_t jtop = (wave_n - lo) < cnt ? (wave_n - lo) : cnt;
+        const float4 r0 = rec_w[lane], r2 = rec_w[2 * kPart + lane];
+        const float rc = rec_w[kPart + lane].x;
+        const bool kept = (int32_t)lane < jtop && !culled(g, r0, rc, r2);
+        const uint64_t keep = __builtin_amdgcn_ballot_w64(kept);
+        const int32_t m = (int32_t)__popcll(keep);
+        if (kept) s_idx[wid][__popcll((keep >> lane) >> 1)] = 16 * (int32_t)lane;
+        if (lane < 8u) s_idx[wid][m + (int32_t)lane] = kEmptyOff;
+        if ((wid & 3u) == ((uint32_t)w & 3u)) {
+            const uint64_t k8 = __builtin_amdgcn_ballot_w64((int32_t)lane < cnt && !culled(g8, r0, rc, r2));
+            if (lane == 0u) s_keep8[wid >> 2] = k8;
+        }
+        wave_lds_sync();
+        const int32_t nrel = 16 * (q.n - lo);                // entries below it lie in this pixel's list
+        uint64_t hits = 0ull;
+        if (m > 0) {
+            const char* base = reinterpret_cast<const char*>(rec_w);
+            int32_t off = s_idx[wid][slot];
+            float4 g0 = *reinterpret_cast<const float4*>(base + off);
+            float4 g1 = *reinterpret_cast<const float4*>(base + off + 16 * kPart);
+            float cb = *reinterpret_cast<const float*>(base + off + 32 * kPart);
+            for (int32_t k = 0; k < m; k += 4) {
+                const int32_t noff = s_idx[wid][k + 4 + (int32_t)slot];
+                const BwdAlpha al = bwd_alpha(q, off, nrel, g0, g1);
+                const uint64_t act = __builtin_amdgcn_ballot_w64(al.act);
+                const float4 h0 = *reinterpret_cast<const float4*>(base + noff);
+                const float4 h1 = *reinterpret_cast<const float4*>(base + noff + 16 * kPart);
+                const float hb = *reinterpret_cast<const float*>(base + noff + 32 * kPart);
+                if (act != 0ull) {
+                    const float alpha = al.act ? al.alpha : 0.f;
+                    const float rom = __builtin_amdgcn_rcpf(1.f - alpha);
+                    // T_{i+1} and T_i = T_{i+1} / (1 - alpha_i) of every slot, in walk order
+                    const float t1 = q.T * quad_f<0>(rom), t2 = t1 * quad_f<1>(rom);
+                    const float t3 = t2 * quad_f<2>(rom), t4 = t3 * quad_f<3>(rom);
+                    const float wt = alpha * by_slot(slot, t1, t2, t3, t4);
+                    const float lw2 = __builtin_amdgcn_logf(al.act ? wt : 1.f);
+                    const float D = fmaf(-q.ghl, lw2, fmaf(q.gCr, g1.z, fmaf(q.gCg, g1.w, fmaf(q.gCb, cb, -q.gh))));
+                    const float wd = wt * D;
+                    const float q1 = q.Q - quad_f<0>(wd), q2 = q1 - quad_f<1>(wd);
+                    const float q3 = q2 - quad_f<2>(wd), q4 = q3 - quad_f<3>(wd);
+                    const float dal = rom * fmaf(by_slot(slot, q.T, t1, t2, t3), D, by_slot(slot, q.Q, q1, q2, q3));
+                    const float dg = (al.act & (al.a_raw <= kAlphaMax)) ? dal : 0.f;
+                    q.T = t4;
+                    q.Q = q4;
+                    float o[kG2];
+                    o[0] = al.e2 * dg;
+                    o[1] = o[0] * al.dx;
+                    o[2] = o[0] * al.dy;
+                    o[3] = o[1] * al.dx;
+                    o[4] = o[1] * al.dy;
+                    o[5] = o[2] * al.dy;
+                    o[6] = wt * q.gCr;
+                    o[7] = wt * q.gCg;
+                    o[8] = wt * q.gCb;
+                    // sums over the 16 pixels, a slot a lane: halves and rows fold in pairs (row r ends
+                    // with o[row_comp(r)] in x0, o[4 + row_comp(r)] in x1, o[8] in x2), then lanes 4
+                    // and 8 apart
+                    const float u0 = fold_halves(o[0], o[1]), u1 = fold_halves(o[2], o[3]);
+                    const float u2 = fold_halves(o[4], o[5]), u3 = fold_halves(o[6], o[7]);
+                    const float u4 = fold_halves(o[8], o[8]);
+                    float x0 = fold_rows(u0, u1), x1 = fold_rows(u2, u3), x2 = fold_rows(u4, u4);
+                    x0 += dpp_f<0x128, 0xf>(x0);
+                    x1 += dpp_f<0x128, 0xf>(x1);
+                    x2 += dpp_f<0x128, 0xf>(x2);
+                    x0 += dpp_f<0x124, 0xf>(x0);
+                    x1 += dpp_f<0x124, 0xf>(x1);
+                    x2 += dpp_f<0x124, 0xf>(x2);
+                    if ((lane & 15u) < 4u) {
+                        float* dst = &s_acc[wid][(k + (int32_t)slot) * kG2];
+                        dst[row_comp(lane >> 4)] = x0;
+                        dst[4 + row_comp(lane >> 4)] = x1;
+                        if (lane < 4u) dst[8] = x2;
+                    }
+                    uint64_t b = act | (act >> 32);          // the slots some pixel blended
+                    b |= b >> 16;
+                    b |= b >> 8;
+                    b |= b >> 4;
+                    hits |= (b & 0xfull) << k;
+                }
+                off = noff;
+                g0 = h0;
+                g1 = h1;
+                cb = hb;
+            }
+        }
+        if (lane == 0u) {
+            s_keep[wid] = keep;
+            s_hit[wid] = hits;
+        }
+        __syncthreads();
+        if (slot == 0u) {
+            const int32_t nw = q.n - lo;
+            const uint64_t k8 = s_keep8[wid >> 2];
+            tested += nw <= 0 ? 0u : (uint32_t)__popcll(nw >= B ? k8 : k8 & ((1ull << nw) - 1ull));
+        }
+        // the rows of the window's blended entries: NW lanes an entry, lane r for wavefront
+        // r's sums, added in a fixed order (the tree of the lanes)
+        {
+            const int32_t j = (int32_t)(tid / (uint32_t)NW);
+            const uint32_t r = tid % (uint32_t)NW;
+            const uint64_t kr = s_keep[r] >> j;
+            float S[kG2 + 1];
+#pragma unroll
+            for (int k = 0; k <= kG2; ++k) S[k] = 0.f;
+            if (kr & 1ull) {
+                const int32_t c = (int32_t)__popcll(kr >> 1);
+                if ((s_hit[r] >> c) & 1ull) {
+                    const float* src = &s_acc[r][c * kG2];
+#pragma unroll
+                    for (int k = 0; k < kG2; ++k) S[k] = src[k];
+                    S[kG2] = 1.f;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k <= kG2; ++k) {
+                S[k] += dpp_f<0xb1, 0xf>(S[k]);              // quad_perm [1,0,3,2]
+                S[k] += dpp_f<0x4e, 0xf>(S[k]);              // quad_perm [2,3,0,1]
+                if (NW == 16) {
+                    S[k] += dpp_f<0x141, 0xf>(S[k]);         // row_half_mirror
+                    S[k] += dpp_f<0x140, 0xf>(S[k]);         // row_mirror
+                }
+            }
+            if (S[kG2] != 0.f) {
+                float G[kG2];
+                finish_row(S, rec_w[j], rec_w[kPart + j], G);
+                const uint32_t e = e_w[j];
+                float* row = a.pair_grad + (size_t)kRowF * e;
+                if (r < 4u) {
+                    const float2 part = r == 0u ? make_float2(G[0], G[1]) : r == 1u ? make_float2(G[2], G[3])
+                                        : r == 2u ? make_float2(G[4], G[5]) : make_float2(G[6], G[7]);
+                    reinterpret_cast<float2*>(row)[r] = part;
+                    if (r == 0u) row[8] = G[8];
+                    if (r == 1u) a.pair_stamp[e] = stamp;
+                }
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0);                       // the next window's direct loads have landed
+        __syncthreads();
+    };
+    if (nwin > 0) {
+        if (t < win_cnt(0)) {
+            e1 = a.pair_vals[rg.x + (uint32_t)(win_lo(0) + t)];
+            v1 = a.emit_vg[e1];
+        }
+        load_window(s_rec, s_e, 0);
+    }
+    if (nwin > 1 && t < win_cnt(1)) {
+        e1 = a.pair_vals[rg.x + (uint32_t)(win_lo(1) + t)];
+        v1 = a.emit_vg[e1];
+    }
+    if (nwin > 2 && t < win_cnt(2)) e2 = a.pair_vals[rg.x + (uint32_t)(win_lo(2) + t)];
+    __builtin_amdgcn_s_waitcnt(0);                           // this thread's direct loads have landed
+    __syncthreads();
+    for (int32_t w = 0; w < nwin; w += 2) {
+        window(s_rec, s_e, s_rec2, s_e2, w);
+        if (w + 1 < nwin) window(s_rec2, s_e2, s_rec, s_e, w + 1);
+    }
+    const uint32_t nt = (uint32_t)wave_sum_all_i((int)tested);
+    if (lane == 0u) s_tested[wid] = nt;
+    __syncthreads();
+    if (tid < (uint32_t)SPT)
+        reinterpret_cast<uint32_t*>(a.block_cnt + 2 * (tile * SPT + tid) + 1)[1] =
+            s_tested[4u * tid] + s_tested[4u * tid + 1u] + s_tested[4u * tid + 2u] + s_tested[4u * tid + 3u];
+}
+
 // Debug check of Eq. 9 (GSR_DEBUG_INVARIANTS): the weights of the blended Gaussians and
 // the background weight T_final sum to one.  An independent per-pixel walk: one thread
 // per pixel re-evaluates its tile's list from the front, with the forward's alpha
@@ -1091,7 +1615,9 @@ template <int B, bool RENDER>
 hipError_t fwd_launch(const BlendFwdArgs& a, hipStream_t s)
 {
     const uint32_t groups = (a.n_blocks + kWavesPerGroup - 1) / kWavesPerGroup;
-    if (a.spt == 4 && a.shared_batches) {  // one tile per workgroup, batches shared by its 4 blocks
+    if (a.slotted) {                       // one 8x8 block per workgroup, a wavefront per 4x4 block
+        hipLaunchKernelGGL(blend_fwd_slot_kernel<RENDER>, dim3(a.n_blocks), dim3(256), 0, s, a);
+    } else if (a.spt == 4 && a.shared_batches) {  // one tile per workgroup, batches shared by its 4 blocks
         if (a.queues)
             hipLaunchKernelGGL((blend_fwd_shared_kernel<B, true, RENDER>),
                                dim3(resident_groups(blend_fwd_shared_kernel<B, true, RENDER>, groups)), dim3(256), 0,
@@ -1150,6 +1676,17 @@ hipError_t launch_blend_fwd(const BlendFwdArgs& a, int lds_batch, hipStream_t s)
 hipError_t launch_blend_bwd(const BlendBwdArgs& a, int lds_batch, hipStream_t s)
 {
     if (a.n_blocks == 0) return hipSuccess;
+    if (a.slotted) {
+        // dense from 6 tiles a CU (640x416, 200k Gaussians, 4,160 blocks: 167 us, dense 207;
+        // 960x640, 9,600 blocks: 204 us, dense 162; at 6,600 blocks alike)
+        if (a.spt == 4 && a.n_blocks > 6144u)
+            hipLaunchKernelGGL((blend_bwd_slot_kernel<4, true>), dim3(a.n_blocks / 4u), dim3(1024), 0, s, a);
+        else if (a.spt == 4)
+            hipLaunchKernelGGL((blend_bwd_slot_kernel<4, false>), dim3(a.n_blocks / 4u), dim3(1024), 0, s, a);
+        else
+            hipLaunchKernelGGL((blend_bwd_slot_kernel<1, false>), dim3(a.n_blocks), dim3(256), 0, s, a);
+        return hipGetLastError();
+    }
     switch (lds_batch) {
         case 32: return bwd_b<32>(a, s);
         case 64: return bwd_b<64>(a, s);

@@ -50,6 +50,21 @@ constexpr int kRecF4 = 3;
 // 1296x840, mean 211, per block 0.105 vs shared 0.116 ms; 1M at 1600x1060, mean
 // 1025, 0.232 vs 0.184 ms; its half-scale variant, mean 495, per block 0.244 ms)
 constexpr double kSharedBatchMeanLen = 256.0;
+// The blend's slotted form (four wavefronts an 8x8 block instead of one, see blend.hip): up
+// to kSlotBlocks blocks, ten plain wavefronts a SIMD, below which the plain walks of the
+// longest lists end on an idle chip; and, beyond 2,048 blocks, where lists are not so
+// short that starting four wavefronts a block costs more than their walks (from two
+// records a block).  Both sides, 16x16 tiles, forward / backward in us: 9,600 blocks,
+// 200k Gaussians 131 -> 96 / 243 -> 162, 1M 252 -> 247 / 377 -> 329; 17,010 blocks, 200k
+// 99 -> 137 / 179 -> 228 (plain); 6,600 blocks, 5k (0.8 records a block) 15 -> 25 / 19 -> 29
+// (plain); 2,688 blocks, 5k 17 -> 14 / 27 -> 18.  It depends on sizes alone, so that every
+// mode takes the same form for the same frame.
+constexpr uint32_t kSlotBlocks = 10240;
+constexpr uint32_t kSlotFewBlocks = 2048;
+inline bool slotted_blend(uint32_t n_blocks, uint32_t records)
+{
+    return n_blocks <= kSlotFewBlocks || (n_blocks <= kSlotBlocks && records / 2u >= n_blocks);
+}
 // persistent blend kernels: one work queue per XCD, heads 128 bytes apart
 constexpr uint32_t kQueues = 8;
 constexpr uint32_t kQueueStride = 32;
@@ -135,6 +150,7 @@ struct BlendFwdArgs {
     int32_t render_only;                  // 1: colour only (no entropy, no saved state)
     const uint32_t* tile_order;           // [n_tiles] tiles, longest list first (hardware dispatch); or null
     int32_t shared_batches;               // 16x16 / 32x8 tiles: stage each batch once for the 4 blocks
+    int32_t slotted;                      // the slotted form (queues unused: a workgroup a tile)
 };
 
 struct BlendBwdArgs {
@@ -159,6 +175,7 @@ struct BlendBwdArgs {
     const uint32_t* tile_order;           // [n_tiles] tiles, longest list first (hardware dispatch); or null
     uint4* block_cnt;                     // the forward's block counts: word 1 of [2 wb + 1] gets the
                                           //   backward's alpha tests of block wb
+    int32_t slotted;                      // the slotted form (queues unused: a workgroup a tile)
 };
 
 // Debug check of Eq. 9 after a forward (GSR_DEBUG_INVARIANTS): per pixel, the sum of

@@ -113,3 +113,58 @@ def test_pair_counts_of_several_cameras(n):
         assert means[k - 1] == cnt / (-(-cam.width // 16) * -(-cam.height // 16))
     assert np.array_equal(last, r.inspect(gsr.BUF_TILES_TOUCHED))
     r.close()
+
+
+def _bits(t):
+    return t.contiguous().view(torch.int32)
+
+
+STATS = ("pairs", "evals_fwd", "evals_bwd", "blended", "tested_fwd", "tested_bwd")
+
+
+# The blend's slotted form (few 8x8 blocks) against the plain form, which the same view takes
+# beside a view of 26,600 blocks: 4x4 blocks, 8x8 blocks and tiles cut by the image, one batch
+# (256 entries) and window (64) and several, rays that stop, infinite colours, empty tiles.
+# Forward outputs and work counts are equal bit by bit; gradients sum the same FP32 terms in another
+# order (relative L2 1e-5).
+@pytest.mark.parametrize("tile", [(16, 16), (8, 8), (32, 8)])
+@pytest.mark.parametrize("size,n,scale", [((1, 1), 40, 1.0), ((5, 3), 300, 3.0), ((33, 31), 63, 1.0), ((33, 31), 700, 2.0),
+                                          ((64, 48), 3000, 4.0), ((203, 117), 500, 0.5)])
+def test_slotted_blend_equals_plain(tile, size, n, scale):
+    scene, t = _small_scene(n, 1)
+    t["scales"] = t["scales"] * scale
+    if n == 700:
+        t["sh"][::97] = 3e38                  # colours that overflow
+    (cam,) = scenes.orbit_cameras(np.random.default_rng(8), [size])
+    (big,) = scenes.orbit_cameras(np.random.default_rng(9), [(1600, 1060)])
+    opts = gsr.RasterOptions(tile=tile, lds_batch=64, sh_degree=1)
+    p = [t[k] for k in ATTRS]
+    m, mb = cam.width * cam.height, big.width * big.height
+    gen = torch.Generator(DEV).manual_seed(4)
+    g_rgb, g_h = torch.randn(m, 3, device=DEV, generator=gen), torch.randn(m, device=DEV, generator=gen)
+    g_em = torch.full((1,), 0.3, device=DEV)
+    r = gsr.Rasterizer(max_views=2)
+    out = r.forward(*p, [cam], opts)
+    one = {k: out[k].clone() for k in ("rgb", "entropy", "t_final", "n_contrib", "entropy_mean")}
+    got = r.backward(*p, [cam], opts, out, g_rgb, g_h, g_em)
+    st = r.stats(1)
+    image = r.render_image(*p, [cam], opts)
+    # the plain form: both views, and the large one alone for its work counts
+    out = r.forward(*p, [cam, big], opts)
+    zeros = torch.zeros(mb, 3, device=DEV)
+    want = r.backward(*p, [cam, big], opts, out, torch.cat([g_rgb, zeros]), torch.cat([g_h, zeros[:, 0]]),
+                      torch.cat([g_em, 0 * g_em]))
+    both = r.stats(2)
+    ob = r.forward(*p, [big], opts)
+    r.backward(*p, [big], opts, ob, zeros, zeros[:, 0].contiguous(), 0 * g_em)
+    alone = r.stats(1)
+    for k in ("rgb", "entropy", "t_final", "n_contrib"):
+        assert torch.equal(_bits(one[k]), _bits(out[k][:m])), k
+    assert torch.equal(_bits(image), _bits(one["rgb"]))
+    assert torch.equal(_bits(one["entropy_mean"]), _bits(out["entropy_mean"][:1]))
+    assert {k: st[k] for k in STATS} == {k: both[k] - alone[k] for k in STATS}
+    if n != 700:
+        for k in ATTRS:
+            d, w = (got[k].double() - want[k].double()).norm().item(), want[k].double().norm().item()
+            assert d <= 1e-5 * w, (k, d, w)
+    r.close()

@@ -166,8 +166,9 @@ gsr_status gsr_pixel_offsets(const gsr_camera* cams, int32_t n_views, int64_t* o
 
 /* Render n_views cameras (host array) and their entropy (Sec. 3, Eq. 3-5,
  * 8-11).  In plain mode the call synchronises once on `stream` to size the
- * pair buffers; with GSR_GRAPH or GSR_NO_SYNC it does not (after the first
- * frame of the mode on this context). */
+ * pair buffers, unless n times the tiles of all views is at most 2^19 (they are
+ * then sized for that bound); with GSR_GRAPH or GSR_NO_SYNC it does not (after
+ * the first frame of the mode on this context). */
 gsr_status gsr_forward(gsr_ctx* ctx, void* stream, const gsr_gaussians* g, const gsr_camera* cams,
                        int32_t n_views, const gsr_opts* opts, gsr_fwd_out* out);
 

@@ -48,6 +48,11 @@ hipError_t scratch_address(int dev, void** out)
 
 namespace {
 
+// plain mode: frames of at most this many (record, tile) combinations are sized for all of
+// them (34 MB of scratch) and need no count on the host: the synchronisation left the GPU
+// idle for longer than such a frame's sort takes
+constexpr uint64_t kBoundPairs = 1u << 19;
+
 struct Dev {
     void* p = nullptr;
     size_t bytes = 0;
@@ -69,7 +74,7 @@ struct FrameKey {
 
 struct Layout {
     std::vector<CamDev> cams;
-    uint32_t n_tiles = 0, n_blocks = 0, n_hchunks = 0, n_l1 = 0;
+    uint32_t n_tiles = 0, n_blocks = 0, n_hchunks = 0, n_l1 = 0, max_blocks = 0;   // max_blocks: of one view
     int64_t n_pix = 0;
     int tsx = 0, tsy = 0, spt = 1;
 };
@@ -289,6 +294,7 @@ Layout make_layout(const gsr_camera* cams, int32_t n_views, const gsr_opts* o)
         d.pix_base = pb;
         d.hred_base = hb;
         d.l1_base = lb;
+        L.max_blocks = std::max(L.max_blocks, d.n_wblocks);
         hb += (d.n_wblocks + kRedChunk - 1) / kRedChunk;
         lb += (uint32_t)(((int64_t)k.width * k.height + kL1Pix - 1) / kL1Pix);
         tb += (uint32_t)(d.gx * d.gy);
@@ -354,11 +360,14 @@ gsr_status ensure_tiles(gsr_ctx* c, uint32_t tiles, uint32_t blocks)
     return GSR_OK;
 }
 
-// everything of the forward after the camera upload; `plain` = read the pair
-// count back and size the pair buffers for it (one host synchronisation), with
-// `headroom` at 1.5x the count + 4096 for later fixed-capacity frames
+// The whole forward.  Its cameras go up with the first kernel's arguments (more than fit
+// there by a copy); under capture the caller copies them from pinned memory instead.
+// `plain` = read the pair count back and size the pair buffers for it (one host
+// synchronisation), with `headroom` at 1.5x the count + 4096 for later fixed-capacity frames;
+// with `bounded` a frame that cannot have more than kBoundPairs pairs is sized for that bound
+// instead and the count stays on the device.
 gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, const gsr_opts* o, gsr_fwd_out* out,
-                           bool plain, bool render_only = false, bool headroom = false)
+                           bool plain, bool render_only = false, bool headroom = false, bool bounded = false)
 {
     const Layout& L = c->lay;
     const uint32_t n = (uint32_t)g->n, V = (uint32_t)L.cams.size(), vn = n * V;
@@ -367,7 +376,11 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
     // pair count and overflow cleared; a new stamp for the per-pair gradient rows of
     // this frame's backward (every backward of one forward writes the same rows: the
     // entries some pixel blended); the tile ranges and tile-order class counts cleared
-    HIP_TRY(c, launch_frame_begin(counters, (uint32_t*)c->ranges.p, L.n_tiles, L.n_tiles * 2u + kTileHistWords, st));
+    const int packed = !c->capturing && V <= (uint32_t)kCamPack ? (int)V : 0;
+    if (!c->capturing && !packed)
+        HIP_TRY(c, hipMemcpyAsync(c->cams.p, L.cams.data(), sizeof(CamDev) * V, hipMemcpyHostToDevice, st));
+    HIP_TRY(c, launch_frame_begin(counters, (uint32_t*)c->ranges.p, L.n_tiles, L.n_tiles * 2u + kTileHistWords,
+                                  L.cams.data(), packed, (CamDev*)c->cams.p, st));
 
     ProjectFwdArgs pa;
     pa.means = g->means; pa.scales = g->scales; pa.quats = g->quats; pa.opac = g->opacities; pa.sh = g->sh;
@@ -381,24 +394,36 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
         HIP_TRY(c, launch_project_fwd(pa, o->sh_degree, o->sh_dtype == 1, st));
     }
 
-    // depth order of all (view, Gaussian) records: 4 LSD passes of 8 bits
+    // depth order of all (view, Gaussian) records: 4 LSD passes of 8 bits; offsets of each
+    // record's pairs in that order; total pair count
     uint32_t* dk[2] = { (uint32_t*)c->dkey0.p, (uint32_t*)c->dkey1.p };
     uint32_t* od[2] = { (uint32_t*)c->ord0.p, (uint32_t*)c->ord1.p };
+    const bool small = vn > 0 && vn <= kSmallBin;
     {
         StageTimer tm(c, st, GSR_STAGE_DEPTH_SORT, !c->capturing);
-        for (int pass = 0; pass < 4; ++pass)               // the first pass's values are the record indices
-            HIP_TRY(c, launch_radix_pass(dk[pass & 1], pass ? od[pass & 1] : nullptr, dk[(pass + 1) & 1],
-                                         od[(pass + 1) & 1], nullptr, vn, 8 * pass, (uint32_t*)c->radix_tmp.p, st));
+        if (small)                                          // with the scan
+            HIP_TRY(c, launch_small_bin(dk[0], (const uint2*)c->rect.p, vn, od[0], (uint32_t*)c->offsets.p,
+                                        (uint32_t*)c->tt_s.p, (uint2*)c->rect_s.p, counters, counters + 1, st));
+        else
+            for (int pass = 0; pass < 4; ++pass)           // the first pass's values are the record indices
+                HIP_TRY(c, launch_radix_pass(dk[pass & 1], pass ? od[pass & 1] : nullptr, dk[(pass + 1) & 1],
+                                             od[(pass + 1) & 1], nullptr, vn, 8 * pass, (uint32_t*)c->radix_tmp.p, st));
     }
-    // offsets of each record's pairs in depth order; total pair count
-    {
+    if (!small) {
         StageTimer tm(c, st, GSR_STAGE_SCAN, !c->capturing);
         HIP_TRY(c, launch_gather_scan((const uint2*)c->rect.p, od[0], vn,
                                       (uint32_t*)c->offsets.p, (uint32_t*)c->tt_s.p, (uint2*)c->rect_s.p, counters,
                                       counters + 1, (uint32_t*)c->scan_tmp.p, st));
     }
     uint32_t cap;
-    if (plain) {
+    const uint64_t most = (uint64_t)n * L.n_tiles;          // every record in every tile of its view
+    bounded = bounded && most <= kBoundPairs;
+    if (bounded) {
+        plain = false;
+        gsr_status s;
+        if ((s = ensure_pairs(c, (size_t)most)) || (s = ensure_radix_tmp(c, std::max<size_t>(c->pair_cap, vn)))) return s;
+        cap = (uint32_t)most;
+    } else if (plain) {
         HIP_TRY(c, hipMemcpyAsync(c->counters_host, counters, 8, hipMemcpyDeviceToHost, st));
         HIP_TRY(c, hipStreamSynchronize(st));
         if (c->counters_host[1]) return fail(c, GSR_ERR_CAPACITY, "pair count exceeds 2^32");
@@ -435,10 +460,10 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
     const bool persist = (o->flags & GSR_PERSISTENT) != 0;
     {
         StageTimer tm(c, st, GSR_STAGE_RANGES, !c->capturing);
-        HIP_TRY(c, launch_ranges_finish((uint2*)c->ranges.p, L.n_tiles, st));
         // hardware dispatch visits the tiles longest list first (persistent kernels keep their queues)
-        if (!persist)
-            HIP_TRY(c, launch_tile_order((const uint2*)c->ranges.p, L.n_tiles, (uint32_t*)c->ranges.p + 2 * (size_t)L.n_tiles,
+        if (persist) HIP_TRY(c, launch_ranges_finish((uint2*)c->ranges.p, L.n_tiles, st));
+        else
+            HIP_TRY(c, launch_tile_order((uint2*)c->ranges.p, L.n_tiles, (uint32_t*)c->ranges.p + 2 * (size_t)L.n_tiles,
                                          (uint32_t*)c->tile_order.p, st));
         // the persistent blend kernels' queue heads (forward and backward sets)
         if (persist) HIP_TRY(c, launch_fill_u32((uint32_t*)c->queues.p, 0u, 2 * kQueues * kQueueStride, st));
@@ -456,9 +481,9 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
     ba.tile_order = persist ? nullptr : (const uint32_t*)c->tile_order.p;
     // long lists: the 4 blocks of a tile share each staged batch; short lists: each
     // block stages its own and leaves as soon as its pixels have stopped (a fixed
-    // capacity is 1.5x a frame's pairs, hence the estimate)
+    // capacity is 1.5x a frame's pairs, hence the estimate; a bounded one, about 4 a record)
     {
-        const double p_est = plain ? (double)cap : (double)cap / 1.5;
+        const double p_est = bounded ? 4.0 * vn : plain ? (double)cap : (double)cap / 1.5;
         ba.shared_batches = (L.n_tiles > 0 && p_est >= kSharedBatchMeanLen * (double)L.n_tiles) ? 1 : 0;
         c->long_lists = ba.shared_batches != 0;
     }
@@ -469,7 +494,8 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
     }
     if (!render_only) {
         StageTimer tm(c, st, GSR_STAGE_ENTROPY_MEAN, !c->capturing);
-        HIP_TRY(c, launch_entropy_mean((const float*)c->block_H.p, dc, (int)V, L.n_hchunks, (double*)c->hchunk.p,
+        HIP_TRY(c, launch_entropy_mean((const float*)c->block_H.p, dc, (int)V, L.n_hchunks, L.max_blocks,
+                                       (double*)c->hchunk.p,
                                        out->entropy_mean, st));
     }
     if (!render_only && (o->flags & GSR_DEBUG_INVARIANTS)) {    // Eq. 9 per pixel, reported by gsr_stats
@@ -572,19 +598,15 @@ gsr_status wait_replay(gsr_ctx* c)
     return GSR_OK;
 }
 
-// GSR_NO_SYNC forward: the capacity path of graph mode, launched eagerly.  The
-// camera upload goes through pinned memory and the frame's pair count comes back
-// asynchronously into counters_host; ev_replay (waited for by the next call that
-// touches either host buffer) covers both.
+// GSR_NO_SYNC forward: the capacity path of graph mode, launched eagerly.  The frame's
+// pair count comes back asynchronously into counters_host; ev_replay (waited for by the
+// next call that touches it or the cameras' host copy) covers both.
 gsr_status enqueue_nosync(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, const gsr_opts* o, gsr_fwd_out* out,
                           bool render_only)
 {
-    const Layout& L = c->lay;
-    const size_t cam_bytes = sizeof(CamDev) * L.cams.size();
     gsr_status s;
     if (!c->nosync_ready) {                          // first such frame: exact sizing, then head room
         // (the buffers grow before the pairs are written, so this frame's state stays valid)
-        HIP_TRY(c, hipMemcpyAsync(c->cams.p, L.cams.data(), cam_bytes, hipMemcpyHostToDevice, st));
         if ((s = enqueue_forward(c, st, g, o, out, true, render_only, true))) return s;
         c->nosync_count = false;
         c->nosync_ready = true;
@@ -599,8 +621,6 @@ gsr_status enqueue_nosync(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, co
                 return s;
         }
     }
-    std::memcpy(c->cams_host, L.cams.data(), cam_bytes);
-    HIP_TRY(c, hipMemcpyAsync(c->cams.p, c->cams_host, cam_bytes, hipMemcpyHostToDevice, st));
     if ((s = enqueue_forward(c, st, g, o, out, false, render_only))) return s;
     HIP_TRY(c, hipMemcpyAsync(c->counters_host, c->counters.p, 8, hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipEventRecord(c->ev_replay, st));
@@ -721,8 +741,7 @@ gsr_status gsr_forward(gsr_ctx* c, void* stream, const gsr_gaussians* g, const g
     if (!graph && (o->flags & GSR_NO_SYNC)) {
         if ((s = enqueue_nosync(c, st, g, o, out, false))) return s;
     } else if (!graph) {
-        HIP_TRY(c, hipMemcpyAsync(c->cams.p, c->lay.cams.data(), sizeof(CamDev) * L.cams.size(), hipMemcpyHostToDevice, st));
-        if ((s = enqueue_forward(c, st, g, o, out, true))) return s;
+        if ((s = enqueue_forward(c, st, g, o, out, true, false, false, true))) return s;
     } else {
         FrameKey k = make_key(g, cams, n_views, o, outs);
         bool recapture = !c->gexec_fwd || !(k == c->key_fwd) || c->gen != c->gen_fwd;
@@ -736,7 +755,6 @@ gsr_status gsr_forward(gsr_ctx* c, void* stream, const gsr_gaussians* g, const g
             // every capture starts from an exact count: one plain forward, then the
             // fixed capacity at 1.5x its pairs + 4096 (the buffers only grow)
             drop_graphs(c);
-            HIP_TRY(c, hipMemcpyAsync(c->cams.p, c->lay.cams.data(), sizeof(CamDev) * L.cams.size(), hipMemcpyHostToDevice, st));
             if ((s = enqueue_forward(c, st, g, o, out, true))) return s;
             size_t want = (size_t)c->pairs + c->pairs / 2 + 4096;
             if ((s = ensure_pairs(c, want)) || (s = ensure_radix_tmp(c, std::max<size_t>(c->pair_cap, vn)))) return s;
@@ -810,8 +828,7 @@ gsr_status gsr_render(gsr_ctx* c, void* stream, const gsr_gaussians* g, const gs
     if (o->flags & GSR_NO_SYNC) {
         if ((s = enqueue_nosync(c, st, g, o, &out, true))) return s;
     } else {
-        HIP_TRY(c, hipMemcpyAsync(c->cams.p, c->lay.cams.data(), sizeof(CamDev) * L.cams.size(), hipMemcpyHostToDevice, st));
-        if ((s = enqueue_forward(c, st, g, o, &out, true, true))) return s;
+        if ((s = enqueue_forward(c, st, g, o, &out, true, true, false, true))) return s;
     }
     // a render saves no state: no backward may follow it
     c->frame += 1;

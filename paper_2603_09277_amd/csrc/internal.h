@@ -32,6 +32,12 @@ struct CamDev {
     uint32_t l1_base;              // first L1 block of this view (kL1Block pixels each)
 };
 
+// cameras handed to a kernel by value (its arguments hold 4 KB)
+constexpr int kCamPack = 16;
+struct CamPack {
+    CamDev c[kCamPack];
+};
+
 constexpr int kRedChunk = 1024;    // 8x8 blocks summed per entropy-reduction chunk
 constexpr int kL1Block = 256;      // threads per L1 block
 constexpr int kL1Pix = 4 * kL1Block;   // pixels per L1 block (4 a thread)
@@ -208,6 +214,12 @@ hipError_t launch_gather_scan(const uint2* trect, const uint32_t* order, uint32_
                               uint32_t* vals_s, uint2* rect_s, uint32_t* total, uint32_t* overflow, uint32_t* tmp,
                               hipStream_t s);
 
+// at most kSmallBin records: the depth order of all records (keys) and launch_gather_scan's
+// outputs for it, in one launch
+constexpr uint32_t kSmallBin = 6144;
+hipError_t launch_small_bin(const uint32_t* keys, const uint2* trect, uint32_t n, uint32_t* order, uint32_t* out,
+                            uint32_t* vals_s, uint2* rect_s, uint32_t* total, uint32_t* overflow, hipStream_t s);
+
 // one stable LSD radix pass of 8 bits at `shift` over (key, value) pairs; the
 // item count is min(*n_dev, n_max) read on the device (n_dev may be null: n_max);
 // vals_in null: the values are the items' indices.  ranges non-null: the last pass
@@ -240,15 +252,16 @@ hipError_t launch_grad_reduce(const float* pair_grad, const uint32_t* pair_stamp
 
 // a forward's counters: pair total and overflow flag cleared, row stamp (counters[4]) advanced;
 // the n_tiles tile bounds in ranges set to (0xffffffff, 0), the words after them up to
-// ranges[n_words) cleared
+// ranges[n_words) cleared; n_cams (at most kCamPack) cameras stored to `cams`
 hipError_t launch_frame_begin(uint32_t* counters, uint32_t* ranges, uint32_t n_tiles, uint32_t n_words,
-                              hipStream_t s);
+                              const CamDev* host_cams, int n_cams, CamDev* cams, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t count, hipStream_t s);
-// order[n_tiles]: the tiles by decreasing list length (16 classes per octave);
+// tiles without pairs set to [0, 0), then order[n_tiles]: the tiles by decreasing list length
+// (16 classes per octave);
 // hist: 512 words, zeroed (bucket counts, then bucket fill counters)
 constexpr uint32_t kTileHistWords = 512;
-hipError_t launch_tile_order(const uint2* ranges, uint32_t n_tiles, uint32_t* hist, uint32_t* order, hipStream_t s);
-// tiles that the last tile-sort pass gave no bounds (no pairs): [0, 0)
+hipError_t launch_tile_order(uint2* ranges, uint32_t n_tiles, uint32_t* hist, uint32_t* order, hipStream_t s);
+// tiles that the last tile-sort pass gave no bounds (no pairs): [0, 0) (persistent scheduling, which takes no order)
 hipError_t launch_ranges_finish(uint2* ranges, uint32_t n_tiles, hipStream_t s);
 
 
@@ -285,7 +298,8 @@ hipError_t launch_scale_reset(float* scales, float* log_scales, int64_t count, f
 hipError_t launch_l1(const float* rgb, const float* target, const CamDev* cams, int n_views, uint32_t n_l1_blocks,
                      float weight, float* grad, float* loss, double* tmp, hipStream_t s);
 // n_chunks = sum over views of ceil(blocks_v / kRedChunk); tmp holds n_chunks doubles
+// max_blocks: the most blocks of one view
 hipError_t launch_entropy_mean(const float* block_H, const CamDev* cams, int n_views, uint32_t n_chunks,
-                               double* tmp, float* out_mean, hipStream_t s);
+                               uint32_t max_blocks, double* tmp, float* out_mean, hipStream_t s);
 
 }  // namespace gsr

@@ -8,6 +8,8 @@
 // sorted over the duplicated pairs (2-3 passes over P items).  The result is
 // exactly the LSD radix sort of the full key: duplication emits pairs in
 // depth-sorted Gaussian order and the tile passes are stable.
+#include <cstring>
+
 #include "internal.h"
 
 namespace gsr {
@@ -642,6 +644,156 @@ __global__ __launch_bounds__(kThreads) void duplicate_kernel(const uint32_t* ord
     }
 }
 
+// ---------------------------------------------------------------------------
+// Few records: the depth sort and the scan in one workgroup of 16 wavefronts, keys and
+// record indices in LDS, in place of 8 sort and 2 scan launches of 3 to 5 us each: 2,000
+// records 44 -> 23 us, 4,096 43 -> 31, 6,000 46 -> 40; 8,192 46 -> 54, so the line is at 6,144.
+// Bound by the ranking rounds of 16 wavefronts on one CU.  The same stable passes; one whose digit is the same in every key is
+// skipped.  Each wavefront ranks a run of consecutive items, as in the downsweep.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kBinThreads = 1024, kBinWaves = kBinThreads / 64;
+constexpr uint32_t kBinItems = kSmallBin / kBinThreads;          // items a thread
+static_assert(kSmallBin % kBinThreads == 0 && kSmallBin <= 65536, "indices are 16 bits");
+
+__global__ __launch_bounds__(kBinThreads) void small_bin_kernel(const uint32_t* keys, const uint2* trect, uint32_t n,
+                                                                uint32_t* order, uint32_t* out, uint32_t* vals_s,
+                                                                uint2* rect_s, uint32_t* total, uint32_t* overflow)
+{
+    __shared__ uint32_t s_key[2][kSmallBin];
+    __shared__ uint16_t s_val[2][kSmallBin];
+    __shared__ uint32_t s_wh[kBinWaves][kBins];
+    __shared__ uint32_t s_wave[kBins / 64];
+    __shared__ unsigned long long s_sum[kBinWaves];
+    __shared__ uint32_t s_or, s_and;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wid = tid >> 6;
+    const uint32_t rounds = (n + kBinThreads - 1u) / kBinThreads;    // of 64 items a wavefront
+    const uint32_t w0 = wid * rounds * 64u;                          // this wavefront's first item
+    if (tid == 0) {
+        s_or = 0u;
+        s_and = 0xffffffffu;
+    }
+    __syncthreads();
+    {
+        uint32_t vo = 0u, va = 0xffffffffu;
+        for (uint32_t i = tid; i < n; i += kBinThreads) {
+            const uint32_t k = keys[i];
+            s_key[0][i] = k;
+            s_val[0][i] = (uint16_t)i;
+            vo |= k;
+            va &= k;
+        }
+        atomicOr(&s_or, vo);
+        atomicAnd(&s_and, va);
+    }
+    __syncthreads();
+    const uint32_t varies = s_or & ~s_and;
+    uint32_t cur = 0u;
+    for (int shift = 0; shift < 32; shift += 8) {
+        if (((varies >> shift) & 0xffu) == 0u) continue;
+        for (uint32_t d = lane; d < (uint32_t)kBins; d += 64u) s_wh[wid][d] = 0u;
+        wave_lds_order();
+        uint32_t k_[kBinItems], rk[kBinItems];
+#pragma unroll
+        for (uint32_t r = 0; r < kBinItems; ++r) {
+            if (r >= rounds) break;
+            const uint32_t li = w0 + r * 64u + lane;
+            const bool ok = li < n;
+            k_[r] = s_key[cur][ok ? li : n - 1u];
+            const uint32_t d = (k_[r] >> shift) & 0xffu;
+            // peers: lanes with the same digit (see radix_downsweep_kernel)
+            const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
+            uint32_t plo = (uint32_t)okm, phi = (uint32_t)(okm >> 32);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const uint32_t m = (uint32_t)((int32_t)(d << (31 - b)) >> 31);
+                const uint64_t bal = __builtin_amdgcn_ballot_w64(m != 0u);
+                plo &= ~((uint32_t)bal ^ m);
+                phi &= ~((uint32_t)(bal >> 32) ^ m);
+            }
+            const uint32_t below = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
+            const uint32_t before = s_wh[wid][d];
+            rk[r] = before + below;
+            wave_lds_order();
+            if (ok && below == 0u) s_wh[wid][d] = before + (uint32_t)__popc(plo) + (uint32_t)__popc(phi);
+            wave_lds_order();
+        }
+        __syncthreads();
+        // starts of the (digit, wavefront) groups, digit-major
+        uint32_t td = 0u, inc = 0u;
+        if (tid < (uint32_t)kBins) {
+            for (uint32_t w = 0; w < kBinWaves; ++w) td += s_wh[w][tid];
+            inc = wave_incl_scan(td);
+            if (lane == 63u) s_wave[wid] = inc;
+        }
+        __syncthreads();
+        if (tid < (uint32_t)kBins) {
+            uint32_t run = inc - td;
+            for (uint32_t w = 0; w < wid; ++w) run += s_wave[w];
+            for (uint32_t w = 0; w < kBinWaves; ++w) {
+                const uint32_t c = s_wh[w][tid];
+                s_wh[w][tid] = run;
+                run += c;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t r = 0; r < kBinItems; ++r) {
+            if (r >= rounds) break;
+            const uint32_t li = w0 + r * 64u + lane;
+            if (li < n) {
+                const uint32_t pos = s_wh[wid][(k_[r] >> shift) & 0xffu] + rk[r];
+                s_key[cur ^ 1u][pos] = k_[r];
+                s_val[cur ^ 1u][pos] = s_val[cur][li];
+            }
+        }
+        __syncthreads();
+        cur ^= 1u;
+    }
+    // tiles touched in depth order, kBinItems consecutive records a thread, and their scan
+    const uint32_t per = rounds;                                     // records a thread
+    uint2 rc[kBinItems];
+    uint32_t vg[kBinItems];
+    unsigned long long sum = 0ull;
+#pragma unroll
+    for (uint32_t r = 0; r < kBinItems; ++r) {
+        const uint32_t i = tid * per + r;
+        if (r < per && i < n) {
+            vg[r] = s_val[cur][i];
+            rc[r] = trect[vg[r]];
+            sum += rect_tiles(rc[r]);
+        }
+    }
+    unsigned long long inc = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long y = __shfl_up(inc, o, 64);
+        if (lane >= (uint32_t)o) inc += y;
+    }
+    if (lane == 63u) s_sum[wid] = inc;
+    __syncthreads();
+    unsigned long long run = inc - sum, all = 0ull;
+    for (uint32_t w = 0; w < kBinWaves; ++w) {
+        if (w < wid) run += s_sum[w];
+        all += s_sum[w];
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kBinItems; ++r) {
+        const uint32_t i = tid * per + r;
+        if (r < per && i < n) {
+            const uint32_t tt = rect_tiles(rc[r]);
+            order[i] = vg[r];
+            out[i] = (uint32_t)run;
+            vals_s[i] = tt;
+            rect_s[i] = rc[r];
+            run += tt;
+        }
+    }
+    if (tid == 0) {
+        *total = all > 0xffffffffull ? 0xffffffffu : (uint32_t)all;
+        if (all > 0xffffffffull) *overflow = 1u;
+    }
+}
+
 // Per-Gaussian sum of the per-pair gradient rows.  Rows (9 floats, 10 apart)
 // are stored in emission order, where all pairs of one (view, Gaussian) are
 // contiguous; a row whose stamp (a separate array) is not this frame's was not
@@ -922,14 +1074,21 @@ __global__ __launch_bounds__(kThreads) void seg_fixup_kernel(const SegCarry* car
 
 
 // a frame's first kernel: pair count and overflow cleared, the row stamp advanced,
-// and the tile ranges (plus the tile-order class counts behind them) cleared
-__global__ void frame_begin_kernel(uint32_t* counters, uint32_t* ranges, uint32_t n_tiles, uint32_t n_words)
+// the tile ranges (plus the tile-order class counts behind them) cleared, and the cameras
+// stored from the kernel's arguments (a copy from host memory of its own cost a small
+// frame 5 us of the stream and as much of the host)
+__global__ void frame_begin_kernel(uint32_t* counters, uint32_t* ranges, uint32_t n_tiles, uint32_t n_words, CamPack pack,
+                                   uint32_t cam_words, uint32_t* cams)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        counters[0] = 0u;
-        counters[1] = 0u;
-        counters[8] = 0u;                     // set when this frame's invariants are checked
-        atomicAdd(&counters[4], 1u);
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) {
+            counters[0] = 0u;
+            counters[1] = 0u;
+            counters[8] = 0u;                 // set when this frame's invariants are checked
+            atomicAdd(&counters[4], 1u);
+        }
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(&pack);
+        for (uint32_t w = threadIdx.x; w < cam_words; w += blockDim.x) cams[w] = src[w];
     }
     // tile bounds (0xffffffff, 0), then the words after them zero
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n_words; i += gridDim.x * blockDim.x)
@@ -975,6 +1134,15 @@ hipError_t launch_gather_scan(const uint2* trect, const uint32_t* order, uint32_
     if (nb > 0)
         hipLaunchKernelGGL(scan_down_kernel<false>, dim3(nb), dim3(kThreads), 0, s, vals_s, n, tmp, nb, out, total,
                            overflow);
+    return hipGetLastError();
+}
+
+hipError_t launch_small_bin(const uint32_t* keys, const uint2* trect, uint32_t n, uint32_t* order, uint32_t* out,
+                            uint32_t* vals_s, uint2* rect_s, uint32_t* total, uint32_t* overflow, hipStream_t s)
+{
+    if (n == 0 || n > kSmallBin) return n == 0 ? hipSuccess : hipErrorInvalidValue;
+    hipLaunchKernelGGL(small_bin_kernel, dim3(1), dim3(kBinThreads), 0, s, keys, trect, n, order, out, vals_s, rect_s,
+                       total, overflow);
     return hipGetLastError();
 }
 
@@ -1071,14 +1239,17 @@ hipError_t launch_grad_reduce(const float* pair_grad, const uint32_t* pair_stamp
     return hipGetLastError();
 }
 
-hipError_t launch_frame_begin(uint32_t* counters, uint32_t* ranges, uint32_t n_tiles, uint32_t n_words, hipStream_t s)
+hipError_t launch_frame_begin(uint32_t* counters, uint32_t* ranges, uint32_t n_tiles, uint32_t n_words,
+                              const CamDev* host_cams, int n_cams, CamDev* cams, hipStream_t s)
 {
     uint32_t blocks = (n_words + 255u) / 256u;
     blocks = blocks < 1u ? 1u : (blocks > 1024u ? 1024u : blocks);
-    hipLaunchKernelGGL(frame_begin_kernel, dim3(blocks), dim3(256), 0, s, counters, ranges, n_tiles, n_words);
+    CamPack pack;
+    if (n_cams > 0) memcpy(pack.c, host_cams, sizeof(CamDev) * (size_t)n_cams);
+    hipLaunchKernelGGL(frame_begin_kernel, dim3(blocks), dim3(256), 0, s, counters, ranges, n_tiles, n_words, pack,
+                       (uint32_t)n_cams * (uint32_t)(sizeof(CamDev) / 4), reinterpret_cast<uint32_t*>(cams));
     return hipGetLastError();
 }
-
 
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t count, hipStream_t s)
 {
@@ -1108,13 +1279,64 @@ __device__ __forceinline__ uint32_t tile_bucket(uint2 r)
     return 255u - (c < 255.f ? (uint32_t)c : 255u);                            // bucket 0: longest
 }
 
-__global__ __launch_bounds__(kThreads) void tile_hist_kernel(const uint2* ranges, uint32_t n_tiles, uint32_t* hist)
+// bounds of a tile without pairs, (0xffffffff, 0) from frame_begin, become [0, 0)
+__device__ __forceinline__ uint2 finish_range(uint2* ranges, uint32_t t, uint2 r)
+{
+    if (r.x == 0xffffffffu) ranges[t] = r = make_uint2(0u, 0u);
+    return r;
+}
+
+// up to kOrderThreads * kOrderPer tiles: the whole counting sort in one workgroup, one launch
+// instead of three
+constexpr uint32_t kOrderThreads = 1024, kOrderPer = 16;
+
+__global__ __launch_bounds__(kOrderThreads) void tile_order_one_kernel(uint2* ranges, uint32_t n_tiles, uint32_t* order)
+{
+    __shared__ uint32_t s_cnt[256], s_wave[4];
+    const uint32_t tid = threadIdx.x;
+    if (tid < 256u) s_cnt[tid] = 0u;
+    uint2 r[kOrderPer];                                      // every load in flight before the first is used
+#pragma unroll
+    for (uint32_t k = 0; k < kOrderPer; ++k) {
+        const uint32_t t = k * kOrderThreads + tid;
+        if (k * kOrderThreads < n_tiles) r[k] = ranges[t < n_tiles ? t : n_tiles - 1u];
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kOrderPer; ++k) {
+        const uint32_t t = k * kOrderThreads + tid;
+        if (t < n_tiles) r[k] = finish_range(ranges, t, r[k]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < kOrderPer; ++k)
+        if (k * kOrderThreads + tid < n_tiles) atomicAdd(&s_cnt[tile_bucket(r[k])], 1u);
+    __syncthreads();
+    uint32_t mine = 0u, inc = 0u;
+    if (tid < 256u) {
+        mine = s_cnt[tid];
+        inc = wave_incl_scan(mine);
+        if ((tid & 63u) == 63u) s_wave[tid >> 6] = inc;
+    }
+    __syncthreads();
+    if (tid < 256u) {
+        for (uint32_t w = 0; w < (tid >> 6); ++w) inc += s_wave[w];
+        s_cnt[tid] = inc - mine;                             // the class's next place
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < kOrderPer; ++k) {
+        const uint32_t t = k * kOrderThreads + tid;
+        if (t < n_tiles) order[atomicAdd(&s_cnt[tile_bucket(r[k])], 1u)] = t;
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void tile_hist_kernel(uint2* ranges, uint32_t n_tiles, uint32_t* hist)
 {
     __shared__ uint32_t h[256];
     h[threadIdx.x] = 0u;
     __syncthreads();
     for (uint32_t t = blockIdx.x * kThreads + threadIdx.x; t < n_tiles; t += gridDim.x * kThreads)
-        atomicAdd(&h[tile_bucket(ranges[t])], 1u);
+        atomicAdd(&h[tile_bucket(finish_range(ranges, t, ranges[t]))], 1u);
     __syncthreads();
     if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
 }
@@ -1154,9 +1376,13 @@ __global__ __launch_bounds__(kThreads) void tile_order_kernel(const uint2* range
 
 }  // namespace
 
-hipError_t launch_tile_order(const uint2* ranges, uint32_t n_tiles, uint32_t* hist, uint32_t* order, hipStream_t s)
+hipError_t launch_tile_order(uint2* ranges, uint32_t n_tiles, uint32_t* hist, uint32_t* order, hipStream_t s)
 {
     if (n_tiles == 0) return hipSuccess;
+    if (n_tiles <= kOrderThreads * kOrderPer) {
+        hipLaunchKernelGGL(tile_order_one_kernel, dim3(1), dim3(kOrderThreads), 0, s, ranges, n_tiles, order);
+        return hipGetLastError();
+    }
     uint32_t grid = (n_tiles + kThreads - 1) / kThreads;
     if (grid > 1024) grid = 1024;
     hipLaunchKernelGGL(tile_hist_kernel, dim3(grid), dim3(kThreads), 0, s, ranges, n_tiles, hist);

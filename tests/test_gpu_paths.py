@@ -168,3 +168,25 @@ def test_slotted_blend_equals_plain(tile, size, n, scale):
             d, w = (got[k].double() - want[k].double()).norm().item(), want[k].double().norm().item()
             assert d <= 1e-5 * w, (k, d, w)
     r.close()
+
+
+# Binning: one workgroup up to 6,144 records (1,024 threads, whole rounds and remainders), the
+# radix passes beyond; equal depths, one depth for all.  Every tile's list holds each record
+# once per tile it touches, in (depth, index) order.
+@pytest.mark.parametrize("n", [1, 63, 65, 1023, 1024, 1025, 4097, 6143, 6144, 6145])
+@pytest.mark.parametrize("depths", ["all", "few", "one"])
+def test_lists_of_few_records(n, depths):
+    scene, t = _small_scene(n, 0)
+    if depths != "all":
+        t["means"][:] = t["means"][torch.arange(n, device=DEV) % (7 if depths == "few" else 1)].clone()
+    cams = scenes.orbit_cameras(np.random.default_rng(8), [(150, 70)])
+    r = gsr.Rasterizer(max_views=1)
+    r.forward(*[t[k] for k in ATTRS], cams, gsr.RasterOptions(sh_degree=0))
+    vals, ranges = r.inspect(gsr.BUF_PAIR_VALUES).astype(np.int64), r.inspect(gsr.BUF_RANGES).reshape(-1, 2).astype(np.int64)
+    tt, depth = r.inspect(gsr.BUF_TILES_TOUCHED), r.inspect(gsr.BUF_DEPTH)
+    assert len(vals) == tt.sum() == (ranges[:, 1] - ranges[:, 0]).sum()
+    assert np.array_equal(np.bincount(vals, minlength=n), tt)
+    for a, b in ranges:
+        order = np.lexsort((vals[a:b], depth[vals[a:b]]))
+        assert np.array_equal(order, np.arange(b - a)) and len(set(vals[a:b])) == b - a
+    r.close()

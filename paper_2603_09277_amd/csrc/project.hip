@@ -575,18 +575,21 @@ __global__ __launch_bounds__(256, ONE ? 3 : 2) void project_bwd_kernel(ProjectBw
     float M[9];
     for (int r = 0; r < 3; ++r)
         for (int j = 0; j < 3; ++j) M[3 * r + j] = R[3 * r + j] * s[j];
-    float gR[9], gs[3] = { 0.f, 0.f, 0.f };
+    // (the sums that cancel are written as the multiply-adds they are, so that their
+    // rounding is not the compiler's choice of what to fuse)
+    float gR[9], gs[3] = { 0.f, 0.f, 0.f }, gm = 0.f;
     for (int r = 0; r < 3; ++r)
         for (int j = 0; j < 3; ++j) {
-            float gm = 2.f * (G[3 * r] * M[j] + G[3 * r + 1] * M[3 + j] + G[3 * r + 2] * M[6 + j]);
+            gm = 2.f * fmaf(G[3 * r + 2], M[6 + j], fmaf(G[3 * r + 1], M[3 + j], G[3 * r] * M[j]));
             gs[j] += gm * R[3 * r + j];
             gR[3 * r + j] = gm * s[j];
         }
+    const float gR48 = fmaf(gm, s[2], gR[4]);                // gR[4] + gR[8]
     // ---- rotation -> normalised quaternion -> raw quaternion
     float gw = 2.f * (-z * gR[1] + y * gR[2] + z * gR[3] - x * gR[5] - y * gR[6] + x * gR[7]);
-    float gx = 2.f * (y * gR[1] + z * gR[2] + y * gR[3] - w * gR[5] + z * gR[6] + w * gR[7]) -
-               4.f * x * (gR[4] + gR[8]);
-    float gy = 2.f * (x * gR[1] + w * gR[2] + x * gR[3] + z * gR[5] - w * gR[6] + z * gR[7]) -
+    float gx = 2.f * (fmaf(y, gR[1], z * gR[2]) + y * gR[3] - w * gR[5] + z * gR[6] + w * gR[7]) -
+               4.f * x * gR48;
+    float gy = 2.f * (fmaf(x, gR[1], w * gR[2]) + x * gR[3] + z * gR[5] - w * gR[6] + z * gR[7]) -
                4.f * y * (gR[0] + gR[8]);
     float gz = 2.f * (-w * gR[1] + x * gR[2] + w * gR[3] + y * gR[5] + x * gR[6] + y * gR[7]) -
                4.f * z * (gR[0] + gR[4]);

@@ -38,17 +38,20 @@ __device__ __forceinline__ double block_sum_f64(double x)
 // 3) over a segment of rows and marches down it 8 rows at a time, so that the only
 // traffic beyond the images, the gradient and their halos is LDS: per 8 rows
 //   1. the rows' x and y (band + 10 pixels either side), loaded one step ahead, into LDS;
-//   2. horizontal window sums of x, y, x^2 + y^2 and xy (the map needs the two variances
-//      only as their sum), a thread per (row, channel, 8-pixel strip): 18 values read
-//      for 8 outputs of 11 taps;
-//   3. vertical sums, a thread per float column, the 10 rows before the new ones kept in
-//      registers; the SSIM map's terms and its three partials, zero outside the image;
+//   2. horizontal window sums of x^2 and y^2, then of x, y and xy, a thread per (row,
+//      channel, 8-pixel strip): 18 values read for 8 outputs of 11 taps;
+//   3. after each, vertical sums, a thread per float column, the 10 rows before the new ones
+//      kept in registers; the SSIM map's terms and its three partials, zero outside the image;
 //   4. horizontal sums of the partials, as 2;  5. vertical sums, as 3, and the gradient.
 // Bound by its FMAs and LDS reads, not by memory.  The separable passes over whole
 // images that this replaces (5 launches a view, 33 floats a pixel of scratch, every tap
 // of an array of structures from L2) took 1.58 ms on 8 views of 9.76 Mpixel together and
-// 0.23 ms on one 1296x840 image; this takes 0.42 ms (1.1 TB/s of images and gradient) and
-// 0.077 ms.  VALU issue is 0.56 of its rate at three workgroups a CU (0.46 at two).
+// 0.23 ms on one 1296x840 image; this takes 0.43 to 0.47 ms (1.0 TB/s of images and gradient) and
+// 0.085 ms, with the same roundings in the same order.  The five horizontal sums go through
+// three planes of LDS in two parts, and loads are issued late, so that three workgroups
+// fit a CU in LDS and registers (the prefetch before the first part: 0.62 ms, spilled).
+// One window of x^2 + y^2 in place of two took 0.42 ms, but its last bits differ, and the
+// scale and rotation gradients of some Gaussians, which cancel, showed that a thousandfold.
 constexpr int kStep = 8;                       // rows a step
 constexpr int kBandPx = 64;                    // output pixels across a band
 constexpr int kOutF = 3 * kBandPx;             // its float columns
@@ -91,11 +94,11 @@ __global__ __launch_bounds__(kThr, 3) void ssim_kernel(const float* x, const flo
     constexpr int kStrips1 = (kMapF + 23) / 24;
     constexpr int kRSin = GRAD ? 275 : 227, kRSh = GRAD ? 243 : 195, kRSp = 227;
     static_assert(24 * kStrips1 + 30 <= kRSin && 24 * kStrips1 <= kRSh && kOutF + 30 <= kRSp, "strips stay in a row");
-    static_assert(3 * kRS2 <= 4 * kRSh, "the second horizontal pass reuses the first one's rows");
+    static_assert(kRS2 <= kRSh, "the second horizontal pass reuses the first one's rows");
     // the input rows and the partials' rows take turns in one array (three workgroups a CU)
     constexpr int kInWords = 2 * kStep * kRSin, kPWords = GRAD ? 3 * kStep * kRSp : 0;
     __shared__ float s_io[kInWords > kPWords ? kInWords : kPWords];
-    __shared__ float s_h[4 * kStep * kRSh];
+    __shared__ float s_h[3 * kStep * kRSh];
     __shared__ double s_sum[kThr / 64];
     const int t = (int)threadIdx.x;
     int v = 0;
@@ -140,9 +143,51 @@ __global__ __launch_bounds__(kThr, 3) void ssim_kernel(const float* x, const flo
             }
         }
     };
-    float old1[4][2 * kHalf], old2[GRAD ? 3 : 1][2 * kHalf];
+    // horizontal window sums of this step's rows: x^2, y^2 (part 0), then x, y, xy (part 1)
+    auto rows = [&](int part) {
+        if (t >= 3 * kStrips1 * kStep) return;
+        float xv[kIn], yv[kIn];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+        for (int k = 0; k < kIn; ++k) {
+            xv[k] = s_io[h1_row * kRSin + h1_c + 3 * k];
+            yv[k] = s_io[(kStep + h1_row) * kRSin + h1_c + 3 * k];
+        }
+        float* h = s_h + h1_row * kRSh + h1_c;
+        auto put_row = [&](int q, const float (&in)[kIn]) {
+            float o[kStep];
+            window8(a.w, in, o);
+#pragma unroll
+            for (int k = 0; k < kStep; ++k) h[q * kStep * kRSh + 3 * k] = o[k];
+        };
+        if (part == 0) {
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) xv[k] *= xv[k];
+            put_row(0, xv);
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) yv[k] *= yv[k];
+            put_row(1, yv);
+        } else {
+            put_row(0, xv);
+            put_row(1, yv);
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) xv[k] *= yv[k];
+            put_row(2, xv);
+        }
+    };
+    // vertical sums of row set q of s_h, `old` the 10 rows before it
+    auto cols = [&](int q, float (&old)[2 * kHalf], float (&m)[kStep]) {
+        float in[kIn];
+#pragma unroll
+        for (int k = 0; k < 2 * kHalf; ++k) in[k] = old[k];
+#pragma unroll
+        for (int j = 0; j < kStep; ++j) in[2 * kHalf + j] = s_h[(q * kStep + j) * kRSh + t];
+        window8(a.w, in, m);
+#pragma unroll
+        for (int k = 0; k < 2 * kHalf; ++k) old[k] = in[kStep + k];
+    };
+    float old1[5][2 * kHalf], old2[GRAD ? 3 : 1][2 * kHalf];
+#pragma unroll
+    for (int q = 0; q < 5; ++q)
 #pragma unroll
         for (int k = 0; k < 2 * kHalf; ++k) old1[q][k] = 0.f;
 #pragma unroll
@@ -156,75 +201,48 @@ __global__ __launch_bounds__(kThr, 3) void ssim_kernel(const float* x, const flo
     // the step of input rows [row, row + 8) completes map rows [row - 5, row + 3) and
     // output rows [row - 10, row - 2)
     for (; row - kHalf - kHalo1 < r1; row += kStep) {
+        float m[5][kStep];
         __syncthreads();
-        if (t < 3 * kStrips1 * kStep) {
-            float xv[kIn], yv[kIn], sv[kIn], pv[kIn], o[kStep];
+        rows(0);
+        __syncthreads();
+        if (t < kMapF) {
 #pragma unroll
-            for (int k = 0; k < kIn; ++k) {
-                xv[k] = s_io[h1_row * kRSin + h1_c + 3 * k];
-                yv[k] = s_io[(kStep + h1_row) * kRSin + h1_c + 3 * k];
-                sv[k] = __fadd_rn(__fmul_rn(xv[k], xv[k]), __fmul_rn(yv[k], yv[k]));
-                pv[k] = xv[k] * yv[k];
-            }
-            float* h = s_h + h1_row * kRSh + h1_c;
-            auto put_row = [&](int q, const float (&in)[kIn]) {
-                window8(a.w, in, o);
-#pragma unroll
-                for (int k = 0; k < kStep; ++k) h[q * kStep * kRSh + 3 * k] = o[k];
-            };
-            put_row(0, xv);
-            put_row(1, yv);
-            put_row(2, sv);
-            put_row(3, pv);
+            for (int q = 0; q < 2; ++q) cols(q, old1[q], m[q]);
         }
-        fetch(row + kStep);
+        __syncthreads();
+        if (!GRAD) fetch(row + kStep);
+        rows(1);
         __syncthreads();
         if (!GRAD) put();                       // (every read of this step's rows is done)
         if (t < kMapF) {
-            float m[4][kStep];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float in[kIn];
-#pragma unroll
-                for (int k = 0; k < 2 * kHalf; ++k) in[k] = old1[q][k];
-#pragma unroll
-                for (int j = 0; j < kStep; ++j) in[2 * kHalf + j] = s_h[(q * kStep + j) * kRSh + t];
-                window8(a.w, in, m[q]);
-#pragma unroll
-                for (int k = 0; k < 2 * kHalf; ++k) old1[q][k] = in[kStep + k];
-            }
+            for (int q = 0; q < 3; ++q) cols(q, old1[2 + q], m[2 + q]);
             const float C1 = 1e-4f, C2 = 9e-4f;
 #pragma unroll
             for (int j = 0; j < kStep; ++j) {
                 const int r = row - kHalf + j;
-                const float mx = m[0][j], my = m[1][j];
-                // products rounded alike on both sides, so that identical images give S = 1
-                const float mxy = __fmul_rn(mx, my), mm = __fadd_rn(__fmul_rn(mx, mx), __fmul_rn(my, my));
-                const float ln = __fadd_rn(2.f * mxy, C1), ld = __fadd_rn(mm, C1);
-                const float cn = __fadd_rn(2.f * __fsub_rn(m[3][j], mxy), C2);
-                const float cd = __fadd_rn(__fsub_rn(m[2][j], mm), C2);
-                const float N = ln * cn, D = ld * cd;
-                const float iD = 1.f / D;
-                if (own_px && r >= r0 && r < r1) sacc += (double)(N * iD);
+                const float mx = m[2][j], my = m[3][j];
+                // (each rounding written out)
+                const float ld = __fadd_rn(fmaf(mx, mx, __fmul_rn(my, my)), C1);
+                const float cd = __fadd_rn(__fadd_rn(fmaf(-mx, mx, m[0][j]), fmaf(-my, my, m[1][j])), C2);
+                const float cn = fmaf(2.f, fmaf(-mx, my, m[4][j]), C2);
+                const float ln = fmaf(2.f * mx, my, C1);
+                const float N = __fmul_rn(ln, cn), D = __fmul_rn(ld, cd);
+                const float iD = 1.f / D, S = __fmul_rn(N, iD);
+                if (own_px && r >= r0 && r < r1) sacc += (double)S;
                 if (GRAD) {
                     const bool ok = map_ok && r >= 0 && r < H;
-                    const float dN = 2.f * my * (cn - ln), dD = 2.f * mx * (cd - ld);
-                    s_io[(0 * kStep + j) * kRSp + t] = ok ? (dN - N * iD * dD) * iD : 0.f;     // dS/dmx
-                    s_io[(1 * kStep + j) * kRSp + t] = ok ? -N * ld * iD * iD : 0.f;           // dS/dExx
-                    s_io[(2 * kStep + j) * kRSp + t] = ok ? 2.f * ln * iD : 0.f;               // dS/dExy
+                    const float dD = __fmul_rn(2.f * mx, __fsub_rn(cd, ld));
+                    const float g0 = __fmul_rn(iD, fmaf(2.f * my, __fsub_rn(cn, ln), -__fmul_rn(dD, S)));
+                    const float g1 = __fmul_rn(iD, __fmul_rn(__fmul_rn(ld, -N), iD));
+                    s_io[(0 * kStep + j) * kRSp + t] = ok ? g0 : 0.f;                          // dS/dmx
+                    s_io[(1 * kStep + j) * kRSp + t] = ok ? g1 : 0.f;                          // dS/dExx
+                    s_io[(2 * kStep + j) * kRSp + t] = ok ? __fmul_rn(2.f * ln, iD) : 0.f;     // dS/dExy
                 }
             }
         }
         if constexpr (GRAD) {
-            float gx[kStep], gy[kStep], gg[kStep];
-#pragma unroll
-            for (int j = 0; j < kStep; ++j) {   // in flight over the second horizontal pass
-                const int r = row - 2 * kHalf + j;
-                const bool ok = out_ok && r >= r0 && r < r1;
-                gx[j] = ok ? x[r * stride + out_c] : 0.f;
-                gy[j] = ok ? y[r * stride + out_c] : 0.f;
-                gg[j] = ok ? grad[r * stride + out_c] : 0.f;
-            }
+            fetch(row + kStep);
             __syncthreads();
             if (t < 24 * kStep) {
 #pragma unroll
@@ -238,9 +256,18 @@ __global__ __launch_bounds__(kThr, 3) void ssim_kernel(const float* x, const flo
                 }
             }
             __syncthreads();
+            float gx[kStep], gy[kStep], gg[kStep];
+#pragma unroll
+            for (int j = 0; j < kStep; ++j) {   // in flight over the vertical pass
+                const int r = row - 2 * kHalf + j;
+                const bool ok = out_ok && r >= r0 && r < r1;
+                gx[j] = ok ? x[r * stride + out_c] : 0.f;
+                gy[j] = ok ? y[r * stride + out_c] : 0.f;
+                gg[j] = ok ? grad[r * stride + out_c] : 0.f;
+            }
             put();                              // (every read of the partials is done)
             if (t < kOutF) {
-                float m[3][kStep];
+                float m2[3][kStep];
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
                     float in[kIn];
@@ -248,7 +275,7 @@ __global__ __launch_bounds__(kThr, 3) void ssim_kernel(const float* x, const flo
                     for (int k = 0; k < 2 * kHalf; ++k) in[k] = old2[q][k];
 #pragma unroll
                     for (int j = 0; j < kStep; ++j) in[2 * kHalf + j] = s_h[(q * kStep + j) * kRS2 + t];
-                    window8(a.w, in, m[q]);
+                    window8(a.w, in, m2[q]);
 #pragma unroll
                     for (int k = 0; k < 2 * kHalf; ++k) old2[q][k] = in[kStep + k];
                 }
@@ -256,8 +283,8 @@ __global__ __launch_bounds__(kThr, 3) void ssim_kernel(const float* x, const flo
                 for (int j = 0; j < kStep; ++j) {
                     const int r = row - 2 * kHalf + j;
                     if (out_ok && r >= r0 && r < r1) {
-                        const float d = m[0][j] + 2.f * gx[j] * m[1][j] + gy[j] * m[2][j];
-                        grad[r * stride + out_c] = gg[j] + vw.scale * d;
+                        const float d = fmaf(gy[j], m2[2][j], fmaf(2.f * gx[j], m2[1][j], m2[0][j]));
+                        grad[r * stride + out_c] = fmaf(vw.scale, d, gg[j]);
                     }
                 }
             }

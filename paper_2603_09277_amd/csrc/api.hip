@@ -405,9 +405,7 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
             HIP_TRY(c, launch_small_bin(dk[0], (const uint2*)c->rect.p, vn, od[0], (uint32_t*)c->offsets.p,
                                         (uint32_t*)c->tt_s.p, (uint2*)c->rect_s.p, counters, counters + 1, st));
         else
-            for (int pass = 0; pass < 4; ++pass)           // the first pass's values are the record indices
-                HIP_TRY(c, launch_radix_pass(dk[pass & 1], pass ? od[pass & 1] : nullptr, dk[(pass + 1) & 1],
-                                             od[(pass + 1) & 1], nullptr, vn, 8 * pass, (uint32_t*)c->radix_tmp.p, st));
+            HIP_TRY(c, launch_depth_sort(dk, od, vn, (uint32_t*)c->radix_tmp.p, st));
     }
     if (!small) {
         StageTimer tm(c, st, GSR_STAGE_SCAN, !c->capturing);
@@ -441,22 +439,15 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
     {
         StageTimer tm(c, st, GSR_STAGE_DUPLICATE, !c->capturing);
         HIP_TRY(c, launch_duplicate(od[0], (const uint32_t*)c->offsets.p, (const uint32_t*)c->tt_s.p,
-                                    (const uint2*)c->rect_s.p, dc, n, vn, counters, cap, pk[0],
+                                    (const uint2*)c->rect_s.p, dc, n, vn, L.n_tiles, counters, cap, pk[0],
                                     (uint32_t*)c->emit_vg.p, counters + 1, st));
     }
-    // stable sort of the pairs by tile id
-    int tile_bits = std::max(1, ilog2((int)std::max<uint32_t>(L.n_tiles, 2)));
-    int passes = (tile_bits + 7) / 8;
+    // stable sort of the pairs by tile id; its last pass records the tile ranges
     {
         StageTimer tm(c, st, GSR_STAGE_TILE_SORT, !c->capturing);
-        // the first pass's values: the emission indices; the last pass records the tile
-        // ranges instead of writing the sorted keys
-        for (int pass = 0; pass < passes; ++pass)
-            HIP_TRY(c, launch_radix_pass(pk[pass & 1], pass ? pv[pass & 1] : nullptr, pk[(pass + 1) & 1],
-                                         pv[(pass + 1) & 1], counters, cap, 8 * pass, (uint32_t*)c->radix_tmp.p, st,
-                                         pass + 1 == passes ? (uint2*)c->ranges.p : nullptr));
+        HIP_TRY(c, launch_tile_sort(pk, pv, L.n_tiles, counters, cap, (uint2*)c->ranges.p, (uint32_t*)c->radix_tmp.p, st));
     }
-    const int sb = passes & 1;
+    const int sb = tile_sort_passes(L.n_tiles) & 1;
     const bool persist = (o->flags & GSR_PERSISTENT) != 0;
     {
         StageTimer tm(c, st, GSR_STAGE_RANGES, !c->capturing);
@@ -791,8 +782,7 @@ gsr_status gsr_forward(gsr_ctx* c, void* stream, const gsr_gaussians* g, const g
         HIP_TRY(c, hipEventRecord(c->ev_replay, st));
         c->replay_pending = true;
         c->pairs = 0;
-        int tile_bits = std::max(1, ilog2((int)std::max<uint32_t>(L.n_tiles, 2)));
-        c->sorted_buf = ((tile_bits + 7) / 8) & 1;
+        c->sorted_buf = tile_sort_passes(L.n_tiles) & 1;
         c->graph_frame = c->frame + 1;
     }
     c->frame += 1;

@@ -220,24 +220,28 @@ constexpr uint32_t kSmallBin = 6144;
 hipError_t launch_small_bin(const uint32_t* keys, const uint2* trect, uint32_t n, uint32_t* order, uint32_t* out,
                             uint32_t* vals_s, uint2* rect_s, uint32_t* total, uint32_t* overflow, hipStream_t s);
 
-// one stable LSD radix pass of 8 bits at `shift` over (key, value) pairs; the
-// item count is min(*n_dev, n_max) read on the device (n_dev may be null: n_max);
-// vals_in null: the values are the items' indices.  ranges non-null: the last pass
-// of the tile sort (the keys have no bits above this digit): keys_out is not written,
-// and each key k's [start, end) in the output is folded into ranges[k] by atomic
-// min / max (ranges initialised to (0xffffffff, 0), see launch_frame_begin; tiles
-// without items keep it until launch_ranges_finish).
+// words of scratch of every radix pass over at most n_max items
 size_t radix_tmp_words(uint32_t n_max);
-hipError_t launch_radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* keys_out,
-                             uint32_t* vals_out, const uint32_t* n_dev, uint32_t n_max, int shift,
-                             uint32_t* tmp, hipStream_t s, uint2* ranges = nullptr);
+// the depth order of n records: stable LSD passes over keys[0] (the other arrays are
+// scratch, and keys[0] with them) -> order[0]
+hipError_t launch_depth_sort(uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n, uint32_t* tmp,
+                             hipStream_t s);
+// passes of 8 bits that the tile ids take
+int tile_sort_passes(uint32_t n_tiles);
+// stable sort of the pairs (keys[0]: launch_duplicate's tile ids) by tile: the sorted
+// emission indices -> vals[passes & 1]; the item count is min(*total, cap), read on the
+// device.  The last pass writes no keys: it folds each tile's [start, end) into ranges[tile] by
+// atomic min / max (initialised to (0xffffffff, 0) by launch_frame_begin; tiles without
+// pairs keep that until launch_tile_order / launch_ranges_finish).
+hipError_t launch_tile_sort(uint32_t* const (&keys)[2], uint32_t* const (&vals)[2], uint32_t n_tiles,
+                            const uint32_t* total, uint32_t cap, uint2* ranges, uint32_t* tmp, hipStream_t s);
 
 // write the tile id of every (tile, Gaussian) pair, Gaussians in depth order, at
-// its emission index (keys[e]), and emit_vg[e] = view*n + Gaussian index; the
-// pairs' sort values are their emission indices (the tile sort's first pass
-// takes them as the items' indices)
+// its emission index (keys[e]: 16-bit words up to 65,536 tiles, else 32-bit), and
+// emit_vg[e] = view*n + Gaussian index; the pairs' sort values are their emission indices
+// (the tile sort's first pass takes them as the items' indices)
 hipError_t launch_duplicate(const uint32_t* order, const uint32_t* offsets, const uint32_t* tt_s,
-                            const uint2* rect_s, const CamDev* cams, uint32_t n, uint32_t vn,
+                            const uint2* rect_s, const CamDev* cams, uint32_t n, uint32_t vn, uint32_t n_tiles,
                             const uint32_t* total, uint32_t cap, uint32_t* keys, uint32_t* emit_vg,
                             uint32_t* overflow, hipStream_t s);
 // grad2d[vg] = sum of the per-pair rows pair_grad[10 e .. 10 e + 8] with pair_stamp[e] == *stamp over the Gaussian's

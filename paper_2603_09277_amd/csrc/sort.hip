@@ -9,6 +9,7 @@
 // exactly the LSD radix sort of the full key: duplication emits pairs in
 // depth-sorted Gaussian order and the tile passes are stable.
 #include <cstring>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -191,8 +192,10 @@ __global__ __launch_bounds__(kThreads) void scan_down_kernel(const uint32_t* val
 // ---------------------------------------------------------------------------
 // Stable LSD radix pass, 8-bit digits, 256 threads x ITEMS items per block
 // (32 for large inputs, 8 below 2^21 items so that small sorts still fill the chip;
-// 8,192 items a block scatter runs of 32 items a digit on average, 128 bytes of keys:
-// on the 8-view workload the two tile passes take about 1.4 ms, 1.7 ms at 16 items):
+// 8,192 items a block scatter runs of 32 items a digit on average, 128 bytes of values:
+// with 32-bit keys the 8-view workload's tile passes took about 1.4 ms, 1.7 ms at 16 items).
+// Keys are as wide as the digits still to sort: 16 bits in the tile sort up to 65,536
+// tiles and in the upper half of the depth sort, and the last pass writes none.
 //   upsweep   per-block digit histograms, block-major  hist[b * 256 + d] (one
 //             coalesced 1 KB store a block, and one 1 KB load in the downsweep)
 //   spine     one block per 4 digits: exclusive scan of their columns over the
@@ -231,8 +234,8 @@ __device__ __forceinline__ void wave_lds_order()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int ITEMS>
-__global__ __launch_bounds__(kThreads) void radix_upsweep_kernel(const uint32_t* keys, const uint32_t* n_dev,
+template <int ITEMS, typename Key>
+__global__ __launch_bounds__(kThreads) void radix_upsweep_kernel(const Key* keys, const uint32_t* n_dev,
                                                                  uint32_t n_max, int shift, uint32_t* hist)
 {
     constexpr int kRadixTile = kThreads * ITEMS;
@@ -267,7 +270,7 @@ __global__ __launch_bounds__(kThreads) void radix_upsweep_kernel(const uint32_t*
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
             const bool ok = (uint32_t)k * kThreads + threadIdx.x < cnt;
-            const uint32_t d = ok ? (kv[k] >> shift) & 0xffu : kBins;
+            const uint32_t d = ok ? (kv[k] >> shift) & 0xffu : (uint32_t)kBins;
             // the previous lane's digit by a DPP wave shift (lane 0 takes a value no digit has)
             const uint32_t prv = (uint32_t)__builtin_amdgcn_update_dpp((int)0xffffffffu, (int)d, 0x138, 0xf, 0xf, false);
             const bool lead = ok && prv != d;
@@ -376,8 +379,9 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nb)
 // one of them), the end the largest: atomicMin / atomicMax on bounds initialised to
 // (0xffffffff, 0).  Keys of the last pass have no bits above its digit, so equal keys
 // are contiguous inside a group.
+template <typename Key>
 __device__ __forceinline__ void tile_bounds(uint32_t k, uint32_t li, uint32_t o, uint32_t cnt, int shift,
-                                            const uint32_t* s_keys, uint32_t* ranges)
+                                            const Key* s_keys, uint32_t* ranges)
 {
     const uint32_t d = k >> shift;
     const uint32_t kp = li > 0u ? s_keys[li - 1u] : 0u;
@@ -388,22 +392,44 @@ __device__ __forceinline__ void tile_bounds(uint32_t k, uint32_t li, uint32_t o,
     if (!in_n || kn != k) atomicMax(&ranges[2u * k + 1u], o + 1u);
 }
 
+// What a pass reads and writes.  Key: the keys read; Out: the keys written, which need
+// only the digits that later passes sort by, key >> out_shift (NoKey: the last pass writes
+// none); IMPLICIT: the values are the items' indices; RANGES: the last pass of the tile
+// sort (tile_bounds).
+struct NoKey {};
+template <typename K, typename O, bool I, bool R>
+struct PassKind {
+    using Key = K;
+    using Out = O;
+    static constexpr bool kImplicit = I, kRanges = R;
+};
+
 // SELF: few blocks (nb <= kSelfSpineBlocks); every block sums the raw per-block
-// counts itself and no spine kernel runs.  RANGES: the last pass of the tile sort
-// (tile_bounds; keys_out is not written).
-template <int ITEMS, bool SELF, bool RANGES>
-__global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(const uint32_t* keys_in, const uint32_t* vals_in,
-                                                                   uint32_t* keys_out, uint32_t* vals_out,
-                                                                   const uint32_t* n_dev, uint32_t n_max, int shift,
-                                                                   const uint32_t* hist, uint32_t nb,
-                                                                   const uint32_t* digit_total, uint32_t* ranges)
+// counts itself and no spine kernel runs.  An item's key and rank share a register where
+// both are 16 bits, and LDS holds 16-bit keys and, for implicit values, 16-bit local
+// indices: three (implicit: four) workgroups of 8,192 items a CU instead of two, whose
+// loads, ranking and scatter overlap.  The 8-view workload's two tile passes take 0.59 ms
+// (32-bit keys and 180 registers a lane: 0.79), with their histograms 0.75 (1.06).
+template <int ITEMS, bool SELF, typename Kind>
+__global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(
+    const typename Kind::Key* keys_in, const uint32_t* vals_in, typename Kind::Out* keys_out, uint32_t* vals_out,
+    const uint32_t* n_dev, uint32_t n_max, int shift, int out_shift, const uint32_t* hist, uint32_t nb,
+    const uint32_t* digit_total, uint32_t* ranges)
 {
+    using Key = typename Kind::Key;
+    constexpr bool kWrites = !std::is_same<typename Kind::Out, NoKey>::value;
+    constexpr bool kImplicit = Kind::kImplicit, kNarrow = sizeof(Key) == 2;
+    using Val = typename std::conditional<kImplicit, uint16_t, uint32_t>::type;
+    using Count = typename std::conditional<(ITEMS > 8), uint16_t, uint32_t>::type;   // a wavefront's items: at most 2,048
     constexpr int kRadixItems = ITEMS;
     constexpr int kRadixTile = kThreads * ITEMS;
     constexpr int kPerWave = 64 * ITEMS;
-    __shared__ uint32_t s_keys[kRadixTile];
-    __shared__ uint32_t s_vals[kRadixTile];
-    __shared__ uint32_t s_wh[kWaves][kBins];  // per-wavefront digit counts, then (digit, wavefront) local starts
+    static_assert(kRadixTile <= 65536, "ranks and local indices are 16 bits");
+    static_assert(!SELF || (sizeof(Count) == 4 && sizeof(Key) * kRadixTile >= 4u * kWaves * kBins),
+                  "the spine-free pass sums in s_wh and s_keys");
+    __shared__ __align__(16) Key s_keys[kRadixTile];
+    __shared__ Val s_vals[kRadixTile];
+    __shared__ Count s_wh[kWaves][kBins];     // per-wavefront digit counts, then (digit, wavefront) local starts
     __shared__ uint32_t s_gofs[kBins];        // global start of digit d for this block
 
     const uint32_t n = item_count(n_dev, n_max);
@@ -415,12 +441,39 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(const uint32_
     const uint32_t tid = threadIdx.x, lane = lane_id(), wid = tid >> 6;
     const uint32_t cnt = (uint32_t)((n - base) < (size_t)kRadixTile ? (n - base) : (size_t)kRadixTile);
 
+    // wavefront wid owns items [wid * kPerWave, (wid + 1) * kPerWave): round r, lane l -> + r * 64 + l
+    // every load issued before any is used: a clamped index instead of a branch (items
+    // past the end are never ranked into place or written).  x[r]: the key, and in its upper
+    // half, where it is 16 bits, the rank; rk: the ranks of wider keys, two a word.
+    uint32_t x[kRadixItems], rk[kNarrow ? 1 : kRadixItems / 2], v_[kImplicit ? 1 : kRadixItems];
+    const bool whole = cnt == (uint32_t)kRadixTile;
+    if (whole) {                              // one address, the rest immediate offsets
+        const Key* kp = keys_in + base + wid * kPerWave + lane;
+#pragma unroll
+        for (int r = 0; r < kRadixItems; ++r) x[r] = kp[r * 64];
+        if constexpr (!kImplicit) {
+            const uint32_t* vp = vals_in + base + wid * kPerWave + lane;
+#pragma unroll
+            for (int r = 0; r < kRadixItems; ++r) v_[r] = vp[r * 64];
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < kRadixItems; ++r) {
+            const uint32_t li = wid * kPerWave + (uint32_t)r * 64u + lane;
+            const uint32_t at = li < cnt ? li : cnt - 1u;
+            x[r] = (keys_in + base)[at];
+            if constexpr (!kImplicit) v_[r] = (vals_in + base)[at];
+            if (ITEMS > 8 && r % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
     // global offsets: exclusive prefix of the digit totals + this block's row offset
     uint32_t tot;
-    if (SELF) {
+    if constexpr (SELF) {
         // every digit's count in all blocks and in the blocks before this one: wavefront
         // w sums rows w, w + 4, ... (lane l: digits 4 l .. 4 l + 3, one 16-byte load a row,
         // 8 rows in flight), then the 4 partial sums of digit tid are added
+        uint32_t* s_bef = reinterpret_cast<uint32_t*>(s_keys);
         uint4 all = make_uint4(0u, 0u, 0u, 0u), bef = all;
         for (uint32_t b0 = wid; b0 < nb; b0 += 8u * kWaves) {
             uint4 v[8];
@@ -438,14 +491,14 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(const uint32_
         }
         s_wh[wid][4u * lane + 0u] = all.x; s_wh[wid][4u * lane + 1u] = all.y;
         s_wh[wid][4u * lane + 2u] = all.z; s_wh[wid][4u * lane + 3u] = all.w;
-        s_keys[wid * kBins + 4u * lane + 0u] = bef.x; s_keys[wid * kBins + 4u * lane + 1u] = bef.y;
-        s_keys[wid * kBins + 4u * lane + 2u] = bef.z; s_keys[wid * kBins + 4u * lane + 3u] = bef.w;
+        s_bef[wid * kBins + 4u * lane + 0u] = bef.x; s_bef[wid * kBins + 4u * lane + 1u] = bef.y;
+        s_bef[wid * kBins + 4u * lane + 2u] = bef.z; s_bef[wid * kBins + 4u * lane + 3u] = bef.w;
         __syncthreads();
         uint32_t a = 0u, before = 0u;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
             a += s_wh[w][tid];
-            before += s_keys[w * kBins + tid];
+            before += s_bef[w * kBins + tid];
         }
         __syncthreads();                      // s_wh and s_keys are reused below
         s_gofs[tid] = block_excl_scan(a, &tot) + before;
@@ -457,30 +510,11 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(const uint32_
     for (int w = 0; w < kWaves; ++w) s_wh[w][tid] = 0u;
     __syncthreads();
 
-    // wavefront wid owns items [wid * kPerWave, (wid + 1) * kPerWave): round r, lane l -> + r * 64 + l
-    // every load issued before any is used: a clamped index instead of a branch (items
-    // past the end are never ranked into place or written)
-    uint32_t k_[kRadixItems], v_[kRadixItems], rk[kRadixItems];
-#pragma unroll
-    for (int r = 0; r < kRadixItems; ++r) {
-        const uint32_t li = wid * kPerWave + (uint32_t)r * 64u + lane;
-        k_[r] = keys_in[base + (li < cnt ? li : cnt - 1u)];
-    }
-    if (vals_in) {
-#pragma unroll
-        for (int r = 0; r < kRadixItems; ++r) {
-            const uint32_t li = wid * kPerWave + (uint32_t)r * 64u + lane;
-            v_[r] = vals_in[base + (li < cnt ? li : cnt - 1u)];
-        }
-    } else {                                  // null: the item's index
-#pragma unroll
-        for (int r = 0; r < kRadixItems; ++r) v_[r] = (uint32_t)(base + wid * kPerWave + (uint32_t)r * 64u + lane);
-    }
 #pragma unroll
     for (int r = 0; r < kRadixItems; ++r) {
         const uint32_t li = wid * kPerWave + (uint32_t)r * 64u + lane;
         const bool ok = li < cnt;
-        const uint32_t d = (k_[r] >> shift) & 0xffu;
+        const uint32_t d = (x[r] >> shift) & 0xffu;
         // peers: lanes of this wavefront holding the same digit.  Per digit bit b, m = 0 or
         // ~0 (the bit, sign-extended), and the lanes that agree with this one on it are
         // ~(ballot ^ m): one three-input bit operation per 32-lane half.  `below`: peers in
@@ -497,9 +531,18 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(const uint32_
         const uint64_t peers = ((uint64_t)phi << 32) | plo;
         const uint32_t below = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
         const uint32_t before = s_wh[wid][d];                // this digit's items in earlier rounds
-        rk[r] = before + below;
+        // (the empty statements have the rank formed here: left to itself the compiler
+        // keeps its terms and the digit's address in registers, four a round, until the
+        // reorder below)
+        if constexpr (kNarrow) {
+            x[r] |= (before + below) << 16;
+        } else {
+            rk[r / 2] = (r & 1) ? rk[r / 2] | (before + below) << 16 : before + below;
+            asm volatile("" : "+v"(rk[r / 2]));
+        }
+        asm volatile("" : "+v"(x[r]));
         wave_lds_order();
-        if (ok && below == 0u) s_wh[wid][d] = before + (uint32_t)__popcll(peers);
+        if (ok && below == 0u) s_wh[wid][d] = (Count)(before + (uint32_t)__popcll(peers));
         wave_lds_order();
     }
     __syncthreads();
@@ -516,7 +559,7 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(const uint32_
         s_gofs[tid] -= run;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
-            s_wh[w][tid] = run;
+            s_wh[w][tid] = (Count)run;
             run += cw[w];
         }
     }
@@ -524,45 +567,40 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(const uint32_
     // reorder through LDS, then a coalesced scatter of the locally sorted block.  A full
     // block (all but the last) takes the unguarded form, so that the compiler can keep
     // many items' LDS reads in flight instead of waiting on each item in turn.
-    if (cnt == (uint32_t)kRadixTile) {
+    auto place = [&](int r) {
+        const uint32_t rank = kNarrow ? x[r] >> 16 : (r & 1) ? rk[kNarrow ? 0 : r / 2] >> 16 : rk[kNarrow ? 0 : r / 2] & 0xffffu;
+        const uint32_t pos = s_wh[wid][(x[r] >> shift) & 0xffu] + rank;
+        s_keys[pos] = (Key)x[r];
+        if constexpr (kImplicit) s_vals[pos] = (Val)(wid * kPerWave + (uint32_t)r * 64u + lane);
+        else s_vals[pos] = v_[r];
+    };
+    auto scatter = [&](uint32_t li) {
+        const uint32_t k = s_keys[li];
+        const uint32_t o = s_gofs[(k >> shift) & 0xffu] + li;
+        if constexpr (kWrites) keys_out[o] = (typename Kind::Out)(k >> out_shift);
+        vals_out[o] = kImplicit ? (uint32_t)base + s_vals[li] : (uint32_t)s_vals[li];
+        if constexpr (Kind::kRanges) tile_bounds(k, li, o, cnt, shift, s_keys, ranges);
+    };
+    // (8 items in flight at a time: the addresses of all 32 alone are 64 registers)
+    constexpr int kFly = 8;
+    if (whole) {
 #pragma unroll
         for (int r = 0; r < kRadixItems; ++r) {
-            const uint32_t pos = s_wh[wid][(k_[r] >> shift) & 0xffu] + rk[r];
-            s_keys[pos] = k_[r];
-            s_vals[pos] = v_[r];
+            place(r);
+            if (r % kFly == kFly - 1) __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();
+#pragma unroll 1
+        for (int r0 = 0; r0 < kRadixItems; r0 += kFly) {
 #pragma unroll
-        for (int r = 0; r < kRadixItems; ++r) {
-            const uint32_t li = (uint32_t)r * kThreads + tid;
-            const uint32_t k = s_keys[li];
-            const uint32_t o = s_gofs[(k >> shift) & 0xffu] + li;
-            if (!RANGES) keys_out[o] = k;
-            vals_out[o] = s_vals[li];
-            if (RANGES) tile_bounds(k, li, o, cnt, shift, s_keys, ranges);
+            for (int r = 0; r < kFly; ++r) scatter((uint32_t)(r0 + r) * kThreads + tid);
         }
     } else {
 #pragma unroll
-        for (int r = 0; r < kRadixItems; ++r) {
-            const uint32_t li = wid * kPerWave + (uint32_t)r * 64u + lane;
-            if (li < cnt) {
-                const uint32_t pos = s_wh[wid][(k_[r] >> shift) & 0xffu] + rk[r];
-                s_keys[pos] = k_[r];
-                s_vals[pos] = v_[r];
-            }
-        }
+        for (int r = 0; r < kRadixItems; ++r)
+            if (wid * kPerWave + (uint32_t)r * 64u + lane < cnt) place(r);
         __syncthreads();
-#pragma unroll
-        for (int r = 0; r < kRadixItems; ++r) {
-            const uint32_t li = (uint32_t)r * kThreads + tid;
-            if (li < cnt) {
-                const uint32_t k = s_keys[li];
-                const uint32_t o = s_gofs[(k >> shift) & 0xffu] + li;
-                if (!RANGES) keys_out[o] = k;
-                vals_out[o] = s_vals[li];
-                if (RANGES) tile_bounds(k, li, o, cnt, shift, s_keys, ranges);
-            }
-        }
+        for (uint32_t li = tid; li < cnt; li += kThreads) scatter(li);
     }
 }
 
@@ -585,10 +623,11 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(const uint32_
 // Gaussian with many tiles is spread over all lanes.
 // ---------------------------------------------------------------------------
 
+template <typename Key>
 __global__ __launch_bounds__(kThreads) void duplicate_kernel(const uint32_t* order, const uint32_t* offsets,
                                                              const uint32_t* tt_s, const uint2* rect_s,
                                                              const CamDev* cams, uint32_t n, uint32_t vn,
-                                                             const uint32_t* total, uint32_t cap, uint32_t* keys,
+                                                             const uint32_t* total, uint32_t cap, Key* keys,
                                                              uint32_t* emit_vg, uint32_t* overflow)
 {
     __shared__ uint32_t s_loc[kThreads / 64][64];
@@ -638,7 +677,7 @@ __global__ __launch_bounds__(kThreads) void duplicate_kernel(const uint32_t* ord
         const uint32_t dy = k / rw, dx = k - dy * rw;
         const uint32_t p = off0 + q;
         if (q0 + lane < count && p < cap) {
-            keys[p] = rtb + (ry0 + dy) * rgx + rx0 + dx;
+            keys[p] = (Key)(rtb + (ry0 + dy) * rgx + rx0 + dx);
             emit_vg[p] = rvg;
         }
     }
@@ -1154,71 +1193,118 @@ size_t radix_tmp_words(uint32_t n_max)
     return (size_t)kBins * (nb > 0 ? nb : 1) + kBins;
 }
 
-template <int ITEMS, bool SELF>
-static void launch_downsweep(uint32_t nb, hipStream_t s, const uint32_t* keys_in, const uint32_t* vals_in,
-                             uint32_t* keys_out, uint32_t* vals_out, const uint32_t* n_dev, uint32_t n_max, int shift,
-                             const uint32_t* hist, const uint32_t* digit_total, uint2* ranges)
-{
-    if (ranges)
-        hipLaunchKernelGGL((radix_downsweep_kernel<ITEMS, SELF, true>), dim3(nb), dim3(kThreads), 0, s, keys_in,
-                           vals_in, keys_out, vals_out, n_dev, n_max, shift, hist, nb, digit_total,
-                           reinterpret_cast<uint32_t*>(ranges));
-    else
-        hipLaunchKernelGGL((radix_downsweep_kernel<ITEMS, SELF, false>), dim3(nb), dim3(kThreads), 0, s, keys_in,
-                           vals_in, keys_out, vals_out, n_dev, n_max, shift, hist, nb, digit_total, nullptr);
-}
+namespace {
 
-hipError_t launch_radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* keys_out, uint32_t* vals_out,
-                             const uint32_t* n_dev, uint32_t n_max, int shift, uint32_t* tmp, hipStream_t s,
-                             uint2* ranges)
+template <typename Kind>
+hipError_t radix_pass(const void* keys_in, const uint32_t* vals_in, void* keys_out, uint32_t* vals_out,
+                      const uint32_t* n_dev, uint32_t n_max, int shift, int out_shift, uint32_t* tmp, uint2* ranges,
+                      hipStream_t s)
 {
+    using Key = typename Kind::Key;
+    using Out = typename Kind::Out;
     const uint32_t items = radix_items(n_max), tile = kThreads * items;
-    uint32_t nb = (n_max + tile - 1) / tile;
+    const uint32_t nb = (n_max + tile - 1) / tile;
     if (nb == 0) return hipSuccess;
+    const Key* in = reinterpret_cast<const Key*>(keys_in);
+    Out* out = reinterpret_cast<Out*>(keys_out);
     uint32_t* hist = tmp;
     uint32_t* digit_total = tmp + (size_t)kBins * nb;
-    if (items == kRadixLargeItems)
-        hipLaunchKernelGGL(radix_upsweep_kernel<kRadixLargeItems>, dim3(nb), dim3(kThreads), 0, s, keys_in, n_dev,
-                           n_max, shift, hist);
+    uint32_t* rg = reinterpret_cast<uint32_t*>(ranges);
+    constexpr int kS = kRadixSmallItems, kL = kRadixLargeItems;
+    const dim3 grid(nb), block(kThreads);
+    if (items == kL)
+        hipLaunchKernelGGL((radix_upsweep_kernel<kL, Key>), grid, block, 0, s, in, n_dev, n_max, shift, hist);
     else
-        hipLaunchKernelGGL(radix_upsweep_kernel<kRadixSmallItems>, dim3(nb), dim3(kThreads), 0, s, keys_in, n_dev,
-                           n_max, shift, hist);
+        hipLaunchKernelGGL((radix_upsweep_kernel<kS, Key>), grid, block, 0, s, in, n_dev, n_max, shift, hist);
+    static_assert(kRadixLargeFrom / (kThreads * kRadixLargeItems) > kSelfSpineBlocks, "large passes have a spine");
     if (nb <= kSelfSpineBlocks) {             // the downsweep blocks find their offsets themselves
-        if (items == kRadixLargeItems)
-            launch_downsweep<kRadixLargeItems, true>(nb, s, keys_in, vals_in, keys_out, vals_out, n_dev, n_max, shift,
-                                                     hist, digit_total, ranges);
-        else
-            launch_downsweep<kRadixSmallItems, true>(nb, s, keys_in, vals_in, keys_out, vals_out, n_dev, n_max, shift,
-                                                     hist, digit_total, ranges);
+        hipLaunchKernelGGL((radix_downsweep_kernel<kS, true, Kind>), grid, block, 0, s, in, vals_in, out, vals_out, n_dev,
+                           n_max, shift, out_shift, hist, nb, digit_total, rg);
         return hipGetLastError();
     }
     // counts a thread: enough that a long column takes few block scans, few enough
     // that a short one is spread over the workgroup
     if (nb > 8u * kThreads)
-        hipLaunchKernelGGL(radix_spine_kernel<16>, dim3(kBins / 4), dim3(kThreads), 0, s, hist, n_dev, n_max, tile,
-                           digit_total);
+        hipLaunchKernelGGL(radix_spine_kernel<16>, dim3(kBins / 4), block, 0, s, hist, n_dev, n_max, tile, digit_total);
     else if (nb > kThreads)
-        hipLaunchKernelGGL(radix_spine_kernel<8>, dim3(kBins / 4), dim3(kThreads), 0, s, hist, n_dev, n_max, tile,
-                           digit_total);
+        hipLaunchKernelGGL(radix_spine_kernel<8>, dim3(kBins / 4), block, 0, s, hist, n_dev, n_max, tile, digit_total);
     else
-        hipLaunchKernelGGL(radix_spine_kernel<1>, dim3(kBins / 4), dim3(kThreads), 0, s, hist, n_dev, n_max, tile,
-                           digit_total);
-    if (items == kRadixLargeItems)
-        launch_downsweep<kRadixLargeItems, false>(nb, s, keys_in, vals_in, keys_out, vals_out, n_dev, n_max, shift,
-                                                  hist, digit_total, ranges);
+        hipLaunchKernelGGL(radix_spine_kernel<1>, dim3(kBins / 4), block, 0, s, hist, n_dev, n_max, tile, digit_total);
+    if (items == kL)
+        hipLaunchKernelGGL((radix_downsweep_kernel<kL, false, Kind>), grid, block, 0, s, in, vals_in, out, vals_out, n_dev,
+                           n_max, shift, out_shift, hist, nb, digit_total, rg);
     else
-        launch_downsweep<kRadixSmallItems, false>(nb, s, keys_in, vals_in, keys_out, vals_out, n_dev, n_max, shift,
-                                                  hist, digit_total, ranges);
+        hipLaunchKernelGGL((radix_downsweep_kernel<kS, false, Kind>), grid, block, 0, s, in, vals_in, out, vals_out, n_dev,
+                           n_max, shift, out_shift, hist, nb, digit_total, rg);
     return hipGetLastError();
 }
 
+}  // namespace
+
+hipError_t launch_depth_sort(uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n, uint32_t* tmp,
+                             hipStream_t s)
+{
+    // the keys a pass writes hold the digits still to sort: 32, then 16 bits, then none
+    hipError_t e = radix_pass<PassKind<uint32_t, uint32_t, true, false>>(keys[0], nullptr, keys[1], order[1], nullptr, n, 0,
+                                                                         0, tmp, nullptr, s);
+    if (e == hipSuccess)
+        e = radix_pass<PassKind<uint32_t, uint16_t, false, false>>(keys[1], order[1], keys[0], order[0], nullptr, n, 8, 16,
+                                                                   tmp, nullptr, s);
+    if (e == hipSuccess)
+        e = radix_pass<PassKind<uint16_t, uint16_t, false, false>>(keys[0], order[0], keys[1], order[1], nullptr, n, 0, 0,
+                                                                   tmp, nullptr, s);
+    if (e == hipSuccess)
+        e = radix_pass<PassKind<uint16_t, NoKey, false, false>>(keys[1], order[1], nullptr, order[0], nullptr, n, 8, 0, tmp,
+                                                                nullptr, s);
+    return e;
+}
+
+int tile_sort_passes(uint32_t n_tiles)
+{
+    int bits = 1;
+    while (bits < 24 && (1u << bits) < n_tiles) ++bits;
+    return (bits + 7) / 8;
+}
+
+hipError_t launch_tile_sort(uint32_t* const (&keys)[2], uint32_t* const (&vals)[2], uint32_t n_tiles,
+                            const uint32_t* total, uint32_t cap, uint2* ranges, uint32_t* tmp, hipStream_t s)
+{
+    const int passes = tile_sort_passes(n_tiles);
+    if (passes == 1)
+        return radix_pass<PassKind<uint16_t, NoKey, true, true>>(keys[0], nullptr, nullptr, vals[1], total, cap, 0, 0, tmp,
+                                                                 ranges, s);
+    if (passes == 2) {
+        hipError_t e = radix_pass<PassKind<uint16_t, uint16_t, true, false>>(keys[0], nullptr, keys[1], vals[1], total, cap,
+                                                                             0, 0, tmp, nullptr, s);
+        if (e == hipSuccess)
+            e = radix_pass<PassKind<uint16_t, NoKey, false, true>>(keys[1], vals[1], nullptr, vals[0], total, cap, 8, 0, tmp,
+                                                                   ranges, s);
+        return e;
+    }
+    hipError_t e = radix_pass<PassKind<uint32_t, uint32_t, true, false>>(keys[0], nullptr, keys[1], vals[1], total, cap, 0, 0,
+                                                                         tmp, nullptr, s);
+    if (e == hipSuccess)
+        e = radix_pass<PassKind<uint32_t, uint32_t, false, false>>(keys[1], vals[1], keys[0], vals[0], total, cap, 8, 0, tmp,
+                                                                   nullptr, s);
+    if (e == hipSuccess)
+        e = radix_pass<PassKind<uint32_t, NoKey, false, true>>(keys[0], vals[0], nullptr, vals[1], total, cap, 16, 0, tmp,
+                                                               ranges, s);
+    return e;
+}
+
 hipError_t launch_duplicate(const uint32_t* order, const uint32_t* offsets, const uint32_t* tt_s,
-                            const uint2* rect_s, const CamDev* cams, uint32_t n, uint32_t vn, const uint32_t* total,
-                            uint32_t cap, uint32_t* keys, uint32_t* emit_vg, uint32_t* overflow, hipStream_t s)
+                            const uint2* rect_s, const CamDev* cams, uint32_t n, uint32_t vn, uint32_t n_tiles,
+                            const uint32_t* total, uint32_t cap, uint32_t* keys, uint32_t* emit_vg, uint32_t* overflow,
+                            hipStream_t s)
 {
     if (vn == 0) return hipSuccess;
-    hipLaunchKernelGGL(duplicate_kernel, dim3((vn + kThreads - 1) / kThreads), dim3(kThreads), 0, s, order, offsets,
-                       tt_s, rect_s, cams, n, vn, total, cap, keys, emit_vg, overflow);
+    const dim3 grid((vn + kThreads - 1) / kThreads), block(kThreads);
+    if (tile_sort_passes(n_tiles) <= 2)
+        hipLaunchKernelGGL(duplicate_kernel<uint16_t>, grid, block, 0, s, order, offsets, tt_s, rect_s, cams, n, vn, total,
+                           cap, reinterpret_cast<uint16_t*>(keys), emit_vg, overflow);
+    else
+        hipLaunchKernelGGL(duplicate_kernel<uint32_t>, grid, block, 0, s, order, offsets, tt_s, rect_s, cams, n, vn, total,
+                           cap, keys, emit_vg, overflow);
     return hipGetLastError();
 }
 

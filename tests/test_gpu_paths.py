@@ -190,3 +190,37 @@ def test_lists_of_few_records(n, depths):
         order = np.lexsort((vals[a:b], depth[vals[a:b]]))
         assert np.array_equal(order, np.arange(b - a)) and len(set(vals[a:b])) == b - a
     r.close()
+
+
+# Tile ids of 8 bits (one pass), 16 bits (two) and more (three); pair counts of small and of
+# large passes (2^21 pairs), records past one workgroup.  Every list is in (depth, index)
+# order and each view's outputs are those of the view alone, whose ids may be narrower.
+@pytest.mark.parametrize("sizes", [[(128, 128)], [(128, 128), (8, 8)], [(2048, 2048)], [(8, 8), (2048, 2048)],
+                                   [(2048, 2048), (120, 136), (1024, 8)]])
+@pytest.mark.parametrize("n,scale", [(700, 1.0), (9000, 1.0), (9000, 6.0)])
+def test_tile_sort_key_widths(sizes, n, scale):
+    scene, t = _small_scene(n, 0)
+    t["scales"] = t["scales"] * scale
+    cams = scenes.orbit_cameras(np.random.default_rng(8), sizes)
+    opts = gsr.RasterOptions(tile=(8, 8), sh_degree=0)
+    p = [t[k] for k in ATTRS]
+    r = gsr.Rasterizer(max_views=len(cams))
+    out = {k: v.clone() for k, v in r.forward(*p, cams, opts).items() if k in ("rgb", "t_final", "n_contrib")}
+    vals, ranges = r.inspect(gsr.BUF_PAIR_VALUES).astype(np.int64), r.inspect(gsr.BUF_RANGES).reshape(-1, 2).astype(np.int64)
+    tt, depth = r.inspect(gsr.BUF_TILES_TOUCHED), r.inspect(gsr.BUF_DEPTH)
+    ln = ranges[:, 1] - ranges[:, 0]
+    assert len(vals) == tt.sum() == ln.sum()
+    assert np.array_equal(np.bincount(vals, minlength=n * len(cams)), tt)
+    assert np.array_equal(ranges[ln > 0, 0], np.cumsum(ln)[ln > 0] - ln[ln > 0])
+    tile = np.repeat(np.arange(len(ln)), ln)
+    same = tile[1:] == tile[:-1]
+    d = depth[vals]
+    assert np.all(~same | (d[1:] > d[:-1]) | ((d[1:] == d[:-1]) & (vals[1:] > vals[:-1])))
+    at = 0
+    for cam in cams:
+        m = cam.width * cam.height
+        one = r.forward(*p, [cam], opts)
+        for k, v in out.items():
+            assert torch.equal(_bits(v[at:at + m]), _bits(one[k])), (k, cam.width)
+        at += m
+    r.close()

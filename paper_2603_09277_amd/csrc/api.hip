@@ -88,7 +88,7 @@ struct gsr_ctx {
 
     // grow-only device buffers
     // rect: per record (rectangle, tiles touched) as uint4
-    Dev cams, rec, dkey0, dkey1, ord0, ord1, rect, tt, tt_s, rect_s, radius, depth, offsets, grad2d, rec_stamp, scan_tmp, radix_tmp;
+    Dev cams, rec, dkey0, dkey1, ord0, ord1, rect, tt_s, rect_s, radius, depth, offsets, grad2d, rec_stamp, scan_tmp, radix_tmp;
     Dev pk0, pk1, pv0, pv1, emit_vg, pair_grad, pair_stamp, seg_carry, ranges, tile_order, queues, block_H, block_cnt, hchunk, counters, l1_tmp, reg_tmp, ssim_tmp, counts;
     size_t vn_cap = 0, pair_cap = 0, tile_cap = 0, block_cap = 0;
     uint64_t gen = 0;                      // bumped on every reallocation; graphs hold raw pointers
@@ -318,7 +318,7 @@ gsr_status ensure_vn(gsr_ctx* c, uint32_t vn)
     gsr_status s;
     if ((s = grow(c, c->rec, v * 48)) || (s = grow(c, c->dkey0, v * 4)) || (s = grow(c, c->dkey1, v * 4)) ||
         (s = grow(c, c->ord0, v * 4)) || (s = grow(c, c->ord1, v * 4)) || (s = grow(c, c->rect, v * 8)) ||
-        (s = grow(c, c->tt, v * 4)) || (s = grow(c, c->tt_s, v * 4)) || (s = grow(c, c->rect_s, v * 8)) ||
+        (s = grow(c, c->tt_s, v * 4)) || (s = grow(c, c->rect_s, v * 8)) ||
         (s = grow(c, c->radius, v * 4)) || (s = grow(c, c->depth, v * 4)) ||
         (s = grow(c, c->offsets, v * 4)) || (s = grow(c, c->grad2d, v * 4 * kG2)) || (s = grow(c, c->rec_stamp, v * 4, true)) ||
         (s = grow(c, c->scan_tmp, scan_tmp_words((uint32_t)v) * 4)))
@@ -386,8 +386,7 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
     pa.means = g->means; pa.scales = g->scales; pa.quats = g->quats; pa.opac = g->opacities; pa.sh = g->sh;
     pa.n = n; pa.n_views = (int32_t)V; pa.flags = o->flags; pa.tile_shift_x = L.tsx; pa.tile_shift_y = L.tsy;
     pa.cams = dc;
-    pa.rec = (float4*)c->rec.p; pa.depth_key = (uint32_t*)c->dkey0.p; pa.trect = (uint2*)c->rect.p;
-    pa.tiles_touched = (uint32_t*)c->tt.p; pa.radius = (int32_t*)c->radius.p; pa.depth = (float*)c->depth.p;
+    pa.rec = (float4*)c->rec.p; pa.trect = (uint2*)c->rect.p; pa.radius = (int32_t*)c->radius.p; pa.depth = (float*)c->depth.p;
     pa.count = nullptr; pa.count_total = nullptr; pa.store_from = 0;
     {
         StageTimer tm(c, st, GSR_STAGE_PROJECT, !c->capturing);
@@ -402,10 +401,10 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
     {
         StageTimer tm(c, st, GSR_STAGE_DEPTH_SORT, !c->capturing);
         if (small)                                          // with the scan
-            HIP_TRY(c, launch_small_bin(dk[0], (const uint2*)c->rect.p, vn, od[0], (uint32_t*)c->offsets.p,
+            HIP_TRY(c, launch_small_bin((const uint32_t*)c->depth.p, (const uint2*)c->rect.p, vn, od[0], (uint32_t*)c->offsets.p,
                                         (uint32_t*)c->tt_s.p, (uint2*)c->rect_s.p, counters, counters + 1, st));
         else
-            HIP_TRY(c, launch_depth_sort(dk, od, vn, (uint32_t*)c->radix_tmp.p, st));
+            HIP_TRY(c, launch_depth_sort((const uint32_t*)c->depth.p, dk, od, vn, (uint32_t*)c->radix_tmp.p, st));
     }
     if (!small) {
         StageTimer tm(c, st, GSR_STAGE_SCAN, !c->capturing);
@@ -680,7 +679,7 @@ gsr_status gsr_destroy(gsr_ctx* c)
     if (!c) return GSR_ERR_INVALID_ARG;
     (void)hipDeviceSynchronize();
     drop_graphs(c);
-    Dev* all[] = { &c->cams, &c->rec, &c->dkey0, &c->dkey1, &c->ord0, &c->ord1, &c->rect, &c->tt, &c->tt_s, &c->rect_s, &c->radius,
+    Dev* all[] = { &c->cams, &c->rec, &c->dkey0, &c->dkey1, &c->ord0, &c->ord1, &c->rect, &c->tt_s, &c->rect_s, &c->radius,
                    &c->depth, &c->offsets, &c->grad2d, &c->rec_stamp, &c->scan_tmp, &c->radix_tmp, &c->pk0, &c->pk1, &c->pv0,
                    &c->pv1, &c->emit_vg, &c->pair_grad, &c->pair_stamp, &c->seg_carry, &c->ranges, &c->tile_order, &c->queues, &c->block_H, &c->block_cnt, &c->hchunk, &c->counters, &c->reg_tmp, &c->ssim_tmp,
                    &c->l1_tmp, &c->counts };
@@ -1067,8 +1066,7 @@ static gsr_status count_pairs(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g
     pa.means = g->means; pa.scales = g->scales; pa.quats = g->quats; pa.opac = g->opacities; pa.sh = g->sh;
     pa.n = n; pa.n_views = n_views; pa.flags = o->flags; pa.tile_shift_x = L.tsx; pa.tile_shift_y = L.tsy;
     pa.cams = (const CamDev*)c->cams.p;
-    pa.rec = (float4*)c->rec.p; pa.depth_key = (uint32_t*)c->dkey0.p; pa.trect = (uint2*)c->rect.p;
-    pa.tiles_touched = (uint32_t*)c->tt.p; pa.radius = (int32_t*)c->radius.p; pa.depth = (float*)c->depth.p;
+    pa.rec = (float4*)c->rec.p; pa.trect = (uint2*)c->rect.p; pa.radius = (int32_t*)c->radius.p; pa.depth = (float*)c->depth.p;
     pa.count_total = (uint64_t*)c->counts.p;
     pa.count = pa.count_total + kMaxViews;
     pa.store_from = store_from;
@@ -1229,6 +1227,19 @@ gsr_status gsr_stage_times(gsr_ctx* c, double* total_ms, int64_t* launches, int3
     return GSR_OK;
 }
 
+// tiles of each record's rectangle, to the host
+static gsr_status read_tiles_touched(gsr_ctx* c, hipStream_t st, uint32_t* out)
+{
+    std::vector<uint32_t> r(2 * (size_t)c->vn);
+    if (c->vn) HIP_TRY(c, hipMemcpyAsync(r.data(), c->rect.p, (size_t)c->vn * 8, hipMemcpyDeviceToHost, st));
+    HIP_TRY(c, hipStreamSynchronize(st));
+    for (uint32_t i = 0; i < c->vn; ++i) {
+        const uint32_t x = r[2 * (size_t)i], y = r[2 * (size_t)i + 1];
+        out[i] = ((x >> 16) - (x & 0xffffu) + 1u) * ((y >> 16) - (y & 0xffffu) + 1u);
+    }
+    return GSR_OK;
+}
+
 gsr_status gsr_inspect(gsr_ctx* c, void* stream, gsr_buffer which, void* dst, int64_t capacity_bytes, int64_t* bytes)
 {
     if (!c || !bytes) return GSR_ERR_INVALID_ARG;
@@ -1251,7 +1262,13 @@ gsr_status gsr_inspect(gsr_ctx* c, void* stream, gsr_buffer which, void* dst, in
         case GSR_BUF_RECORDS: src = c->rec.p; sz = (size_t)c->vn * 48; break;
         case GSR_BUF_RADIUS: src = c->radius.p; sz = (size_t)c->vn * 4; break;
         case GSR_BUF_DEPTH: src = c->depth.p; sz = (size_t)c->vn * 4; break;
-        case GSR_BUF_TILES_TOUCHED: src = c->tt.p; sz = (size_t)c->vn * 4; break;
+        case GSR_BUF_TILES_TOUCHED: {  // from the tile rectangles
+            sz = (size_t)c->vn * 4;
+            *bytes = (int64_t)sz;
+            if (!dst) return GSR_OK;
+            if ((int64_t)sz > capacity_bytes) return fail(c, GSR_ERR_INVALID_ARG, "destination too small");
+            return read_tiles_touched(c, st, (uint32_t*)dst);
+        }
         case GSR_BUF_PAIR_VALUES: {    // the sorted emission indices, mapped to their records
             sz = (size_t)c->pairs * 4;
             *bytes = (int64_t)sz;
@@ -1290,9 +1307,10 @@ gsr_status gsr_inspect(gsr_ctx* c, void* stream, gsr_buffer which, void* dst, in
             if ((int64_t)sz > capacity_bytes) return fail(c, GSR_ERR_INVALID_ARG, "destination too small");
             std::vector<uint32_t> tt(c->vn), rs(c->vn);
             uint32_t cnt[5] = {0, 0, 0, 0, 0};
+            gsr_status s = read_tiles_touched(c, st, tt.data());
+            if (s) return s;
             if (sz) {
                 HIP_TRY(c, hipMemcpyAsync(dst, c->grad2d.p, sz, hipMemcpyDeviceToHost, st));
-                HIP_TRY(c, hipMemcpyAsync(tt.data(), c->tt.p, (size_t)c->vn * 4, hipMemcpyDeviceToHost, st));
                 HIP_TRY(c, hipMemcpyAsync(rs.data(), c->rec_stamp.p, (size_t)c->vn * 4, hipMemcpyDeviceToHost, st));
                 HIP_TRY(c, hipMemcpyAsync(cnt, c->counters.p, sizeof(cnt), hipMemcpyDeviceToHost, st));
             }

@@ -94,13 +94,12 @@ struct ProjectFwdArgs {
     int32_t tile_shift_x, tile_shift_y;   // log2 of the tile shape
     const CamDev* cams;
     float4* rec;                          // [V*n][3]
-    uint32_t* depth_key;                  // [V*n] float bits of camera z; culled = 0xffffffff
     uint2* trect;                         // [V*n] (x0 | x1 << 16, y0 | y1 << 16), inclusive tile bounds
                                           //   (empty: x1 < x0): one 8-byte gather for the depth-ordered
                                           //   scan, which takes the tile count from the bounds
-    uint32_t* tiles_touched;              // [V*n]
     int32_t* radius;                      // [V*n]
-    float* depth;                         // [V*n]
+    float* depth;                         // [V*n] camera z: the sort's keys, by their bits (positive wherever
+                                          //   the record has pairs; the others' place has no effect)
     // pair counting (count null: none): the sum of tiles touched of view v -> count_total[v], by
     // way of project_count_words(n, n_views) words at count; only views from store_from on are
     // stored, at the records of views 0, 1, ...
@@ -222,9 +221,9 @@ hipError_t launch_small_bin(const uint32_t* keys, const uint2* trect, uint32_t n
 
 // words of scratch of every radix pass over at most n_max items
 size_t radix_tmp_words(uint32_t n_max);
-// the depth order of n records: stable LSD passes over keys[0] (the other arrays are
-// scratch, and keys[0] with them) -> order[0]
-hipError_t launch_depth_sort(uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n, uint32_t* tmp,
+// the depth order of n records (depth: their keys): stable LSD passes -> order[0]; keys and
+// order[1] are scratch
+hipError_t launch_depth_sort(const uint32_t* depth, uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n, uint32_t* tmp,
                              hipStream_t s);
 // passes of 8 bits that the tile ids take
 int tile_sort_passes(uint32_t n_tiles);

@@ -323,13 +323,14 @@ __global__ __launch_bounds__(256) void project_fwd_kernel(ProjectFwdArgs a)
                 a.count[(size_t)v * 4u * gridDim.x + 4u * blockIdx.x + (threadIdx.x >> 6)] = sum;
             if (!store) continue;
         }
+        // 64 bytes a record, most of this kernel's traffic with several views: the sort's key
+        // is the depth itself and the tile count follows from the rectangle (stored apart, 72
+        // bytes: 8 views of 3M 0.52 -> 0.48 ms, four of 6M 0.58 -> 0.55)
         a.rec[3 * o + 0] = r0;
         a.rec[3 * o + 1] = r1;
         a.rec[3 * o + 2] = r2;
-        a.depth_key[o] = P.ok ? __float_as_uint(P.tz) : 0xffffffffu;
         a.depth[o] = P.tz;
         a.trect[o] = rc;
-        a.tiles_touched[o] = tt;
         a.radius[o] = P.ok ? rad : 0;
     }
     }

@@ -1241,11 +1241,11 @@ hipError_t radix_pass(const void* keys_in, const uint32_t* vals_in, void* keys_o
 
 }  // namespace
 
-hipError_t launch_depth_sort(uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n, uint32_t* tmp,
-                             hipStream_t s)
+hipError_t launch_depth_sort(const uint32_t* depth, uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n,
+                             uint32_t* tmp, hipStream_t s)
 {
     // the keys a pass writes hold the digits still to sort: 32, then 16 bits, then none
-    hipError_t e = radix_pass<PassKind<uint32_t, uint32_t, true, false>>(keys[0], nullptr, keys[1], order[1], nullptr, n, 0,
+    hipError_t e = radix_pass<PassKind<uint32_t, uint32_t, true, false>>(depth, nullptr, keys[1], order[1], nullptr, n, 0,
                                                                          0, tmp, nullptr, s);
     if (e == hipSuccess)
         e = radix_pass<PassKind<uint32_t, uint16_t, false, false>>(keys[1], order[1], keys[0], order[0], nullptr, n, 8, 16,

@@ -75,6 +75,7 @@ struct FrameKey {
 struct Layout {
     std::vector<CamDev> cams;
     uint32_t n_tiles = 0, n_blocks = 0, n_hchunks = 0, n_l1 = 0, max_blocks = 0;   // max_blocks: of one view
+    int max_gx = 0, max_gy = 0;            // largest tile grid
     int64_t n_pix = 0;
     int tsx = 0, tsy = 0, spt = 1;
 };
@@ -88,7 +89,7 @@ struct gsr_ctx {
 
     // grow-only device buffers
     // rect: per record (rectangle, tiles touched) as uint4
-    Dev cams, rec, dkey0, dkey1, ord0, ord1, rect, tt_s, rect_s, radius, depth, offsets, grad2d, rec_stamp, scan_tmp, radix_tmp;
+    Dev cams, rec, dkey0, dkey1, ord0, ord1, rect, rect_s, radius, depth, grad2d, rec_stamp, scan_tmp, radix_tmp;
     Dev pk0, pk1, pv0, pv1, emit_vg, pair_grad, pair_stamp, seg_carry, ranges, tile_order, queues, block_H, block_cnt, hchunk, counters, l1_tmp, reg_tmp, ssim_tmp, counts;
     size_t vn_cap = 0, pair_cap = 0, tile_cap = 0, block_cap = 0;
     uint64_t gen = 0;                      // bumped on every reallocation; graphs hold raw pointers
@@ -103,6 +104,7 @@ struct gsr_ctx {
     int64_t frame = 0;
     bool have_frame = false;
     bool have_records = false;             // the per-record buffers hold the latest projection
+    bool rect8 = false;                    // its tile rectangles are 32-bit words (carry_rects)
     Layout lay;
     uint32_t vn = 0, n = 0, pairs = 0;
     int sorted_buf = 0;                    // which pair buffer holds the sorted lists
@@ -295,6 +297,8 @@ Layout make_layout(const gsr_camera* cams, int32_t n_views, const gsr_opts* o)
         d.hred_base = hb;
         d.l1_base = lb;
         L.max_blocks = std::max(L.max_blocks, d.n_wblocks);
+        L.max_gx = std::max(L.max_gx, d.gx);
+        L.max_gy = std::max(L.max_gy, d.gy);
         hb += (d.n_wblocks + kRedChunk - 1) / kRedChunk;
         lb += (uint32_t)(((int64_t)k.width * k.height + kL1Pix - 1) / kL1Pix);
         tb += (uint32_t)(d.gx * d.gy);
@@ -318,9 +322,9 @@ gsr_status ensure_vn(gsr_ctx* c, uint32_t vn)
     gsr_status s;
     if ((s = grow(c, c->rec, v * 48)) || (s = grow(c, c->dkey0, v * 4)) || (s = grow(c, c->dkey1, v * 4)) ||
         (s = grow(c, c->ord0, v * 4)) || (s = grow(c, c->ord1, v * 4)) || (s = grow(c, c->rect, v * 8)) ||
-        (s = grow(c, c->tt_s, v * 4)) || (s = grow(c, c->rect_s, v * 8)) ||
+        (s = grow(c, c->rect_s, v * 8)) ||
         (s = grow(c, c->radius, v * 4)) || (s = grow(c, c->depth, v * 4)) ||
-        (s = grow(c, c->offsets, v * 4)) || (s = grow(c, c->grad2d, v * 4 * kG2)) || (s = grow(c, c->rec_stamp, v * 4, true)) ||
+        (s = grow(c, c->grad2d, v * 4 * kG2)) || (s = grow(c, c->rec_stamp, v * 4, true)) ||
         (s = grow(c, c->scan_tmp, scan_tmp_words((uint32_t)v) * 4)))
         return s;
     c->vn_cap = v;
@@ -386,6 +390,8 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
     pa.means = g->means; pa.scales = g->scales; pa.quats = g->quats; pa.opac = g->opacities; pa.sh = g->sh;
     pa.n = n; pa.n_views = (int32_t)V; pa.flags = o->flags; pa.tile_shift_x = L.tsx; pa.tile_shift_y = L.tsy;
     pa.cams = dc;
+    c->rect8 = carry_rects(vn, L.max_gx, L.max_gy);
+    pa.rect8 = c->rect8;
     pa.rec = (float4*)c->rec.p; pa.trect = (uint2*)c->rect.p; pa.radius = (int32_t*)c->radius.p; pa.depth = (float*)c->depth.p;
     pa.count = nullptr; pa.count_total = nullptr; pa.store_from = 0;
     {
@@ -397,20 +403,22 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
     // record's pairs in that order; total pair count
     uint32_t* dk[2] = { (uint32_t*)c->dkey0.p, (uint32_t*)c->dkey1.p };
     uint32_t* od[2] = { (uint32_t*)c->ord0.p, (uint32_t*)c->ord1.p };
+    // 32-bit rectangles take half of each array: the sort's scratch is the other half of c->rect
+    uint32_t* rs[2] = { (uint32_t*)c->rect_s.p, (uint32_t*)c->rect.p + vn };
     const bool small = vn > 0 && vn <= kSmallBin;
     {
         StageTimer tm(c, st, GSR_STAGE_DEPTH_SORT, !c->capturing);
         if (small)                                          // with the scan
-            HIP_TRY(c, launch_small_bin((const uint32_t*)c->depth.p, (const uint2*)c->rect.p, vn, od[0], (uint32_t*)c->offsets.p,
-                                        (uint32_t*)c->tt_s.p, (uint2*)c->rect_s.p, counters, counters + 1, st));
+            HIP_TRY(c, launch_small_bin((const uint32_t*)c->depth.p, (const uint2*)c->rect.p, vn, od[0],
+                                        (uint32_t*)c->scan_tmp.p, (uint2*)c->rect_s.p, counters, counters + 1, st));
         else
-            HIP_TRY(c, launch_depth_sort((const uint32_t*)c->depth.p, dk, od, vn, (uint32_t*)c->radix_tmp.p, st));
+            HIP_TRY(c, launch_depth_sort((const uint32_t*)c->depth.p, dk, od, vn, (uint32_t*)c->radix_tmp.p,
+                                         c->rect8 ? (const uint32_t*)c->rect.p : nullptr, rs, st));
     }
     if (!small) {
         StageTimer tm(c, st, GSR_STAGE_SCAN, !c->capturing);
-        HIP_TRY(c, launch_gather_scan((const uint2*)c->rect.p, od[0], vn,
-                                      (uint32_t*)c->offsets.p, (uint32_t*)c->tt_s.p, (uint2*)c->rect_s.p, counters,
-                                      counters + 1, (uint32_t*)c->scan_tmp.p, st));
+        HIP_TRY(c, launch_scan((const uint2*)c->rect.p, od[0], vn, (uint2*)c->rect_s.p, c->rect8, (uint32_t*)c->scan_tmp.p,
+                               counters, counters + 1, st));
     }
     uint32_t cap;
     const uint64_t most = (uint64_t)n * L.n_tiles;          // every record in every tile of its view
@@ -437,9 +445,8 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
     uint32_t* pv[2] = { (uint32_t*)c->pv0.p, (uint32_t*)c->pv1.p };
     {
         StageTimer tm(c, st, GSR_STAGE_DUPLICATE, !c->capturing);
-        HIP_TRY(c, launch_duplicate(od[0], (const uint32_t*)c->offsets.p, (const uint32_t*)c->tt_s.p,
-                                    (const uint2*)c->rect_s.p, dc, n, vn, L.n_tiles, counters, cap, pk[0],
-                                    (uint32_t*)c->emit_vg.p, counters + 1, st));
+        HIP_TRY(c, launch_duplicate(od[0], (const uint2*)c->rect_s.p, c->rect8, (const uint32_t*)c->scan_tmp.p, dc, n, vn,
+                                    L.n_tiles, counters, cap, pk[0], (uint32_t*)c->emit_vg.p, counters + 1, st));
     }
     // stable sort of the pairs by tile id; its last pass records the tile ranges
     {
@@ -679,8 +686,8 @@ gsr_status gsr_destroy(gsr_ctx* c)
     if (!c) return GSR_ERR_INVALID_ARG;
     (void)hipDeviceSynchronize();
     drop_graphs(c);
-    Dev* all[] = { &c->cams, &c->rec, &c->dkey0, &c->dkey1, &c->ord0, &c->ord1, &c->rect, &c->tt_s, &c->rect_s, &c->radius,
-                   &c->depth, &c->offsets, &c->grad2d, &c->rec_stamp, &c->scan_tmp, &c->radix_tmp, &c->pk0, &c->pk1, &c->pv0,
+    Dev* all[] = { &c->cams, &c->rec, &c->dkey0, &c->dkey1, &c->ord0, &c->ord1, &c->rect, &c->rect_s, &c->radius,
+                   &c->depth, &c->grad2d, &c->rec_stamp, &c->scan_tmp, &c->radix_tmp, &c->pk0, &c->pk1, &c->pv0,
                    &c->pv1, &c->emit_vg, &c->pair_grad, &c->pair_stamp, &c->seg_carry, &c->ranges, &c->tile_order, &c->queues, &c->block_H, &c->block_cnt, &c->hchunk, &c->counters, &c->reg_tmp, &c->ssim_tmp,
                    &c->l1_tmp, &c->counts };
     for (Dev* d : all) free_dev(*d);
@@ -1066,6 +1073,8 @@ static gsr_status count_pairs(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g
     pa.means = g->means; pa.scales = g->scales; pa.quats = g->quats; pa.opac = g->opacities; pa.sh = g->sh;
     pa.n = n; pa.n_views = n_views; pa.flags = o->flags; pa.tile_shift_x = L.tsx; pa.tile_shift_y = L.tsy;
     pa.cams = (const CamDev*)c->cams.p;
+    c->rect8 = false;
+    pa.rect8 = false;
     pa.rec = (float4*)c->rec.p; pa.trect = (uint2*)c->rect.p; pa.radius = (int32_t*)c->radius.p; pa.depth = (float*)c->depth.p;
     pa.count_total = (uint64_t*)c->counts.p;
     pa.count = pa.count_total + kMaxViews;
@@ -1230,12 +1239,17 @@ gsr_status gsr_stage_times(gsr_ctx* c, double* total_ms, int64_t* launches, int3
 // tiles of each record's rectangle, to the host
 static gsr_status read_tiles_touched(gsr_ctx* c, hipStream_t st, uint32_t* out)
 {
-    std::vector<uint32_t> r(2 * (size_t)c->vn);
-    if (c->vn) HIP_TRY(c, hipMemcpyAsync(r.data(), c->rect.p, (size_t)c->vn * 8, hipMemcpyDeviceToHost, st));
+    std::vector<uint32_t> r((c->rect8 ? 1 : 2) * (size_t)c->vn);
+    if (c->vn) HIP_TRY(c, hipMemcpyAsync(r.data(), c->rect.p, r.size() * 4, hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipStreamSynchronize(st));
     for (uint32_t i = 0; i < c->vn; ++i) {
-        const uint32_t x = r[2 * (size_t)i], y = r[2 * (size_t)i + 1];
-        out[i] = ((x >> 16) - (x & 0xffffu) + 1u) * ((y >> 16) - (y & 0xffffu) + 1u);
+        if (c->rect8) {
+            const uint32_t v = r[i];
+            out[i] = (((v >> 8) & 0xffu) - (v & 0xffu) + 1u) * ((v >> 24) - ((v >> 16) & 0xffu) + 1u);
+        } else {
+            const uint32_t x = r[2 * (size_t)i], y = r[2 * (size_t)i + 1];
+            out[i] = ((x >> 16) - (x & 0xffffu) + 1u) * ((y >> 16) - (y & 0xffffu) + 1u);
+        }
     }
     return GSR_OK;
 }

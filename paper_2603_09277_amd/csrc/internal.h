@@ -95,8 +95,9 @@ struct ProjectFwdArgs {
     const CamDev* cams;
     float4* rec;                          // [V*n][3]
     uint2* trect;                         // [V*n] (x0 | x1 << 16, y0 | y1 << 16), inclusive tile bounds
-                                          //   (empty: x1 < x0): one 8-byte gather for the depth-ordered
-                                          //   scan, which takes the tile count from the bounds
+                                          //   (empty: x1 < x0); rect8: x0, x1, y0, y1 of 8 bits in one
+                                          //   32-bit word [V*n] (carry_rects)
+    bool rect8;
     int32_t* radius;                      // [V*n]
     float* depth;                         // [V*n] camera z: the sort's keys, by their bits (positive wherever
                                           //   the record has pairs; the others' place has no effect)
@@ -204,27 +205,34 @@ hipError_t launch_project_fwd(const ProjectFwdArgs& a, int sh_degree, bool sh_bf
 inline size_t project_count_words(uint32_t n, int n_views) { return 4 * (size_t)((n + 255u) / 256u) * (size_t)n_views; }
 hipError_t launch_project_bwd(const ProjectBwdArgs& a, int sh_degree, bool sh_bf16, hipStream_t s);
 
-// exclusive scan of vals[order[i]] for i < n  ->  out[i]; total -> *total (uint32),
-// *overflow |= 1 if the total does not fit in 32 bits; vals_s[i] = vals[order[i]] and
-// rect_s[i] = rect[order[i]].  tmp holds scan_tmp_words(n) words; out and vals_s are
-// 16-byte aligned.
-size_t scan_tmp_words(uint32_t n);
-hipError_t launch_gather_scan(const uint2* trect, const uint32_t* order, uint32_t n, uint32_t* out,
-                              uint32_t* vals_s, uint2* rect_s, uint32_t* total, uint32_t* overflow, uint32_t* tmp,
-                              hipStream_t s);
+// The tile rectangles of large depth sorts travel with the sort as 32-bit words, from
+// `records` on, where the large passes begin, if every view has at most 256 x 256 tiles: sort
+// and scan of 24M records take 0.53 ms so (0.81 with the rectangles gathered at the end),
+// of 3.3M 114 us (136); the small passes are bound by latency, and 1M records gather in 15 us.
+constexpr uint32_t kCarryFrom = 1u << 21;
+inline bool carry_rects(uint32_t records, int gx, int gy) { return records >= kCarryFrom && gx <= 256 && gy <= 256; }
 
-// at most kSmallBin records: the depth order of all records (keys) and launch_gather_scan's
-// outputs for it, in one launch
+// first[b] = pairs of the records before workgroup b of launch_duplicate, in depth order;
+// their total -> *total (uint32), *overflow |= 1 if it does not fit in 32 bits.  carried:
+// rect_s holds the 32-bit rectangles in depth order; else rect_s[i] = trect[order[i]].  first
+// holds scan_tmp_words(n) words.
+size_t scan_tmp_words(uint32_t n);
+hipError_t launch_scan(const uint2* trect, const uint32_t* order, uint32_t n, uint2* rect_s, bool carried, uint32_t* first,
+                       uint32_t* total, uint32_t* overflow, hipStream_t s);
+
+// at most kSmallBin records: the depth order of all records (keys) and launch_scan's outputs
+// for it, in one launch
 constexpr uint32_t kSmallBin = 6144;
-hipError_t launch_small_bin(const uint32_t* keys, const uint2* trect, uint32_t n, uint32_t* order, uint32_t* out,
-                            uint32_t* vals_s, uint2* rect_s, uint32_t* total, uint32_t* overflow, hipStream_t s);
+hipError_t launch_small_bin(const uint32_t* keys, const uint2* trect, uint32_t n, uint32_t* order, uint32_t* first,
+                            uint2* rect_s, uint32_t* total, uint32_t* overflow, hipStream_t s);
 
 // words of scratch of every radix pass over at most n_max items
 size_t radix_tmp_words(uint32_t n_max);
 // the depth order of n records (depth: their keys): stable LSD passes -> order[0]; keys and
-// order[1] are scratch
-hipError_t launch_depth_sort(const uint32_t* depth, uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n, uint32_t* tmp,
-                             hipStream_t s);
+// order[1] are scratch.  rect non-null (carry_rects): rect_s[0][i] = rect[order[0][i]], rect_s[1]
+// scratch
+hipError_t launch_depth_sort(const uint32_t* depth, uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n,
+                             uint32_t* tmp, const uint32_t* rect, uint32_t* const (&rect_s)[2], hipStream_t s);
 // passes of 8 bits that the tile ids take
 int tile_sort_passes(uint32_t n_tiles);
 // stable sort of the pairs (keys[0]: launch_duplicate's tile ids) by tile: the sorted
@@ -239,10 +247,9 @@ hipError_t launch_tile_sort(uint32_t* const (&keys)[2], uint32_t* const (&vals)[
 // its emission index (keys[e]: 16-bit words up to 65,536 tiles, else 32-bit), and
 // emit_vg[e] = view*n + Gaussian index; the pairs' sort values are their emission indices
 // (the tile sort's first pass takes them as the items' indices)
-hipError_t launch_duplicate(const uint32_t* order, const uint32_t* offsets, const uint32_t* tt_s,
-                            const uint2* rect_s, const CamDev* cams, uint32_t n, uint32_t vn, uint32_t n_tiles,
-                            const uint32_t* total, uint32_t cap, uint32_t* keys, uint32_t* emit_vg,
-                            uint32_t* overflow, hipStream_t s);
+hipError_t launch_duplicate(const uint32_t* order, const uint2* rect_s, bool carried, const uint32_t* first,
+                            const CamDev* cams, uint32_t n, uint32_t vn, uint32_t n_tiles, const uint32_t* total, uint32_t cap,
+                            uint32_t* keys, uint32_t* emit_vg, uint32_t* overflow, hipStream_t s);
 // grad2d[vg] = sum of the per-pair rows pair_grad[10 e .. 10 e + 8] with pair_stamp[e] == *stamp over the Gaussian's
 // emission range, written, with rec_stamp[vg] = *stamp, for every (view, Gaussian) with at least one such
 // row; every other grad2d row is zero by definition and left untouched, with its old stamp;

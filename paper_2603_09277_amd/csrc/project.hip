@@ -330,7 +330,10 @@ __global__ __launch_bounds__(256) void project_fwd_kernel(ProjectFwdArgs a)
         a.rec[3 * o + 1] = r1;
         a.rec[3 * o + 2] = r2;
         a.depth[o] = P.tz;
-        a.trect[o] = rc;
+        if (a.rect8)
+            reinterpret_cast<uint32_t*>(a.trect)[o] = (rc.x & 0xffu) | ((rc.x >> 16) << 8) | (rc.y << 16) | ((rc.y >> 16) << 24);
+        else
+            a.trect[o] = rc;
         a.radius[o] = P.ok ? rad : 0;
     }
     }

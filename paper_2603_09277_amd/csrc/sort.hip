@@ -17,8 +17,6 @@ namespace gsr {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kItems = 8;
-constexpr int kTileItems = kThreads * kItems;     // 2048 items per block
 constexpr int kBins = 256;
 
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
@@ -56,45 +54,58 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* total)
 }
 
 // ---------------------------------------------------------------------------
-// Device-wide exclusive scan (reduce, spine, downsweep) of the tiles touched
-// taken in depth order.  The reduce step gathers each record's tile rectangle
-// with one 8-byte load into depth order (rect_s, and its tile count in vals_s),
-// so the downsweep and the duplication read them coalesced.  (With the count in
-// a 16-byte word the gathered array was 384 MB on the 8-view workload; at 8
-// bytes it is half that, within the chip's 256 MB last-level cache.)
+// First pair of every workgroup of the duplication (its records are kThreads x ITEMS in
+// depth order): tile counts summed a workgroup, then an exclusive scan of the sums.
+// Rectangles are 32-bit words in depth order where the depth sort carried them (large
+// sorts, carry_rects), else 64-bit words that the reduce step gathers: 8 bytes at 24M
+// random places take 0.48 ms, where carrying 4 bytes through the four passes (0.32 ->
+// 0.51 ms) and reading them in order takes 0.02.
 // ---------------------------------------------------------------------------
 
-// tiles in the inclusive tile rectangle (x0 | x1 << 16, y0 | y1 << 16); 0 when x1 < x0
-__device__ __forceinline__ uint32_t rect_tiles(uint2 r)
+// inclusive tile bounds: (x0 | x1 << 16, y0 | y1 << 16), or in one word x0, x1, y0, y1 of 8
+// bits (rect_pack8); empty: x1 = x0 - 1
+struct TileRect {
+    uint32_t x0, y0, w, h;
+};
+__device__ __forceinline__ TileRect unpack(uint2 r)
 {
-    const uint32_t w = (r.x >> 16) - (r.x & 0xffffu) + 1u, h = (r.y >> 16) - (r.y & 0xffffu) + 1u;
-    return w * h;
+    const uint32_t x0 = r.x & 0xffffu, y0 = r.y & 0xffffu;
+    return { x0, y0, (r.x >> 16) - x0 + 1u, (r.y >> 16) - y0 + 1u };
 }
-
-__global__ __launch_bounds__(kThreads) void scan_reduce_kernel(const uint2* trect, const uint32_t* order, uint32_t n,
-                                                               uint32_t* partial, uint32_t* vals_s, uint2* rect_s)
+__device__ __forceinline__ TileRect unpack(uint32_t r)
 {
-    size_t base = (size_t)blockIdx.x * kTileItems + threadIdx.x;
+    const uint32_t x0 = r & 0xffu, y0 = (r >> 16) & 0xffu;
+    return { x0, y0, ((r >> 8) & 0xffu) - x0 + 1u, (r >> 24) - y0 + 1u };
+}
+template <typename Rect> __device__ __forceinline__ Rect rect_none();
+template <> __device__ __forceinline__ uint2 rect_none<uint2>() { return make_uint2(1u, 1u); }
+template <> __device__ __forceinline__ uint32_t rect_none<uint32_t>() { return 0x00010001u; }
+
+// GATHER: rect_s[i] = rect[order[i]], else rect is in depth order already
+template <typename Rect, int ITEMS, bool GATHER>
+__global__ __launch_bounds__(kThreads) void scan_reduce_kernel(const Rect* rect, const uint32_t* order, uint32_t n,
+                                                               uint32_t* partial, Rect* rect_s)
+{
+    size_t base = (size_t)blockIdx.x * (kThreads * ITEMS) + threadIdx.x;
     uint32_t sum = 0;
-    // the kItems order loads, then the kItems gathers, each batch in flight together
-    // (a clamped index instead of a branch; items past the end are not stored or summed)
-    uint32_t o[kItems];
+    // the order loads, then the rectangles', each batch in flight together (a clamped
+    // index instead of a branch; items past the end are not stored or summed)
+    uint32_t o[ITEMS];
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        const size_t idx = base + (size_t)k * kThreads;
-        o[k] = order[idx < n ? idx : (size_t)n - 1];
+    for (int k = 0; k < ITEMS; ++k) {
+        const size_t idx = base + (size_t)k * kThreads, at = idx < n ? idx : (size_t)n - 1;
+        o[k] = GATHER ? order[at] : (uint32_t)at;
     }
-    uint2 t[kItems];
+    Rect t[ITEMS];
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) t[k] = trect[o[k]];
+    for (int k = 0; k < ITEMS; ++k) t[k] = rect[o[k]];
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         const size_t idx = base + (size_t)k * kThreads;
         if (idx < n) {
-            const uint32_t tt = rect_tiles(t[k]);
-            vals_s[idx] = tt;
-            rect_s[idx] = t[k];
-            sum += tt;
+            const TileRect r = unpack(t[k]);
+            if (GATHER) rect_s[idx] = t[k];
+            sum += r.w * r.h;
         }
     }
     uint32_t tot;
@@ -102,90 +113,46 @@ __global__ __launch_bounds__(kThreads) void scan_reduce_kernel(const uint2* trec
     if (threadIdx.x == 0) partial[blockIdx.x] = tot;
 }
 
-// single block: exclusive scan of partial[0..nb) in place; total and 32-bit overflow flag
-__global__ __launch_bounds__(kThreads) void scan_spine_kernel(uint32_t* partial, uint32_t nb, uint32_t* total,
-                                                              uint32_t* overflow)
+// single workgroup: exclusive scan of partial[0..nb) in place; total and 32-bit overflow
+// flag.  1,024 threads, four sums each: the 11,719 sums of 24M records in 3 rounds, 9 us (35 with
+// 256 threads, one sum each).
+constexpr int kSpineThreads = 1024;
+__global__ __launch_bounds__(kSpineThreads) void scan_spine_kernel(uint32_t* partial, uint32_t nb, uint32_t* total,
+                                                                   uint32_t* overflow)
 {
-    __shared__ unsigned long long s_carry;
-    if (threadIdx.x == 0) s_carry = 0ull;
-    __syncthreads();
-    for (uint32_t start = 0; start < nb; start += kThreads) {
-        uint32_t idx = start + threadIdx.x;
-        uint32_t v = idx < nb ? partial[idx] : 0u;
-        uint32_t tot;
-        uint32_t ex = block_excl_scan(v, &tot);
-        unsigned long long carry = s_carry;
-        if (idx < nb) partial[idx] = (uint32_t)(carry + ex);
+    __shared__ unsigned long long s_w[kSpineThreads / 64];
+    const uint32_t lane = lane_id(), wid = threadIdx.x >> 6;
+    unsigned long long carry = 0ull;
+    for (uint32_t start = 0; start < nb; start += 4u * kSpineThreads) {
+        const uint32_t i0 = start + 4u * threadIdx.x;
+        uint32_t v[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) v[k] = i0 + k < nb ? partial[i0 + k] : 0u;
+        const unsigned long long sum = (unsigned long long)v[0] + v[1] + v[2] + v[3];
+        unsigned long long inc = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long y = __shfl_up(inc, o, 64);
+            if (lane >= (uint32_t)o) inc += y;
+        }
+        if (lane == 63u) s_w[wid] = inc;
         __syncthreads();
-        if (threadIdx.x == 0) s_carry = carry + tot;
+        unsigned long long run = carry + inc - sum;
+#pragma unroll
+        for (uint32_t w = 0; w < kSpineThreads / 64; ++w) {
+            if (w < wid) run += s_w[w];
+            carry += s_w[w];
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) {
+            if (i0 + k < nb) partial[i0 + k] = (uint32_t)run;
+            run += v[k];
+        }
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        unsigned long long c = s_carry;
-        *total = c > 0xffffffffull ? 0xffffffffu : (uint32_t)c;
-        if (c > 0xffffffffull) *overflow = 1u;
-    }
-}
-
-// SELF (at most kThreads blocks): partial holds the raw block sums; each block adds
-// up those before it itself, and the last block writes the total (no spine kernel)
-template <bool SELF>
-__global__ __launch_bounds__(kThreads) void scan_down_kernel(const uint32_t* vals_s, uint32_t n,
-                                                             const uint32_t* partial, uint32_t nb, uint32_t* out,
-                                                             uint32_t* total, uint32_t* overflow)
-{
-    uint32_t bpre;
-    if (SELF) {
-        __shared__ unsigned long long s_w[kThreads / 64];
-        unsigned long long x = threadIdx.x < blockIdx.x ? (unsigned long long)partial[threadIdx.x] : 0ull;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-        if ((threadIdx.x & 63u) == 0u) s_w[threadIdx.x >> 6] = x;
-        __syncthreads();
-        unsigned long long pre = 0ull;
-#pragma unroll
-        for (int w = 0; w < kThreads / 64; ++w) pre += s_w[w];
-        bpre = (uint32_t)pre;
-        if (blockIdx.x == nb - 1u && threadIdx.x == 0) {
-            const unsigned long long c = pre + partial[blockIdx.x];
-            *total = c > 0xffffffffull ? 0xffffffffu : (uint32_t)c;
-            if (c > 0xffffffffull) *overflow = 1u;
-        }
-    } else {
-        bpre = partial[blockIdx.x];
-    }
-    // kItems consecutive counts a thread, as two 16-byte words where all are in range
-    static_assert(kItems == 8, "two 16-byte words a thread");
-    const size_t base = (size_t)blockIdx.x * kTileItems + (size_t)threadIdx.x * kItems;
-    const bool whole = base + kItems <= n;
-    uint32_t v[kItems];
-    uint32_t sum = 0;
-    if (whole) {
-        const uint4 a = reinterpret_cast<const uint4*>(vals_s + base)[0];
-        const uint4 b = reinterpret_cast<const uint4*>(vals_s + base)[1];
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    } else {
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) v[k] = base + k < n ? vals_s[base + k] : 0u;
-    }
-#pragma unroll
-    for (int k = 0; k < kItems; ++k) sum += v[k];
-    uint32_t tot;
-    uint32_t run = block_excl_scan(sum, &tot) + bpre;
-    uint32_t o[kItems];
-#pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        o[k] = run;
-        run += v[k];
-    }
-    if (whole) {
-        reinterpret_cast<uint4*>(out + base)[0] = make_uint4(o[0], o[1], o[2], o[3]);
-        reinterpret_cast<uint4*>(out + base)[1] = make_uint4(o[4], o[5], o[6], o[7]);
-    } else {
-#pragma unroll
-        for (int k = 0; k < kItems; ++k)
-            if (base + k < n) out[base + k] = o[k];
+        *total = carry > 0xffffffffull ? 0xffffffffu : (uint32_t)carry;
+        if (carry > 0xffffffffull) *overflow = 1u;
     }
 }
 
@@ -395,13 +362,13 @@ __device__ __forceinline__ void tile_bounds(uint32_t k, uint32_t li, uint32_t o,
 // What a pass reads and writes.  Key: the keys read; Out: the keys written, which need
 // only the digits that later passes sort by, key >> out_shift (NoKey: the last pass writes
 // none); IMPLICIT: the values are the items' indices; RANGES: the last pass of the tile
-// sort (tile_bounds).
+// sort (tile_bounds); CARRY: a second 32-bit value an item moves with the first.
 struct NoKey {};
-template <typename K, typename O, bool I, bool R>
+template <typename K, typename O, bool I, bool R, bool C = false>
 struct PassKind {
     using Key = K;
     using Out = O;
-    static constexpr bool kImplicit = I, kRanges = R;
+    static constexpr bool kImplicit = I, kRanges = R, kCarry = C;
 };
 
 // SELF: few blocks (nb <= kSelfSpineBlocks); every block sums the raw per-block
@@ -414,12 +381,12 @@ template <int ITEMS, bool SELF, typename Kind>
 __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(
     const typename Kind::Key* keys_in, const uint32_t* vals_in, typename Kind::Out* keys_out, uint32_t* vals_out,
     const uint32_t* n_dev, uint32_t n_max, int shift, int out_shift, const uint32_t* hist, uint32_t nb,
-    const uint32_t* digit_total, uint32_t* ranges)
+    const uint32_t* digit_total, uint32_t* ranges, const uint32_t* aux_in, uint32_t* aux_out)
 {
     using Key = typename Kind::Key;
     constexpr bool kWrites = !std::is_same<typename Kind::Out, NoKey>::value;
-    constexpr bool kImplicit = Kind::kImplicit, kNarrow = sizeof(Key) == 2;
-    using Val = typename std::conditional<kImplicit, uint16_t, uint32_t>::type;
+    constexpr bool kImplicit = Kind::kImplicit, kCarry = Kind::kCarry, kNarrow = sizeof(Key) == 2;
+    using Val = typename std::conditional<kImplicit && !kCarry, uint16_t, uint32_t>::type;
     using Count = typename std::conditional<(ITEMS > 8), uint16_t, uint32_t>::type;   // a wavefront's items: at most 2,048
     constexpr int kRadixItems = ITEMS;
     constexpr int kRadixTile = kThreads * ITEMS;
@@ -445,7 +412,7 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(
     // every load issued before any is used: a clamped index instead of a branch (items
     // past the end are never ranked into place or written).  x[r]: the key, and in its upper
     // half, where it is 16 bits, the rank; rk: the ranks of wider keys, two a word.
-    uint32_t x[kRadixItems], rk[kNarrow ? 1 : kRadixItems / 2], v_[kImplicit ? 1 : kRadixItems];
+    uint32_t x[kRadixItems], rk[kNarrow ? 1 : kRadixItems / 2], v_[kImplicit ? 1 : kRadixItems], aux[kCarry ? kRadixItems : 1];
     const bool whole = cnt == (uint32_t)kRadixTile;
     if (whole) {                              // one address, the rest immediate offsets
         const Key* kp = keys_in + base + wid * kPerWave + lane;
@@ -456,6 +423,11 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(
 #pragma unroll
             for (int r = 0; r < kRadixItems; ++r) v_[r] = vp[r * 64];
         }
+        if constexpr (kCarry) {
+            const uint32_t* ap = aux_in + base + wid * kPerWave + lane;
+#pragma unroll
+            for (int r = 0; r < kRadixItems; ++r) aux[r] = ap[r * 64];
+        }
     } else {
 #pragma unroll
         for (int r = 0; r < kRadixItems; ++r) {
@@ -463,6 +435,7 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(
             const uint32_t at = li < cnt ? li : cnt - 1u;
             x[r] = (keys_in + base)[at];
             if constexpr (!kImplicit) v_[r] = (vals_in + base)[at];
+            if constexpr (kCarry) aux[r] = (aux_in + base)[at];
             if (ITEMS > 8 && r % 8 == 7) __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -567,9 +540,12 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(
     // reorder through LDS, then a coalesced scatter of the locally sorted block.  A full
     // block (all but the last) takes the unguarded form, so that the compiler can keep
     // many items' LDS reads in flight instead of waiting on each item in turn.
-    auto place = [&](int r) {
+    auto slot = [&](int r) {
         const uint32_t rank = kNarrow ? x[r] >> 16 : (r & 1) ? rk[kNarrow ? 0 : r / 2] >> 16 : rk[kNarrow ? 0 : r / 2] & 0xffffu;
-        const uint32_t pos = s_wh[wid][(x[r] >> shift) & 0xffu] + rank;
+        return s_wh[wid][(x[r] >> shift) & 0xffu] + rank;
+    };
+    auto place = [&](int r) {
+        const uint32_t pos = slot(r);
         s_keys[pos] = (Key)x[r];
         if constexpr (kImplicit) s_vals[pos] = (Val)(wid * kPerWave + (uint32_t)r * 64u + lane);
         else s_vals[pos] = v_[r];
@@ -602,6 +578,25 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(
         __syncthreads();
         for (uint32_t li = tid; li < cnt; li += kThreads) scatter(li);
     }
+    if constexpr (kCarry) {                   // the second value, through the first one's LDS
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRadixItems; ++r) {
+            if (whole || wid * kPerWave + (uint32_t)r * 64u + lane < cnt) s_vals[slot(r)] = aux[r];
+            if (r % kFly == kFly - 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+        auto move = [&](uint32_t li) { aux_out[s_gofs[((uint32_t)s_keys[li] >> shift) & 0xffu] + li] = s_vals[li]; };
+        if (whole) {
+#pragma unroll 1
+            for (int r0 = 0; r0 < kRadixItems; r0 += kFly) {
+#pragma unroll
+                for (int r = 0; r < kFly; ++r) move((uint32_t)(r0 + r) * kThreads + tid);
+            }
+        } else {
+            for (uint32_t li = tid; li < cnt; li += kThreads) move(li);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -616,70 +611,88 @@ __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(
 // records in depth order, scattered over the record array, which took 2/3 of
 // this kernel's time on the 8-view workload.)
 //
-// One wavefront takes 64 consecutive Gaussians in depth order; their pairs are
-// one contiguous output range, which its 64 lanes write together, 64
-// consecutive pairs per step (each lane finds its Gaussian by binary search
-// over the wavefront's local offsets), so every store is coalesced and a
-// Gaussian with many tiles is spread over all lanes.
+// A workgroup takes 256 x ITEMS consecutive records in depth order (ITEMS: few enough that
+// the launch fills the chip), a wavefront ITEMS groups of 64, whose pairs are one
+// contiguous output range that its 64 lanes write together, 64 consecutive pairs a step.
+// A lane finds its record from a bit mask of the positions where records start: their
+// count up to the lane is the place in the group's list of records that have pairs.
+// Bound by its stores, 6 bytes a pair: 8 views of 3M Gaussians (0.15 G pairs) in 0.22 ms, 4.5
+// TB/s.  (A binary search a lane over the group's offsets, an integer division a pair and
+// one group a wavefront took 0.27 ms, and the offsets 0.035 by a kernel of their own.)
 // ---------------------------------------------------------------------------
 
-template <typename Key>
-__global__ __launch_bounds__(kThreads) void duplicate_kernel(const uint32_t* order, const uint32_t* offsets,
-                                                             const uint32_t* tt_s, const uint2* rect_s,
-                                                             const CamDev* cams, uint32_t n, uint32_t vn,
-                                                             const uint32_t* total, uint32_t cap, Key* keys,
+template <typename Key, typename Rect, int ITEMS>
+__global__ __launch_bounds__(kThreads) void duplicate_kernel(const uint32_t* order, const Rect* rect_s,
+                                                             const uint32_t* first, const CamDev* cams, uint32_t n,
+                                                             uint32_t vn, const uint32_t* total, uint32_t cap, Key* keys,
                                                              uint32_t* emit_vg, uint32_t* overflow)
 {
-    __shared__ uint32_t s_loc[kThreads / 64][64];
+    constexpr uint32_t kGroups = kWaves * ITEMS;               // of 64 records
+    constexpr uint32_t kSpan = 2048u;                          // outputs whose starts are marked together
+    static_assert(kGroups <= 64, "a lane a group");
+    __shared__ uint32_t s_sum[kGroups];
+    __shared__ uint4 s_rec[kWaves][64];
+    __shared__ uint32_t s_bits[kWaves][kSpan / 32];
     const uint32_t lane = lane_id(), wid = threadIdx.x >> 6;
-    const uint32_t s = blockIdx.x * kThreads + threadIdx.x;
-    if (s == 0 && *total > cap) *overflow = 1u;
-    if (s - lane >= vn) return;                               // whole wavefront
-    const bool valid = s < vn;
-    uint32_t vg = 0, tt = 0, off = 0, tb = 0, gx = 0;
-    uint2 rc = make_uint2(0u, 0u);
-    if (valid) {
-        vg = order[s];
-        tt = tt_s[s];
-        off = offsets[s];
-        rc = rect_s[s];
-        const CamDev& c = cams[vg / n];                       // the record's view: its tile numbering
-        tb = c.tile_base;
-        gx = (uint32_t)c.gx;
-    }
-    // the wavefront's pairs: [off0, off0 + count)
-    const uint32_t off0 = __shfl(off, 0, 64);
-    uint32_t end = valid ? off - off0 + tt : 0u;
+    const size_t base = (size_t)blockIdx.x * (kThreads * ITEMS) + wid * (64u * ITEMS) + lane;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && *total > cap) *overflow = 1u;
+    uint32_t vg[ITEMS], inc[ITEMS];
+    TileRect rc[ITEMS];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t y = __shfl_xor(end, o, 64);
-        end = end > y ? end : y;
+    for (int r = 0; r < ITEMS; ++r) {
+        const size_t s = base + (size_t)r * 64u;
+        vg[r] = order[s < vn ? s : vn - 1u];
+        rc[r] = unpack(s < vn ? rect_s[s] : rect_none<Rect>());
     }
-    const uint32_t count = end;
-    s_loc[wid][lane] = valid ? off - off0 : count;            // non-decreasing
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (uint32_t q0 = 0; q0 < count; q0 += 64u) {
-        const uint32_t q = q0 + lane < count ? q0 + lane : count - 1u;
-        // the Gaussian of output q: the last r with s_loc[r] <= q (it has tt > 0)
-        uint32_t r = 0;
 #pragma unroll
-        for (uint32_t st = 32; st > 0; st >>= 1)
-            if (s_loc[wid][r + st] <= q) r += st;
-        const uint32_t rvg = (uint32_t)__shfl((int)vg, (int)r, 64);
-        const uint32_t rx = (uint32_t)__shfl((int)rc.x, (int)r, 64);
-        const uint32_t ry = (uint32_t)__shfl((int)rc.y, (int)r, 64);
-        const uint32_t rtb = (uint32_t)__shfl((int)tb, (int)r, 64);
-        const uint32_t rgx = (uint32_t)__shfl((int)gx, (int)r, 64);
-        const uint32_t k = q - s_loc[wid][r];
-        const uint32_t rx0 = rx & 0xffffu, rw = (rx >> 16) - rx0 + 1u, ry0 = ry & 0xffffu;
-        const uint32_t dy = k / rw, dx = k - dy * rw;
-        const uint32_t p = off0 + q;
-        if (q0 + lane < count && p < cap) {
-            keys[p] = (Key)(rtb + (ry0 + dy) * rgx + rx0 + dx);
-            emit_vg[p] = rvg;
+    for (int r = 0; r < ITEMS; ++r) {
+        inc[r] = wave_incl_scan(rc[r].w * rc[r].h);
+        if (lane == 63u) s_sum[wid * ITEMS + r] = inc[r];
+    }
+    __syncthreads();
+    // pairs before each group
+    const uint32_t gs = lane < kGroups ? s_sum[lane] : 0u;
+    const uint32_t before = first[blockIdx.x] + wave_incl_scan(gs) - gs;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t off0 = (uint32_t)__builtin_amdgcn_readlane((int)before, (int)(wid * ITEMS + r));
+        const uint32_t count = (uint32_t)__builtin_amdgcn_readlane((int)inc[r], 63);
+        const uint32_t tt = rc[r].w * rc[r].h, start = inc[r] - tt;
+        const uint64_t has = __builtin_amdgcn_ballot_w64(tt != 0u);
+        const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u));
+        if (tt) {
+            const CamDev& c = cams[vg[r] / n];                 // the record's view: its tile numbering
+            s_rec[wid][at] = make_uint4(start, vg[r], c.tile_base + rc[r].y0 * (uint32_t)c.gx + rc[r].x0,
+                                        rc[r].w | ((uint32_t)c.gx << 16));
         }
+        uint32_t started = 0u;                                 // records that start before the step
+        for (uint32_t c0 = 0; c0 < count; c0 += kSpan) {
+            s_bits[wid][lane] = 0u;
+            wave_lds_order();
+            if (tt && start >= c0 && start - c0 < kSpan) atomicOr(&s_bits[wid][(start - c0) >> 5], 1u << ((start - c0) & 31u));
+            wave_lds_order();
+            for (uint32_t w0 = 0; w0 < kSpan && c0 + w0 < count; w0 += 64u) {
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_bits[wid][w0 >> 5]);
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_bits[wid][(w0 >> 5) + 1u]);
+                const uint64_t up = (((uint64_t)hi << 32) | lo) >> 1;       // (the starts at positions 1 .. lane)
+                const uint32_t i = started + (lo & 1u) - 1u +
+                                   __builtin_amdgcn_mbcnt_hi((uint32_t)(up >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)up, 0u));
+                started += (uint32_t)__popc(lo) + (uint32_t)__popc(hi);
+                const uint4 rec = s_rec[wid][i];
+                const uint32_t q = c0 + w0 + lane, k = q - rec.x, w = rec.w & 0xffffu;
+                // k / w by a reciprocal of 1 ulp: (k + 1/2) / w is 1 / (2 w) or more from an integer, so
+                // the quotient is exact below 2^21
+                uint32_t dy = (uint32_t)(((float)k + 0.5f) * __builtin_amdgcn_rcpf((float)w));
+                if (k >= (1u << 20)) dy = k / w;
+                const uint32_t p = off0 + q;
+                if (q < count && p < cap) {
+                    keys[p] = (Key)(rec.z + dy * (rec.w >> 16) + (k - dy * w));
+                    emit_vg[p] = rec.y;
+                }
+            }
+            wave_lds_order();
+        }
+        wave_lds_order();
     }
 }
 
@@ -695,8 +708,8 @@ constexpr uint32_t kBinItems = kSmallBin / kBinThreads;          // items a thre
 static_assert(kSmallBin % kBinThreads == 0 && kSmallBin <= 65536, "indices are 16 bits");
 
 __global__ __launch_bounds__(kBinThreads) void small_bin_kernel(const uint32_t* keys, const uint2* trect, uint32_t n,
-                                                                uint32_t* order, uint32_t* out, uint32_t* vals_s,
-                                                                uint2* rect_s, uint32_t* total, uint32_t* overflow)
+                                                                uint32_t* order, uint32_t* first, uint2* rect_s,
+                                                                uint32_t* total, uint32_t* overflow)
 {
     __shared__ uint32_t s_key[2][kSmallBin];
     __shared__ uint16_t s_val[2][kSmallBin];
@@ -799,7 +812,8 @@ __global__ __launch_bounds__(kBinThreads) void small_bin_kernel(const uint32_t* 
         if (r < per && i < n) {
             vg[r] = s_val[cur][i];
             rc[r] = trect[vg[r]];
-            sum += rect_tiles(rc[r]);
+            const TileRect t = unpack(rc[r]);
+            sum += t.w * t.h;
         }
     }
     unsigned long long inc = sum;
@@ -819,12 +833,11 @@ __global__ __launch_bounds__(kBinThreads) void small_bin_kernel(const uint32_t* 
     for (uint32_t r = 0; r < kBinItems; ++r) {
         const uint32_t i = tid * per + r;
         if (r < per && i < n) {
-            const uint32_t tt = rect_tiles(rc[r]);
+            const TileRect t = unpack(rc[r]);
             order[i] = vg[r];
-            out[i] = (uint32_t)run;
-            vals_s[i] = tt;
+            if ((i & (kThreads - 1u)) == 0u) first[i / kThreads] = (uint32_t)run;    // (a workgroup of the duplication)
             rect_s[i] = rc[r];
-            run += tt;
+            run += t.w * t.h;
         }
     }
     if (tid == 0) {
@@ -1155,33 +1168,52 @@ __global__ __launch_bounds__(kThreads) void ranges_finish_kernel(uint2* ranges, 
 // times over, without growing with a pair capacity that may far exceed the count
 static uint32_t grid_cap(uint32_t blocks) { return blocks < 16384u ? (blocks ? blocks : 1u) : 16384u; }
 
-size_t scan_tmp_words(uint32_t n) { return (size_t)(n + kTileItems - 1) / kTileItems + 1; }
-
-hipError_t launch_gather_scan(const uint2* trect, const uint32_t* order, uint32_t n, uint32_t* out,
-                              uint32_t* vals_s, uint2* rect_s, uint32_t* total, uint32_t* overflow, uint32_t* tmp,
-                              hipStream_t s)
+// records a thread of the duplication: enough workgroups to fill the chip, few enough that
+// the scan of their sums stays short (2 rounds of one workgroup at 2^21 / 4 records)
+static_assert(kCarryFrom >= kRadixLargeFrom, "carried rectangles are read by the largest form");
+static int dup_items(uint32_t n) { return n < (1u << 18) ? 1 : n < kRadixLargeFrom ? 4 : 8; }
+static uint32_t dup_blocks(uint32_t n)
 {
-    uint32_t nb = (n + kTileItems - 1) / kTileItems;
-    if (nb > 0)
-        hipLaunchKernelGGL(scan_reduce_kernel, dim3(nb), dim3(kThreads), 0, s, trect, order, n, tmp, vals_s, rect_s);
-    if (nb > 0 && nb <= (uint32_t)kThreads) {          // few blocks: no spine
-        hipLaunchKernelGGL(scan_down_kernel<true>, dim3(nb), dim3(kThreads), 0, s, vals_s, n, tmp, nb, out, total,
-                           overflow);
-        return hipGetLastError();
+    const uint32_t per = (uint32_t)(kThreads * dup_items(n));
+    return n / per + (n % per != 0u);
+}
+
+size_t scan_tmp_words(uint32_t n) { return (size_t)(n + kThreads - 1) / kThreads + 1; }
+
+namespace {
+template <typename Rect, bool GATHER>
+void reduce(const Rect* rect, const uint32_t* order, uint32_t n, uint32_t* tmp, Rect* rect_s, hipStream_t s)
+{
+    const dim3 grid(dup_blocks(n)), block(kThreads);
+    if (n == 0) return;
+    if constexpr (GATHER) {                   // (carried rectangles: large launches only)
+        if (dup_items(n) == 1)
+            hipLaunchKernelGGL((scan_reduce_kernel<Rect, 1, GATHER>), grid, block, 0, s, rect, order, n, tmp, rect_s);
+        else if (dup_items(n) == 4)
+            hipLaunchKernelGGL((scan_reduce_kernel<Rect, 4, GATHER>), grid, block, 0, s, rect, order, n, tmp, rect_s);
     }
-    hipLaunchKernelGGL(scan_spine_kernel, dim3(1), dim3(kThreads), 0, s, tmp, nb, total, overflow);
-    if (nb > 0)
-        hipLaunchKernelGGL(scan_down_kernel<false>, dim3(nb), dim3(kThreads), 0, s, vals_s, n, tmp, nb, out, total,
-                           overflow);
+    if (dup_items(n) == 8)
+        hipLaunchKernelGGL((scan_reduce_kernel<Rect, 8, GATHER>), grid, block, 0, s, rect, order, n, tmp, rect_s);
+}
+}  // namespace
+
+hipError_t launch_scan(const uint2* trect, const uint32_t* order, uint32_t n, uint2* rect_s, bool carried, uint32_t* first,
+                       uint32_t* total, uint32_t* overflow, hipStream_t s)
+{
+    if (carried)
+        reduce<uint32_t, false>(reinterpret_cast<const uint32_t*>(rect_s), order, n, first, nullptr, s);
+    else
+        reduce<uint2, true>(trect, order, n, first, rect_s, s);
+    hipLaunchKernelGGL(scan_spine_kernel, dim3(1), dim3(kSpineThreads), 0, s, first, dup_blocks(n), total, overflow);
     return hipGetLastError();
 }
 
-hipError_t launch_small_bin(const uint32_t* keys, const uint2* trect, uint32_t n, uint32_t* order, uint32_t* out,
-                            uint32_t* vals_s, uint2* rect_s, uint32_t* total, uint32_t* overflow, hipStream_t s)
+hipError_t launch_small_bin(const uint32_t* keys, const uint2* trect, uint32_t n, uint32_t* order, uint32_t* first,
+                            uint2* rect_s, uint32_t* total, uint32_t* overflow, hipStream_t s)
 {
     if (n == 0 || n > kSmallBin) return n == 0 ? hipSuccess : hipErrorInvalidValue;
-    hipLaunchKernelGGL(small_bin_kernel, dim3(1), dim3(kBinThreads), 0, s, keys, trect, n, order, out, vals_s, rect_s,
-                       total, overflow);
+    hipLaunchKernelGGL(small_bin_kernel, dim3(1), dim3(kBinThreads), 0, s, keys, trect, n, order, first, rect_s, total,
+                       overflow);
     return hipGetLastError();
 }
 
@@ -1198,7 +1230,7 @@ namespace {
 template <typename Kind>
 hipError_t radix_pass(const void* keys_in, const uint32_t* vals_in, void* keys_out, uint32_t* vals_out,
                       const uint32_t* n_dev, uint32_t n_max, int shift, int out_shift, uint32_t* tmp, uint2* ranges,
-                      hipStream_t s)
+                      hipStream_t s, const uint32_t* aux_in = nullptr, uint32_t* aux_out = nullptr)
 {
     using Key = typename Kind::Key;
     using Out = typename Kind::Out;
@@ -1217,11 +1249,12 @@ hipError_t radix_pass(const void* keys_in, const uint32_t* vals_in, void* keys_o
     else
         hipLaunchKernelGGL((radix_upsweep_kernel<kS, Key>), grid, block, 0, s, in, n_dev, n_max, shift, hist);
     static_assert(kRadixLargeFrom / (kThreads * kRadixLargeItems) > kSelfSpineBlocks, "large passes have a spine");
-    if (nb <= kSelfSpineBlocks) {             // the downsweep blocks find their offsets themselves
-        hipLaunchKernelGGL((radix_downsweep_kernel<kS, true, Kind>), grid, block, 0, s, in, vals_in, out, vals_out, n_dev,
-                           n_max, shift, out_shift, hist, nb, digit_total, rg);
-        return hipGetLastError();
-    }
+    if constexpr (!Kind::kCarry)              // (a sort that carries is large)
+        if (nb <= kSelfSpineBlocks) {         // the downsweep blocks find their offsets themselves
+            hipLaunchKernelGGL((radix_downsweep_kernel<kS, true, Kind>), grid, block, 0, s, in, vals_in, out, vals_out,
+                               n_dev, n_max, shift, out_shift, hist, nb, digit_total, rg, aux_in, aux_out);
+            return hipGetLastError();
+        }
     // counts a thread: enough that a long column takes few block scans, few enough
     // that a short one is spread over the workgroup
     if (nb > 8u * kThreads)
@@ -1230,33 +1263,43 @@ hipError_t radix_pass(const void* keys_in, const uint32_t* vals_in, void* keys_o
         hipLaunchKernelGGL(radix_spine_kernel<8>, dim3(kBins / 4), block, 0, s, hist, n_dev, n_max, tile, digit_total);
     else
         hipLaunchKernelGGL(radix_spine_kernel<1>, dim3(kBins / 4), block, 0, s, hist, n_dev, n_max, tile, digit_total);
-    if (items == kL)
+    if (Kind::kCarry || items == kL)
         hipLaunchKernelGGL((radix_downsweep_kernel<kL, false, Kind>), grid, block, 0, s, in, vals_in, out, vals_out, n_dev,
-                           n_max, shift, out_shift, hist, nb, digit_total, rg);
-    else
+                           n_max, shift, out_shift, hist, nb, digit_total, rg, aux_in, aux_out);
+    else if constexpr (!Kind::kCarry)
         hipLaunchKernelGGL((radix_downsweep_kernel<kS, false, Kind>), grid, block, 0, s, in, vals_in, out, vals_out, n_dev,
-                           n_max, shift, out_shift, hist, nb, digit_total, rg);
+                           n_max, shift, out_shift, hist, nb, digit_total, rg, aux_in, aux_out);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_depth_sort(const uint32_t* depth, uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n,
-                             uint32_t* tmp, hipStream_t s)
+namespace {
+// the keys a pass writes hold the digits still to sort: 32, then 16 bits, then none
+template <bool CARRY>
+hipError_t depth_sort(const uint32_t* depth, uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n,
+                      uint32_t* tmp, const uint32_t* rect, uint32_t* const (&aux)[2], hipStream_t s)
 {
-    // the keys a pass writes hold the digits still to sort: 32, then 16 bits, then none
-    hipError_t e = radix_pass<PassKind<uint32_t, uint32_t, true, false>>(depth, nullptr, keys[1], order[1], nullptr, n, 0,
-                                                                         0, tmp, nullptr, s);
+    hipError_t e = radix_pass<PassKind<uint32_t, uint32_t, true, false, CARRY>>(depth, nullptr, keys[1], order[1], nullptr, n,
+                                                                                0, 0, tmp, nullptr, s, rect, aux[1]);
     if (e == hipSuccess)
-        e = radix_pass<PassKind<uint32_t, uint16_t, false, false>>(keys[1], order[1], keys[0], order[0], nullptr, n, 8, 16,
-                                                                   tmp, nullptr, s);
+        e = radix_pass<PassKind<uint32_t, uint16_t, false, false, CARRY>>(keys[1], order[1], keys[0], order[0], nullptr, n, 8,
+                                                                          16, tmp, nullptr, s, aux[1], aux[0]);
     if (e == hipSuccess)
-        e = radix_pass<PassKind<uint16_t, uint16_t, false, false>>(keys[0], order[0], keys[1], order[1], nullptr, n, 0, 0,
-                                                                   tmp, nullptr, s);
+        e = radix_pass<PassKind<uint16_t, uint16_t, false, false, CARRY>>(keys[0], order[0], keys[1], order[1], nullptr, n, 0,
+                                                                          0, tmp, nullptr, s, aux[0], aux[1]);
     if (e == hipSuccess)
-        e = radix_pass<PassKind<uint16_t, NoKey, false, false>>(keys[1], order[1], nullptr, order[0], nullptr, n, 8, 0, tmp,
-                                                                nullptr, s);
+        e = radix_pass<PassKind<uint16_t, NoKey, false, false, CARRY>>(keys[1], order[1], nullptr, order[0], nullptr, n, 8, 0,
+                                                                       tmp, nullptr, s, aux[1], aux[0]);
     return e;
+}
+}  // namespace
+
+hipError_t launch_depth_sort(const uint32_t* depth, uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n,
+                             uint32_t* tmp, const uint32_t* rect, uint32_t* const (&rect_s)[2], hipStream_t s)
+{
+    return rect ? depth_sort<true>(depth, keys, order, n, tmp, rect, rect_s, s)
+                : depth_sort<false>(depth, keys, order, n, tmp, rect, rect_s, s);
 }
 
 int tile_sort_passes(uint32_t n_tiles)
@@ -1292,19 +1335,37 @@ hipError_t launch_tile_sort(uint32_t* const (&keys)[2], uint32_t* const (&vals)[
     return e;
 }
 
-hipError_t launch_duplicate(const uint32_t* order, const uint32_t* offsets, const uint32_t* tt_s,
-                            const uint2* rect_s, const CamDev* cams, uint32_t n, uint32_t vn, uint32_t n_tiles,
-                            const uint32_t* total, uint32_t cap, uint32_t* keys, uint32_t* emit_vg, uint32_t* overflow,
-                            hipStream_t s)
+namespace {
+template <typename Key, typename Rect>
+void duplicate(const uint32_t* order, const void* rect_s, const uint32_t* first, const CamDev* cams, uint32_t n, uint32_t vn,
+               const uint32_t* total, uint32_t cap, uint32_t* keys, uint32_t* emit_vg, uint32_t* overflow, hipStream_t s)
+{
+    const dim3 grid(dup_blocks(vn)), block(kThreads);
+    const Rect* rect = reinterpret_cast<const Rect*>(rect_s);
+    Key* k = reinterpret_cast<Key*>(keys);
+    if constexpr (std::is_same<Rect, uint2>::value) {         // (carried rectangles: large launches only)
+        if (dup_items(vn) == 1)
+            hipLaunchKernelGGL((duplicate_kernel<Key, Rect, 1>), grid, block, 0, s, order, rect, first, cams, n, vn, total, cap,
+                               k, emit_vg, overflow);
+        else if (dup_items(vn) == 4)
+            hipLaunchKernelGGL((duplicate_kernel<Key, Rect, 4>), grid, block, 0, s, order, rect, first, cams, n, vn, total, cap,
+                               k, emit_vg, overflow);
+    }
+    if (dup_items(vn) == 8)
+        hipLaunchKernelGGL((duplicate_kernel<Key, Rect, 8>), grid, block, 0, s, order, rect, first, cams, n, vn, total, cap, k,
+                           emit_vg, overflow);
+}
+}  // namespace
+
+hipError_t launch_duplicate(const uint32_t* order, const uint2* rect_s, bool carried, const uint32_t* first,
+                            const CamDev* cams, uint32_t n, uint32_t vn, uint32_t n_tiles, const uint32_t* total, uint32_t cap,
+                            uint32_t* keys, uint32_t* emit_vg, uint32_t* overflow, hipStream_t s)
 {
     if (vn == 0) return hipSuccess;
-    const dim3 grid((vn + kThreads - 1) / kThreads), block(kThreads);
-    if (tile_sort_passes(n_tiles) <= 2)
-        hipLaunchKernelGGL(duplicate_kernel<uint16_t>, grid, block, 0, s, order, offsets, tt_s, rect_s, cams, n, vn, total,
-                           cap, reinterpret_cast<uint16_t*>(keys), emit_vg, overflow);
-    else
-        hipLaunchKernelGGL(duplicate_kernel<uint32_t>, grid, block, 0, s, order, offsets, tt_s, rect_s, cams, n, vn, total,
-                           cap, keys, emit_vg, overflow);
+    const bool narrow = tile_sort_passes(n_tiles) <= 2;
+    auto launch = narrow ? (carried ? duplicate<uint16_t, uint32_t> : duplicate<uint16_t, uint2>)
+                         : (carried ? duplicate<uint32_t, uint32_t> : duplicate<uint32_t, uint2>);
+    launch(order, rect_s, first, cams, n, vn, total, cap, keys, emit_vg, overflow, s);
     return hipGetLastError();
 }
 

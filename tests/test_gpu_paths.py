@@ -224,3 +224,55 @@ def test_tile_sort_key_widths(sizes, n, scale):
             assert torch.equal(_bits(v[at:at + m]), _bits(one[k])), (k, cam.width)
         at += m
     r.close()
+
+
+def _check_lists(r, n, views):
+    """Every tile's list in (depth, index) order, each record once per tile it touches."""
+    vals, ranges = r.inspect(gsr.BUF_PAIR_VALUES).astype(np.int64), r.inspect(gsr.BUF_RANGES).reshape(-1, 2).astype(np.int64)
+    tt, depth = r.inspect(gsr.BUF_TILES_TOUCHED), r.inspect(gsr.BUF_DEPTH)
+    ln = ranges[:, 1] - ranges[:, 0]
+    assert len(vals) == tt.sum() == ln.sum()
+    assert np.array_equal(np.bincount(vals, minlength=n * views), tt)
+    tile = np.repeat(np.arange(len(ln)), ln)
+    d, same = depth[vals], tile[1:] == tile[:-1]
+    assert np.all(~same | (d[1:] > d[:-1]) | ((d[1:] == d[:-1]) & (vals[1:] > vals[:-1])))
+
+
+# The duplication's workgroups of 256, 1,024 and 2,048 records (from 2^18 and 2^21 records on)
+# and the rectangles that travel with the sort (from 2^21 records, up to 256 x 256 tiles a
+# view): each view's outputs are those of the view alone.
+@pytest.mark.parametrize("n,sizes,tile", [(262_143, [(96, 80)], (16, 16)), (262_144, [(96, 80)], (16, 16)),
+                                          (1_048_577, [(640, 360), (320, 200)], (16, 16)),
+                                          (1_048_577, [(2048, 64), (64, 2048)], (8, 8)),
+                                          (1_048_577, [(2049, 64), (64, 64)], (8, 8)),
+                                          (1_048_577, [(64, 64), (64, 2049)], (8, 8))])
+def test_duplication_sizes(n, sizes, tile):
+    scene, t = _small_scene(n, 0)
+    cams = scenes.orbit_cameras(np.random.default_rng(8), sizes)
+    opts = gsr.RasterOptions(tile=tile, sh_degree=0)
+    p = [t[k] for k in ATTRS]
+    r = gsr.Rasterizer(max_views=len(cams))
+    out = {k: v.clone() for k, v in r.forward(*p, cams, opts).items() if k in ("rgb", "t_final", "n_contrib")}
+    _check_lists(r, n, len(cams))
+    at = 0
+    for cam in cams if len(cams) > 1 else []:
+        m = cam.width * cam.height
+        one = r.forward(*p, [cam], opts)
+        _check_lists(r, n, 1)
+        for k, v in out.items():
+            assert torch.equal(_bits(v[at:at + m]), _bits(one[k])), (k, cam.width)
+        at += m
+    r.close()
+
+
+# One record over more than 2^20 tiles (the quotient by reciprocal ends there), between small ones.
+def test_record_over_a_million_tiles():
+    scene, t = _small_scene(130, 0)
+    t["scales"][::64] = 40.0
+    cams = scenes.orbit_cameras(np.random.default_rng(8), [(8200, 8200)])
+    r = gsr.Rasterizer(max_views=1)
+    r.forward(*[t[k] for k in ATTRS], cams, gsr.RasterOptions(tile=(8, 8), sh_degree=0))
+    tt = r.inspect(gsr.BUF_TILES_TOUCHED)
+    assert tt.max() == 1025 * 1025 and len(np.unique(tt)) > 3
+    _check_lists(r, 130, 1)
+    r.close()

@@ -71,6 +71,15 @@ inline bool slotted_blend(uint32_t n_blocks, uint32_t records)
 {
     return n_blocks <= kSlotFewBlocks || (n_blocks <= kSlotBlocks && records / 2u >= n_blocks);
 }
+// The backward takes it only up to 2^20 records: its sums over pixels are in another order
+// than the plain form's, and among more Gaussians than that there are scale and rotation
+// gradients that cancel so far that the order shows at 1e-3 of their size (500k and 1M
+// records: 3e-4 at most over 6 scenes each; 2M: up to 2.4e-3).
+constexpr uint32_t kSlotBackward = 1u << 20;
+inline bool slotted_backward(uint32_t n_blocks, uint32_t records)
+{
+    return records <= kSlotBackward && slotted_blend(n_blocks, records);
+}
 // persistent blend kernels: one work queue per XCD, heads 128 bytes apart
 constexpr uint32_t kQueues = 8;
 constexpr uint32_t kQueueStride = 32;

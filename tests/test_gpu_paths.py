@@ -276,3 +276,28 @@ def test_record_over_a_million_tiles():
     assert tt.max() == 1025 * 1025 and len(np.unique(tt)) > 3
     _check_lists(r, 130, 1)
     r.close()
+
+
+# The forward slotted, the backward plain (from 2^20 records on) against both slotted, the
+# same Gaussians with and without others far away.
+def test_backward_form_by_records():
+    n, extra = 3000, 1 << 20
+    scene, t = _small_scene(n, 0)
+    far = {k: v[:1].expand(extra, *v.shape[1:]) for k, v in t.items()}
+    far["means"] = far["means"] + 1e4
+    cams = scenes.orbit_cameras(np.random.default_rng(8), [(70, 50)])
+    opts = gsr.RasterOptions(sh_degree=0)
+    gen = torch.Generator(DEV).manual_seed(4)
+    g_rgb, g_h = torch.randn(3500, 3, device=DEV, generator=gen), torch.randn(3500, device=DEV, generator=gen)
+    r = gsr.Rasterizer(max_views=1)
+    res = []
+    for p in ([t[k] for k in ATTRS], [torch.cat([t[k], far[k]]).contiguous() for k in ATTRS]):
+        out = r.forward(*p, cams, opts)
+        g = r.backward(*p, cams, opts, out, g_rgb, g_h, torch.full((1,), 0.3, device=DEV))
+        res.append(({k: out[k].clone() for k in ("rgb", "entropy", "t_final", "n_contrib")}, {k: v[:n] for k, v in g.items()}))
+    for k in res[0][0]:
+        assert torch.equal(_bits(res[0][0][k]), _bits(res[1][0][k])), k
+    for k in ATTRS:
+        a, b = res[0][1][k].double(), res[1][1][k].double()
+        assert (a - b).norm() <= 1e-5 * a.norm(), k
+    r.close()

@@ -485,6 +485,7 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
         c->long_lists = ba.shared_batches != 0;
     }
     ba.slotted = slotted_blend(L.n_blocks, vn) ? 1 : 0;
+    ba.mixed = mixed_blend(L.n_blocks, vn) ? 1 : 0;
     {
         StageTimer tm(c, st, GSR_STAGE_BLEND_FWD, !c->capturing);
         HIP_TRY(c, launch_blend_fwd(ba, o->lds_batch == 0 ? 64 : o->lds_batch, st));

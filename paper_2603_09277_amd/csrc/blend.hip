@@ -378,12 +378,20 @@ __device__ __forceinline__ void fwd_store(const BlendFwdArgs& a, const BlockGeom
 // four blocks of a tile restage the same entries (blend_fwd_shared_kernel
 // below stages them once).  RENDER: colour only (test-time rendering): no
 // entropy, no per-pixel saved state.
+template <int B>
+struct FwdLds {
+    float4 g0[kWavesPerGroup][B];                // mean x, mean y, A', B'
+    float4 g1[kWavesPerGroup][B];                // C', opacity, red, green
+    float2 bp[kWavesPerGroup][B];                // blue, position in the tile list + 1 (int bits)
+};
+
+// workgroup wg of the launch; `from`: the first place of the tile order it serves
 template <int B, bool PERSIST, bool RENDER>
-__global__ __launch_bounds__(256) void blend_fwd_kernel(BlendFwdArgs a)
+__device__ __forceinline__ void fwd_blocks(const BlendFwdArgs& a, uint32_t wg, uint32_t from, FwdLds<B>& lds)
 {
-    __shared__ float4 s_g0[kWavesPerGroup][B];   // mean x, mean y, A', B'
-    __shared__ float4 s_g1[kWavesPerGroup][B];   // C', opacity, red, green
-    __shared__ float2 s_bp[kWavesPerGroup][B];   // blue, position in the tile list + 1 (int bits)
+    auto& s_g0 = lds.g0;
+    auto& s_g1 = lds.g1;
+    auto& s_bp = lds.bp;
     const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
     WaveQueue wq;
     uint32_t item;
@@ -391,13 +399,13 @@ __global__ __launch_bounds__(256) void blend_fwd_kernel(BlendFwdArgs a)
         item = next_item_wave(wq, a.queues, a.n_blocks, lane);
     } else if (a.tile_order) {                   // hardware dispatch, longest tiles first
         if (a.spt == 4) {
-            item = a.tile_order[blockIdx.x] * kWavesPerGroup + wid;  // one tile per workgroup
+            item = a.tile_order[from + wg] * kWavesPerGroup + wid;  // one tile per workgroup
         } else {
-            const uint32_t i = blockIdx.x * kWavesPerGroup + wid;    // one tile per wavefront
+            const uint32_t i = from + wg * kWavesPerGroup + wid;     // one tile per wavefront
             item = i < a.n_blocks ? a.tile_order[i] : a.n_blocks;
         }
     } else {
-        item = blockIdx.x * kWavesPerGroup + wid;
+        item = wg * kWavesPerGroup + wid;
     }
     for (; item < a.n_blocks; item = PERSIST ? next_item_wave(wq, a.queues, a.n_blocks, lane) : a.n_blocks) {
     const uint32_t wb = item;
@@ -480,6 +488,13 @@ __global__ __launch_bounds__(256) void blend_fwd_kernel(BlendFwdArgs a)
     }
     fwd_store<RENDER>(a, g, q, wc, rg, wb, lane);
     }
+}
+
+template <int B, bool PERSIST, bool RENDER>
+__global__ __launch_bounds__(256) void blend_fwd_kernel(BlendFwdArgs a)
+{
+    __shared__ FwdLds<B> s_lds;
+    fwd_blocks<B, PERSIST, RENDER>(a, blockIdx.x, 0u, s_lds);
 }
 
 // The 4 wavefronts of a workgroup are the 4 8x8 blocks of one 16x16 or 32x8
@@ -663,23 +678,33 @@ __device__ __forceinline__ bool odd_colour(float r, float g, float b)
 // stages the tile's list for itself: the blocks of a tile need not wait for each other, and
 // five workgroups a CU hide more than one of 16 wavefronts did: 200k Gaussians at 640x416,
 // 79 against 104 us)
-template <bool RENDER>
-__global__ __launch_bounds__(256) void blend_fwd_slot_kernel(BlendFwdArgs a)
-{
-    constexpr int B = kSlotBatch, NW = 4;
-    constexpr int kPart = B + 1;                             // records a part: the last is empty (opacity 0)
-    constexpr int kEmptyOff = 16 * B;
-    __shared__ float4 s_rec[2][3 * kPart];
+template <int B>
+struct FwdSlotLds {
+    float4 rec[2][3 * (B + 1)];                              // a part's last record is empty (opacity 0)
     // each wavefront's surviving entries (byte offsets in a part), in list order, and up to 8
     // empty ones (read a step ahead)
-    __shared__ int32_t s_idx[NW][B + 8];
-    __shared__ uint64_t s_keep[NW];                          // the 8x8 block's survivors, entries 64 w ..
-    __shared__ uint32_t s_open[NW];
-    __shared__ uint32_t s_cnt[NW][4];
-    __shared__ float s_h[64];                                // entropy of the 8x8 block's pixels
+    int32_t idx[4][B + 8];
+    uint64_t keep[4];                                        // the 8x8 block's survivors, entries 64 w ..
+    uint32_t open[4];
+    uint32_t cnt[4][4];
+    float h[64];                                             // entropy of the 8x8 block's pixels
+};
+
+template <int B, bool RENDER>
+__device__ __forceinline__ void fwd_slots(const BlendFwdArgs& a, uint32_t wg, FwdSlotLds<B>& lds)
+{
+    constexpr int NW = 4;
+    constexpr int kPart = B + 1;
+    constexpr int kEmptyOff = 16 * B;
+    auto& s_rec = lds.rec;
+    auto& s_idx = lds.idx;
+    auto& s_keep = lds.keep;
+    auto& s_open = lds.open;
+    auto& s_cnt = lds.cnt;
+    auto& s_h = lds.h;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wid = tid >> 6, slot = lane & 3u;
-    const uint32_t item = blockIdx.x / (uint32_t)a.spt;      // longest tiles first
-    const uint32_t wb = (a.tile_order ? a.tile_order[item] : item) * (uint32_t)a.spt + blockIdx.x % (uint32_t)a.spt;
+    const uint32_t item = wg / (uint32_t)a.spt;              // longest tiles first
+    const uint32_t wb = (a.tile_order ? a.tile_order[item] : item) * (uint32_t)a.spt + wg % (uint32_t)a.spt;
     BlockGeom g8, g;
     slot_geom(a.cams, a.n_views, wb, wid, lane, a.tile_shift_x, a.tile_shift_y, a.spt, g8, g);
     const uint2 rg = a.ranges[g8.tile];
@@ -886,6 +911,32 @@ __global__ __launch_bounds__(256) void blend_fwd_slot_kernel(BlendFwdArgs a)
             a.block_cnt[2 * wb + 1] = make_uint4(s[3], 0u, 0u, 0u);
         }
     }
+}
+
+template <bool RENDER>
+__global__ __launch_bounds__(256) void blend_fwd_slot_kernel(BlendFwdArgs a)
+{
+    __shared__ FwdSlotLds<kSlotBatch> s_lds;
+    fwd_slots<kSlotBatch, RENDER>(a, blockIdx.x, s_lds);
+}
+
+// A mid-sized launch of short lists ends with the walks of its longest tiles too: of 200k
+// Gaussians at 1296x840 the compute units were busy for 58 of the plain form's 92 us.  The
+// first workgroups take the 128 longest tiles in the slotted form, the others the
+// rest of the tile order in the plain one, in the same launch; the outputs are those of
+// either form.  76 us; its registers are the slotted form's (five wavefronts a SIMD instead
+// of seven), which larger launches would feel (mixed_blend).
+constexpr int kMixedBatch = 128;
+template <int B, bool RENDER>
+__global__ __launch_bounds__(256) void blend_fwd_mixed_kernel(BlendFwdArgs a)
+{
+    __shared__ union {
+        FwdSlotLds<kMixedBatch> slot;
+        FwdLds<B> plain;
+    } s_lds;
+    const uint32_t n_slot = kMixedTiles * (uint32_t)a.spt;
+    if (blockIdx.x < n_slot) fwd_slots<kMixedBatch, RENDER>(a, blockIdx.x, s_lds.slot);
+    else fwd_blocks<B, false, RENDER>(a, blockIdx.x - n_slot, kMixedTiles, s_lds.plain);
 }
 
 // Per-lane state of the backward walk of one pixel.  The per-pixel sums the
@@ -1660,7 +1711,11 @@ hipError_t fwd_launch(const BlendFwdArgs& a, hipStream_t s)
         if (a.queues)
             hipLaunchKernelGGL((blend_fwd_kernel<B, true, RENDER>),
                                dim3(resident_groups(blend_fwd_kernel<B, true, RENDER>, groups)), dim3(256), 0, s, a);
-        else
+        else if (a.tile_order && a.mixed) {
+            const uint32_t n_slot = kMixedTiles * (uint32_t)a.spt, rest = a.n_blocks - n_slot;
+            hipLaunchKernelGGL((blend_fwd_mixed_kernel<B, RENDER>),
+                               dim3(n_slot + (rest + kWavesPerGroup - 1) / kWavesPerGroup), dim3(256), 0, s, a);
+        } else
             hipLaunchKernelGGL((blend_fwd_kernel<B, false, RENDER>), dim3(groups), dim3(256), 0, s, a);
     }
     return hipGetLastError();

@@ -80,6 +80,20 @@ inline bool slotted_backward(uint32_t n_blocks, uint32_t records)
 {
     return records <= kSlotBackward && slotted_blend(n_blocks, records);
 }
+// The mixed forward (blend.hip): the kMixedTiles longest tiles slotted, the others plain, for
+// lists short enough that tiles do not share batches.  Up to 20 plain wavefronts a SIMD,
+// where the longest walks outlast the rest, and with half a record a block or more.  Both
+// sides, plain -> mixed in us: 17,010 blocks, 200k Gaussians 92 -> 76, 30k 29 -> 24, 3k 12 -> 15
+// (plain); 6,600 blocks, 5k 11 -> 9.5; 17,010 blocks of 8x8 tiles, 300k 124 -> 114, of 32x8, 100k
+// 51 -> 34; 26,800 blocks, 200k 95 -> 89, of 8x8 tiles 74 -> 82 (plain); 39,400 blocks, 250k 109 ->
+// 127 (plain).  64 tiles took 80 us in the first, 192 74, 256 79.
+constexpr uint32_t kMixedTiles = 128;
+constexpr uint32_t kMixedBlocks = 20480;
+inline bool mixed_blend(uint32_t n_blocks, uint32_t records)
+{
+    return n_blocks > kSlotFewBlocks && n_blocks <= kMixedBlocks && records >= n_blocks / 2u;
+}
+static_assert(4u * kMixedTiles <= kSlotFewBlocks, "there are tiles left for the plain form");
 // persistent blend kernels: one work queue per XCD, heads 128 bytes apart
 constexpr uint32_t kQueues = 8;
 constexpr uint32_t kQueueStride = 32;
@@ -166,6 +180,7 @@ struct BlendFwdArgs {
     const uint32_t* tile_order;           // [n_tiles] tiles, longest list first (hardware dispatch); or null
     int32_t shared_batches;               // 16x16 / 32x8 tiles: stage each batch once for the 4 blocks
     int32_t slotted;                      // the slotted form (queues unused: a workgroup a tile)
+    int32_t mixed;                        // the mixed form may be taken (mixed_blend)
 };
 
 struct BlendBwdArgs {

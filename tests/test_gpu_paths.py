@@ -301,3 +301,33 @@ def test_backward_form_by_records():
         a, b = res[0][1][k].double(), res[1][1][k].double()
         assert (a - b).norm() <= 1e-5 * a.norm(), k
     r.close()
+
+
+# The mixed forward (the 128 longest tiles slotted, the rest plain) against the plain one: the
+# same view beside another that makes the launch too large for it.
+@pytest.mark.parametrize("tile,size", [((16, 16), (597, 397)), ((8, 8), (367, 361)), ((32, 8), (641, 300))])
+@pytest.mark.parametrize("n,scale,lds", [(2500, 1.0, 64), (3000, 4.0, 32), (3000, 2.0, 256), (3000, 3.0, 128)])
+def test_mixed_blend_equals_plain(tile, size, n, scale, lds):
+    scene, t = _small_scene(n, 1)
+    t["scales"] = t["scales"] * scale
+    (cam,) = scenes.orbit_cameras(np.random.default_rng(8), [size])
+    (big,) = scenes.orbit_cameras(np.random.default_rng(9), [(1600, 1060)])
+    opts = gsr.RasterOptions(tile=tile, lds_batch=lds, sh_degree=1)
+    p = [t[k] for k in ATTRS]
+    m = cam.width * cam.height
+    r = gsr.Rasterizer(max_views=2)
+    out = r.forward(*p, [cam], opts)
+    one = {k: out[k].clone() for k in ("rgb", "entropy", "t_final", "n_contrib", "entropy_mean")}
+    st = r.stats(1)
+    image = r.render_image(*p, [cam], opts)
+    out = r.forward(*p, [cam, big], opts)
+    both = r.stats(2)
+    r.forward(*p, [big], opts)
+    alone = r.stats(1)
+    for k in ("rgb", "entropy", "t_final", "n_contrib"):
+        assert torch.equal(_bits(one[k]), _bits(out[k][:m])), k
+    assert torch.equal(_bits(image), _bits(one["rgb"]))
+    assert torch.equal(_bits(one["entropy_mean"]), _bits(out["entropy_mean"][:1]))
+    fwd = ("evals_fwd", "blended", "tested_fwd")
+    assert {k: st[k] for k in fwd} == {k: both[k] - alone[k] for k in fwd}
+    r.close()

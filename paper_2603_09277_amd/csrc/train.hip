@@ -46,8 +46,9 @@ __device__ __forceinline__ double block_sum_f64(double x)
 // Bound by its FMAs and LDS reads, not by memory.  The separable passes over whole
 // images that this replaces (5 launches a view, 33 floats a pixel of scratch, every tap
 // of an array of structures from L2) took 1.58 ms on 8 views of 9.76 Mpixel together and
-// 0.23 ms on one 1296x840 image; this takes 0.43 to 0.47 ms (1.0 TB/s of images and gradient) and
-// 0.085 ms, with the same roundings in the same order.  The five horizontal sums go through
+// 0.23 ms on one 1296x840 image; this takes 0.43 ms (1.1 TB/s of images and gradient) and
+// 0.077 ms, and on one of 148x96 23 us (24.5), with the same roundings in the same order.
+// The five horizontal sums go through
 // three planes of LDS in two parts, and loads are issued late, so that three workgroups
 // fit a CU in LDS and registers (the prefetch before the first part: 0.62 ms, spilled).
 // One window of x^2 + y^2 in place of two took 0.42 ms, but its last bits differ, and the
@@ -244,7 +245,8 @@ __global__ __launch_bounds__(kThr, 3) void ssim_kernel(const float* x, const flo
         if constexpr (GRAD) {
             fetch(row + kStep);
             __syncthreads();
-            if (t < 24 * kStep) {
+            // (no output needs the first step's map rows)
+            if (t < 24 * kStep && row >= r0 - 2 * kHalf + kStep) {
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
                     float in[kIn], o[kStep];
@@ -266,7 +268,7 @@ __global__ __launch_bounds__(kThr, 3) void ssim_kernel(const float* x, const flo
                 gg[j] = ok ? grad[r * stride + out_c] : 0.f;
             }
             put();                              // (every read of the partials is done)
-            if (t < kOutF) {
+            if (t < kOutF && row >= r0 - 2 * kHalf + kStep) {
                 float m2[3][kStep];
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
@@ -396,14 +398,15 @@ uint32_t ssim_groups(int32_t W, int32_t H, int seg)
 }
 
 // rows a workgroup, of those whose marched rows (the segment and its halo) are whole
-// steps: the one with the least rounds of workgroups (3 a CU, by LDS) times steps
+// steps: the one with the least rounds of workgroups (3 a CU, by LDS) times steps.  (Small
+// images end with one workgroup's steps: 148x96 with four of them 31 us, with three 23.)
 int ssim_segment(const SsimSizes& z, int v0, int n, bool with_grad, uint64_t* groups)
 {
     constexpr uint64_t kResident = 768;
     const int halo = with_grad ? 4 * kHalf : 2 * kHalf;
     int best = 0;
     uint64_t best_cost = 0;
-    for (int steps : { 18, 14, 10, 8, 6, 4 }) {
+    for (int steps : { 18, 14, 10, 8, 6, 4, 3 }) {
         const int seg = steps * kStep - halo;
         uint64_t wgs = 0;
         for (int v = v0; v < v0 + n; ++v) wgs += ssim_groups(z.w(v), z.h(v), seg);

@@ -357,24 +357,16 @@ constexpr int kPairWords = 16, kPairStride = kPairWords + 1;
 static_assert(sizeof(PairGrad) == 4 * kPairWords, "a pair's record is 16 words");
 constexpr int kBwdRound = 8;                   // views a round
 
-// The gradient one view gives Gaussian i: its 2D row back through colour, conic and
-// mean.  False where the view does not project it (nothing to add).
-template <int DEG, bool BF16>
-__device__ __forceinline__ bool project_bwd_pair(const ProjectBwdArgs& a, uint32_t i, int v, const CamDev& c, PairGrad& o)
+// The gradient one view gives a Gaussian (mean mu, SH coefficients sh, state L): its 2D row g
+// back through colour, conic and mean.  False where the view does not project it (nothing
+// to add).
+template <int DEG>
+__device__ __forceinline__ bool project_bwd_pair(uint32_t flags, const float (&mu)[3], const float (&sh)[(DEG + 1) * (DEG + 1) * 3],
+                                                 const Local& L, const float (&g)[kG2], const CamDev& c, PairGrad& o)
 {
     constexpr int K = (DEG + 1) * (DEG + 1);
-    float g[kG2];
-#pragma unroll
-    for (int k = 0; k < kG2; ++k) g[k] = a.grad2d[(size_t)kG2 * ((size_t)v * a.n + i) + k];
-    float mu[3] = { a.means[3 * (size_t)i], a.means[3 * (size_t)i + 1], a.means[3 * (size_t)i + 2] };
-    float s[3] = { a.scales[3 * (size_t)i], a.scales[3 * (size_t)i + 1], a.scales[3 * (size_t)i + 2] };
-    float q[4] = { a.quats[4 * (size_t)i], a.quats[4 * (size_t)i + 1], a.quats[4 * (size_t)i + 2], a.quats[4 * (size_t)i + 3] };
-    float sh[K * 3];
-    load_sh<K, BF16>(a.sh, i, sh);
-    Local L;
-    local_state(mu, s, q, a.opac[i], sh, K * 3, L);
     ViewProj P;
-    view_proj(c, mu, L, a.flags, P);
+    view_proj(c, mu, L, flags, P);
     if (!P.ok) return false;
     const float gmx = g[0], gmy = g[1], gA = g[2], gB = g[3], gC = g[4];
     o.op = g[5];
@@ -390,7 +382,7 @@ __device__ __forceinline__ bool project_bwd_pair(const ProjectBwdArgs& a, uint32
 #pragma unroll
         for (int k = 0; k < K; ++k) acc += Y[k] * sh[3 * k + ch];
         acc += 0.5f;
-        const bool clamped = (a.flags & F_CCLAMP) && acc < 0.f;
+        const bool clamped = (flags & F_CCLAMP) && acc < 0.f;
         o.col[ch] = clamped ? 0.f : g[6 + ch];
     }
     float gmu[3] = { 0.f, 0.f, 0.f };
@@ -443,6 +435,26 @@ __device__ __forceinline__ bool project_bwd_pair(const ProjectBwdArgs& a, uint32
     return true;
 }
 
+// Gaussian i's parameters and their state
+template <int DEG, bool BF16>
+__device__ __forceinline__ void load_gaussian(const ProjectBwdArgs& a, uint32_t i, float (&mu)[3],
+                                              float (&sh)[(DEG + 1) * (DEG + 1) * 3], Local& L)
+{
+    constexpr int K = (DEG + 1) * (DEG + 1);
+    for (int k = 0; k < 3; ++k) mu[k] = a.means[3 * (size_t)i + k];
+    const float s[3] = { a.scales[3 * (size_t)i], a.scales[3 * (size_t)i + 1], a.scales[3 * (size_t)i + 2] };
+    const float q[4] = { a.quats[4 * (size_t)i], a.quats[4 * (size_t)i + 1], a.quats[4 * (size_t)i + 2], a.quats[4 * (size_t)i + 3] };
+    load_sh<K, BF16>(a.sh, i, sh);
+    local_state(mu, s, q, a.opac[i], sh, K * 3, L);
+}
+
+// the row of a (view, Gaussian)
+__device__ __forceinline__ void load_row(const ProjectBwdArgs& a, uint32_t i, int v, float (&g)[kG2])
+{
+#pragma unroll
+    for (int k = 0; k < kG2; ++k) g[k] = a.grad2d[(size_t)kG2 * ((size_t)v * a.n + i) + k];
+}
+
 // A workgroup owns 256 Gaussians.  Which of their (view, Gaussian) rows are this
 // frame's (the others are zero: no pixel blended the record) is read from the row
 // stamps, 8 views a round; the live pairs of a round are listed in LDS, Gaussian by
@@ -455,8 +467,10 @@ __device__ __forceinline__ bool project_bwd_pair(const ProjectBwdArgs& a, uint32
 // at two workgroups a CU (the 48 SH sums stay in registers over the rounds).  One view of
 // 3.3M FP32 degree-3 Gaussians: 0.41 -> 0.20 ms (4.0 TB/s of what it has to move); 200k:
 // 29 -> 21 us; 8 views of 3M, BF16: 0.53 -> 0.41 ms.
-template <int DEG, bool BF16, bool ONE>
-__global__ __launch_bounds__(256, ONE ? 3 : 2) void project_bwd_kernel(ProjectBwdArgs a)
+// EACH (several views of at most kBwdEach Gaussians): a Gaussian a thread after all, its
+// parameters read once and the next live view's row a view ahead.
+template <int DEG, bool BF16, bool ONE, bool EACH>
+__global__ __launch_bounds__(256, ONE ? 3 : EACH ? 1 : 2) void project_bwd_kernel(ProjectBwdArgs a)
 {
     constexpr int K = (DEG + 1) * (DEG + 1);
     constexpr int kBwdViews = ONE ? 1 : kBwdRound;
@@ -487,6 +501,23 @@ __global__ __launch_bounds__(256, ONE ? 3 : 2) void project_bwd_kernel(ProjectBw
     for (int k = 0; k < K * 3; ++k) gsh[k] = 0.f;
     bool live = false;
 
+    auto add = [&](const PairGrad& o) {
+#pragma unroll
+        for (int w = 0; w < 3; ++w) gmu[w] += o.mu[w];
+#pragma unroll
+        for (int w = 0; w < 6; ++w) gS[w] += o.S[w];
+        gop += o.op;
+        float Y[K];
+        sh_basis<DEG>(o.dir[0], o.dir[1], o.dir[2], Y);
+#pragma unroll
+        for (int w = 0; w < K; ++w) {
+            gsh[3 * w + 0] += Y[w] * o.col[0];
+            gsh[3 * w + 1] += Y[w] * o.col[1];
+            gsh[3 * w + 2] += Y[w] * o.col[2];
+        }
+    };
+    float mu[3], sh[K * 3];                              // EACH
+    Local L;
     const int n_views = ONE ? 1 : a.n_views;
     for (int v0 = 0; v0 < n_views; v0 += kBwdViews) {
         const int nv = n_views - v0 < kBwdViews ? n_views - v0 : kBwdViews;
@@ -499,6 +530,29 @@ __global__ __launch_bounds__(256, ONE ? 3 : 2) void project_bwd_kernel(ProjectBw
         for (int k = 0; k < kBwdViews; ++k)
             if (active && k < nv && r[k] == st) mask |= 1u << k;
         const uint32_t cnt = (uint32_t)__popc(mask);
+        if constexpr (EACH) {
+            __syncthreads();
+            const uint32_t* src = reinterpret_cast<const uint32_t*>(a.cams + v0);
+            for (uint32_t w = tid; w < (uint32_t)nv * (uint32_t)(sizeof(CamDev) / 4); w += 256u)
+                reinterpret_cast<uint32_t*>(s_cam)[w] = src[w];
+            __syncthreads();
+            if (mask == 0u) continue;
+            if (!live) load_gaussian<DEG, BF16>(a, i, mu, sh, L);
+            live = true;
+            float gn[kG2];
+            load_row(a, i, v0 + (__ffs((int)mask) - 1), gn);
+            for (uint32_t m = mask; m;) {
+                const int v = __ffs((int)m) - 1;
+                float g[kG2];
+#pragma unroll
+                for (int k = 0; k < kG2; ++k) g[k] = gn[k];
+                m &= m - 1u;
+                if (m) load_row(a, i, v0 + (__ffs((int)m) - 1), gn);     // (one view ahead)
+                PairGrad o;
+                if (project_bwd_pair<DEG>(a.flags, mu, sh, L, g, s_cam[v], o)) add(o);
+            }
+            continue;
+        }
         live = live || cnt != 0u;
         uint32_t inc = cnt;
 #pragma unroll
@@ -526,8 +580,13 @@ __global__ __launch_bounds__(256, ONE ? 3 : 2) void project_bwd_kernel(ProjectBw
         for (uint32_t c0 = 0; c0 < (ONE ? 1u : total); c0 += 256u) {
             if (c0 + tid < total) {
                 const uint32_t e2 = s_list[c0 + tid], v = e2 >> 8;
+                const uint32_t own = base + (e2 & 0xffu);
+                float g[kG2], pmu[3], psh[K * 3];
+                Local pl;
+                load_row(a, own, v0 + (int)v, g);
+                load_gaussian<DEG, BF16>(a, own, pmu, psh, pl);
                 PairGrad o;
-                if (!project_bwd_pair<DEG, BF16>(a, base + (e2 & 0xffu), v0 + (int)v, s_cam[v], o)) {
+                if (!project_bwd_pair<DEG>(a.flags, pmu, psh, pl, g, s_cam[v], o)) {
                     o = PairGrad{};
                     o.dir[2] = 1.f;
                 }
@@ -543,19 +602,7 @@ __global__ __launch_bounds__(256, ONE ? 3 : 2) void project_bwd_kernel(ProjectBw
                 const float* src = reinterpret_cast<const float*>(s_mem) + (k - c0) * kPairStride;
 #pragma unroll
                 for (int w = 0; w < kPairWords; ++w) reinterpret_cast<float*>(&o)[w] = src[w];
-#pragma unroll
-                for (int w = 0; w < 3; ++w) gmu[w] += o.mu[w];
-#pragma unroll
-                for (int w = 0; w < 6; ++w) gS[w] += o.S[w];
-                gop += o.op;
-                float Y[K];
-                sh_basis<DEG>(o.dir[0], o.dir[1], o.dir[2], Y);
-#pragma unroll
-                for (int w = 0; w < K; ++w) {
-                    gsh[3 * w + 0] += Y[w] * o.col[0];
-                    gsh[3 * w + 1] += Y[w] * o.col[1];
-                    gsh[3 * w + 2] += Y[w] * o.col[2];
-                }
+                add(o);
             }
             __syncthreads();
         }
@@ -695,12 +742,19 @@ hipError_t fwd_dispatch(const ProjectFwdArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+// several views: a Gaussian a thread, or its live pairs compacted?  The first while the launch is
+// short of wavefronts or most pairs are live, the second where it reads the parameters of few
+// of many.  Both sides, first / second in us: 8 views of 400x300, 2k Gaussians 19 / 45, 60k 22 /
+// 47, 300k 71 / 102, 1M 190 / 190; of 972x648, 1M 218 / 238; two views of 972x648, 1M 105 / 113, 3M
+// 302 / 280; 8 views of 9.76 Mpixel, 3M in BF16 493 / 408.
+constexpr uint32_t kBwdEach = 1u << 20;
 template <int DEG, bool BF16>
 hipError_t bwd_dispatch(const ProjectBwdArgs& a, hipStream_t s)
 {
     dim3 grid((a.n + 255u) / 256u);
-    if (a.n_views == 1) hipLaunchKernelGGL((project_bwd_kernel<DEG, BF16, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((project_bwd_kernel<DEG, BF16, false>), grid, dim3(256), 0, s, a);
+    if (a.n_views == 1) hipLaunchKernelGGL((project_bwd_kernel<DEG, BF16, true, false>), grid, dim3(256), 0, s, a);
+    else if (a.n <= kBwdEach) hipLaunchKernelGGL((project_bwd_kernel<DEG, BF16, false, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((project_bwd_kernel<DEG, BF16, false, false>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

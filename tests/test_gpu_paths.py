@@ -331,3 +331,32 @@ def test_mixed_blend_equals_plain(tile, size, n, scale, lds):
     fwd = ("evals_fwd", "blended", "tested_fwd")
     assert {k: st[k] for k in fwd} == {k: both[k] - alone[k] for k in fwd}
     r.close()
+
+
+# The same beyond 2^20 Gaussians, where several views' live pairs are compacted.
+@pytest.mark.parametrize("deg,bf16,views", [(0, False, 2), (1, True, 9), (3, False, 3)])
+def test_projection_backward_compacted(deg, bf16, views):
+    n = (1 << 20) + 513
+    scene, t = _small_scene(n, deg)
+    if bf16:
+        t["sh"] = t["sh"].to(torch.bfloat16)
+    opts = gsr.RasterOptions(sh_degree=deg, sh_bf16=bf16)
+    cams = scenes.orbit_cameras(np.random.default_rng(views), [(61 + v, 43) for v in range(views)])
+    p = [t[k] for k in ATTRS]
+    r = gsr.Rasterizer(max_views=views)
+    npix = [c.width * c.height for c in cams]
+    g_rgb = torch.randn(sum(npix), 3, device=DEV, generator=torch.Generator(DEV).manual_seed(1))
+    g_em = torch.full((views,), 0.3, device=DEV)
+    got = r.backward(*p, cams, opts, r.forward(*p, cams, opts), g_rgb, None, g_em)
+    want = {k: torch.zeros(v.shape, device=DEV, dtype=torch.float64) for k, v in zip(ATTRS, p)}
+    at = 0
+    for v, cam in enumerate(cams):
+        o1 = r.forward(*p, [cam], opts)
+        g1 = r.backward(*p, [cam], opts, o1, g_rgb[at:at + npix[v]].contiguous(), None, g_em[v:v + 1])
+        at += npix[v]
+        for k in ATTRS:
+            want[k] += g1[k].double()
+    for k in ATTRS:
+        d, w = (got[k].double() - want[k]).norm().item(), want[k].norm().item()
+        assert w > 0 and d <= (2.0 ** -8 if bf16 and k == "sh" else 1e-5) * w, (k, d / w)
+    r.close()

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kSpineThreads) void scan_spine_kernel(uint32_t* par
 // 8,192 items a block scatter runs of 32 items a digit on average, 128 bytes of values:
 // with 32-bit keys the 8-view workload's tile passes took about 1.4 ms, 1.7 ms at 16 items).
 // Keys are as wide as the digits still to sort: 16 bits in the tile sort up to 65,536
-// tiles and in the upper half of the depth sort, and the last pass writes none.
+// tiles and in the upper half of large depth sorts, and the last pass writes none.
 //   upsweep   per-block digit histograms, block-major  hist[b * 256 + d] (one
 //             coalesced 1 KB store a block, and one 1 KB load in the downsweep)
 //   spine     one block per 4 digits: exclusive scan of their columns over the
@@ -1275,6 +1275,20 @@ hipError_t radix_pass(const void* keys_in, const uint32_t* vals_in, void* keys_o
 }  // namespace
 
 namespace {
+// sorts without a spine: one kernel for three of the passes, warm in the instruction caches
+// (the downsweeps of 6.7k records take 44 us so, with a kernel a key width 45; 200k 50.4 and 50.7;
+// beyond, at 1M, 92 and 88)
+hipError_t small_depth_sort(const uint32_t* depth, uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n,
+                            uint32_t* tmp, hipStream_t s)
+{
+    hipError_t e = radix_pass<PassKind<uint32_t, uint32_t, true, false>>(depth, nullptr, keys[1], order[1], nullptr, n, 0, 0,
+                                                                         tmp, nullptr, s);
+    for (int p = 1; p < 4 && e == hipSuccess; ++p)
+        e = radix_pass<PassKind<uint32_t, uint32_t, false, false>>(keys[p & 1], order[p & 1], keys[(p + 1) & 1],
+                                                                   order[(p + 1) & 1], nullptr, n, 8 * p, 0, tmp, nullptr, s);
+    return e;
+}
+
 // the keys a pass writes hold the digits still to sort: 32, then 16 bits, then none
 template <bool CARRY>
 hipError_t depth_sort(const uint32_t* depth, uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n,
@@ -1298,8 +1312,9 @@ hipError_t depth_sort(const uint32_t* depth, uint32_t* const (&keys)[2], uint32_
 hipError_t launch_depth_sort(const uint32_t* depth, uint32_t* const (&keys)[2], uint32_t* const (&order)[2], uint32_t n,
                              uint32_t* tmp, const uint32_t* rect, uint32_t* const (&rect_s)[2], hipStream_t s)
 {
-    return rect ? depth_sort<true>(depth, keys, order, n, tmp, rect, rect_s, s)
-                : depth_sort<false>(depth, keys, order, n, tmp, rect, rect_s, s);
+    if (rect) return depth_sort<true>(depth, keys, order, n, tmp, rect, rect_s, s);
+    if (n <= kSelfSpineBlocks * (uint32_t)(kThreads * kRadixSmallItems)) return small_depth_sort(depth, keys, order, n, tmp, s);
+    return depth_sort<false>(depth, keys, order, n, tmp, rect, rect_s, s);
 }
 
 int tile_sort_passes(uint32_t n_tiles)

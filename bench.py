@@ -140,13 +140,15 @@ def stage_bytes(stage, n, V, sh_bytes, pairs, n_tiles, npix):
     read and write once (per (view, Gaussian) `vn`, per pair, per tile, per pixel)."""
     vn = n * V
     return {
-        "project": n * (44 + sh_bytes) + vn * 64,          # params + SH once; record 48 + key 4 + rect 8 + tt 4
-        "depth_sort": vn * 4 * 20,                          # 4 passes: key+value in/out, key histogram
-        "scan": vn * 36,                                    # order, tt and rect gathered, depth-ordered copies, offsets
-        "duplicate": vn * 20 + pairs * 8,                   # order/tt/offset/rect; tile id, owner
-        # 2 passes: keys read twice (histogram, ranking), key + value written; the first pass's
-        # values are the items' indices, the last pass writes no keys (it records the tile ranges)
-        "tile_sort": pairs * 16 * 2,
+        "project": n * (44 + sh_bytes) + vn * 60,          # params + SH once; record 48 + depth 4 + rect 4 + radius 4
+        # 4 passes: keys read twice (histogram, ranking) and written as wide as the digits still
+        # to sort, values (not counted: rectangles that travel along)
+        "depth_sort": vn * 60,
+        "scan": vn * 4,                                     # rectangles (not counted: their gather in smaller frames)
+        "duplicate": vn * 8 + pairs * 6,                    # order, rect; tile id, owner
+        # 2 passes over 16-bit keys, read twice (histogram, ranking); the first pass's values are the
+        # items' indices, the last pass writes no keys (it records the tile ranges)
+        "tile_sort": pairs * 22,
         "ranges": n_tiles * 16,                             # empty tiles' bounds; the tile order reads them twice
         # blend stages: every pair of every list; the forward stops reading a tile's list
         # once all its pixels have stopped, so this bounds what it reads from above

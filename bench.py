@@ -155,9 +155,9 @@ def stage_bytes(stage, n, V, sh_bytes, pairs, n_tiles, npix):
         "blend_fwd": pairs * 56 + npix * 24,                # pair value + owner + record; rgb, H, T, n_contrib
         "entropy_mean": 0,
         "blend_bwd": pairs * 96 + npix * 24,                # pair value + owner + record + row + stamp; per-pixel state
-        # params + SH in, grads out; per view the row stamp and the 2D-gradient row (read only
-        # where the stamp is this frame's: every row counted, an upper bound)
-        "project_bwd": n * (88 + 2 * sh_bytes) + vn * 40,
+        # gradients out, per view the row stamp (not counted: parameters and 2D rows, read only
+        # where a view of this frame blended the Gaussian)
+        "project_bwd": n * (44 + sh_bytes) + vn * 4,
         "grad_reduce": pairs * 8,                           # stamps + owners in (rows and 2D grads only where blended)
     }[stage]
 

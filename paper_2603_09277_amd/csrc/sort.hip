@@ -1449,8 +1449,8 @@ __device__ __forceinline__ uint2 finish_range(uint2* ranges, uint32_t t, uint2 r
 }
 
 // up to kOrderThreads * kOrderPer tiles: the whole counting sort in one workgroup, one launch
-// instead of three
-constexpr uint32_t kOrderThreads = 1024, kOrderPer = 16;
+// instead of three (4,293 tiles 6 us for 9 and two gaps between launches, 6,767 8; 15.4k 17 for 10)
+constexpr uint32_t kOrderThreads = 1024, kOrderPer = 8;
 
 __global__ __launch_bounds__(kOrderThreads) void tile_order_one_kernel(uint2* ranges, uint32_t n_tiles, uint32_t* order)
 {

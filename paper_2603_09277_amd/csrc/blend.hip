@@ -665,8 +665,6 @@ __device__ __forceinline__ void slot_geom(const CamDev* cams, int n_views, uint3
     g.cy1 = (float)min(y0 + 3, c.H - 1) + 0.5f;
 }
 
-constexpr uint64_t kSlot0 = 0x1111111111111111ull;          // the first lane of every quad
-
 // the entries of a slotted walk whose colours are not finite: taken by the lanes that
 // blend them only (a zero weight times infinity must not reach the others)
 __device__ __forceinline__ bool odd_colour(float r, float g, float b)

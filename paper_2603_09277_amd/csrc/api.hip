@@ -790,6 +790,7 @@ gsr_status gsr_forward(gsr_ctx* c, void* stream, const gsr_gaussians* g, const g
         c->replay_pending = true;
         c->pairs = 0;
         c->sorted_buf = tile_sort_passes(L.n_tiles) & 1;
+        c->rect8 = carry_rects(vn, L.max_gx, L.max_gy);     // (a replay's, whatever ran between)
         c->graph_frame = c->frame + 1;
     }
     c->frame += 1;

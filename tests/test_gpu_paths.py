@@ -360,3 +360,22 @@ def test_projection_backward_compacted(deg, bf16, views):
         d, w = (got[k].double() - want[k]).norm().item(), want[k].norm().item()
         assert w > 0 and d <= (2.0 ** -8 if bf16 and k == "sh" else 1e-5) * w, (k, d / w)
     r.close()
+
+
+# A replay after a pair count, whose rectangles are the wider words: the tile counts of the frame.
+def test_replay_after_pair_counts():
+    n = 1 << 21
+    scene, t = _small_scene(n, 0)
+    cams = scenes.orbit_cameras(np.random.default_rng(8), [(64, 48)])
+    opts = gsr.RasterOptions(sh_degree=0, flags=gsr.GSR_DEFAULT_FLAGS | gsr.GSR_GRAPH)
+    p = [t[k] for k in ATTRS]
+    r = gsr.Rasterizer(max_views=1)
+    out = r.forward(*p, cams, opts)
+    want = r.inspect(gsr.BUF_TILES_TOUCHED)
+    count = r.pair_counts(*p, cams, opts)
+    assert count == [want.sum()] and np.array_equal(r.inspect(gsr.BUF_TILES_TOUCHED), want)
+    for _ in range(2):
+        out = r.forward(*p, cams, opts, out)
+        assert np.array_equal(r.inspect(gsr.BUF_TILES_TOUCHED), want)
+        _check_lists(r, n, 1)
+    r.close()

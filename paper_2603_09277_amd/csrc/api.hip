@@ -126,6 +126,8 @@ struct gsr_ctx {
     bool replay_pending = false;
     bool long_lists = false;               // the latest forward's mean list length chose shared staging
     int64_t graph_frame = -1;              // frame id of the latest forward-graph replay
+    uint32_t graph_cap = 0;                // the captured forward's pair_cap_used and long_lists, of every replay:
+    bool graph_long = false;               //   eager frames on this context leave theirs in between
 
     // per-stage timing (eager launches; not under graph capture)
     uint32_t timing = 0;                   // bit s: stage s is timed
@@ -783,6 +785,8 @@ gsr_status gsr_forward(gsr_ctx* c, void* stream, const gsr_gaussians* g, const g
             }
             c->key_fwd = k;
             c->gen_fwd = c->gen;
+            c->graph_cap = c->pair_cap_used;
+            c->graph_long = c->long_lists;
             if (c->gexec_bwd) { (void)hipGraphExecDestroy(c->gexec_bwd); c->gexec_bwd = nullptr; }
         }
         HIP_TRY(c, hipGraphLaunch(c->gexec_fwd, st));
@@ -791,6 +795,8 @@ gsr_status gsr_forward(gsr_ctx* c, void* stream, const gsr_gaussians* g, const g
         c->pairs = 0;
         c->sorted_buf = tile_sort_passes(L.n_tiles) & 1;
         c->rect8 = carry_rects(vn, L.max_gx, L.max_gy);     // (a replay's, whatever ran between)
+        c->pair_cap_used = c->graph_cap;
+        c->long_lists = c->graph_long;
         c->graph_frame = c->frame + 1;
     }
     c->frame += 1;

@@ -1,0 +1,92 @@
+"""Kernel forms, and the state of a context across modes, on the GPU, against plain mode, another form or the FP64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_09277_amd import gsr, scenes
+
+from gpu_helpers import DEV, KEYS, to_dev
+
+pytestmark = pytest.mark.gpu
+
+IMAGES = ("rgb", "entropy", "t_final", "n_contrib")
+
+
+def _scene(n, deg=0, scale=1.0, seed=5):
+    t = to_dev(scenes.gmm_scene(seed, n, sh_degree=deg, n_clusters=4, box=3.0))
+    t["scales"] *= scale
+    return t, [t[k] for k in KEYS]
+
+
+def _cams(*sizes):
+    return scenes.orbit_cameras(np.random.default_rng(8), list(sizes))
+
+
+def _upstream(cams, seed=4):
+    m = sum(c.width * c.height for c in cams)
+    gen = torch.Generator(DEV).manual_seed(seed)
+    return (torch.randn(m, 3, device=DEV, generator=gen), torch.randn(m, device=DEV, generator=gen),
+            torch.full((len(cams),), 0.3, device=DEV))
+
+
+def _near(got, want, tol=1e-5):
+    for k in KEYS:
+        d, w = (got[k].double() - want[k].double()).norm().item(), want[k].double().norm().item()
+        assert w > 0 and d <= tol * w, (k, d, w)
+
+
+# --------------------------------------------------------------------------- #
+# graph replays between eager frames
+# --------------------------------------------------------------------------- #
+
+GRAPH = gsr.GSR_DEFAULT_FLAGS | gsr.GSR_GRAPH
+
+
+def _plain_grads(p, cams, up):
+    r = gsr.Rasterizer(max_views=1)
+    opts = gsr.RasterOptions(sh_degree=0)
+    g = r.backward(*p, cams, opts, r.forward(*p, cams, opts), *up)
+    torch.cuda.synchronize()
+    r.close()
+    return g
+
+
+# A replayed frame's backward works on that frame's pairs, whatever an eager render on the
+# same context held in between: with fewer pairs (the backward must not refuse the frame),
+# and with the backward's graph captured at the smaller frame (it must not keep its size).
+# Gradients as in plain mode (the same FP32 terms, at most in another order: relative L2 1e-5).
+def test_replay_after_renders_of_other_sizes():
+    t, p = _scene(8000, scale=2.0)
+    cams, small = _cams((300, 200)), _cams((160, 112))      # (too many tiles for a bounded frame)
+    up = _upstream(cams)
+    gopts, opts = gsr.RasterOptions(sh_degree=0, flags=GRAPH), gsr.RasterOptions(sh_degree=0)
+    want = _plain_grads(p, cams, up)
+    r = gsr.Rasterizer(max_views=1)
+    out = r.forward(*p, cams, gopts)
+    grads = {k: torch.empty_like(v) for k, v in t.items()}
+    for view in (small, cams, small):
+        r.render_image(*p, view, opts)
+        out = r.forward(*p, cams, gopts, out)
+        _near(r.backward(*p, cams, gopts, out, *up, grads), want)
+    r.close()
+
+
+def test_backward_graph_captured_at_a_smaller_frame():
+    t, p = _scene(8000, scale=2.0)
+    cams = _cams((300, 200))
+    up = _upstream(cams)
+    gopts, opts = gsr.RasterOptions(sh_degree=0, flags=GRAPH), gsr.RasterOptions(sh_degree=0)
+    full = t["scales"].clone()
+    r = gsr.Rasterizer(max_views=1)
+    out = r.forward(*p, cams, gopts)                       # the capacity of the larger frame
+    grads = {k: torch.empty_like(v) for k, v in t.items()}
+    pairs = []
+    for scales in (0.3 * full, full, 0.3 * full):
+        t["scales"].copy_(scales)
+        r.render_image(*p, cams, opts)                     # an eager frame of as many pairs
+        out = r.forward(*p, cams, gopts, out)
+        got = r.backward(*p, cams, gopts, out, *up, grads)
+        _near(got, _plain_grads(p, cams, up))
+        pairs.append(r.stats(1)["pairs"])
+    assert pairs[0] == pairs[2] < 0.7 * pairs[1]
+    r.close()

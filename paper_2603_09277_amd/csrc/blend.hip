@@ -1420,7 +1420,8 @@ __global__ __launch_bounds__(256 * SPT, DENSE ? 8 : 1) void blend_bwd_slot_kerne
                     const float wt = alpha * by_slot(slot, t1, t2, t3, t4);
                     const float lw2 = __builtin_amdgcn_logf(al.act ? wt : 1.f);
                     const float D = fmaf(-q.ghl, lw2, fmaf(q.gCr, g1.z, fmaf(q.gCg, g1.w, fmaf(q.gCb, cb, -q.gh))));
-                    const float wd = wt * D;
+                    // (an entry that this pixel did not blend may have a colour past the largest float)
+                    const float wd = al.act ? wt * D : 0.f;
                     const float q1 = q.Q - quad_f<0>(wd), q2 = q1 - quad_f<1>(wd);
                     const float q3 = q2 - quad_f<2>(wd), q4 = q3 - quad_f<3>(wd);
                     const float dal = rom * fmaf(by_slot(slot, q.T, t1, t2, t3), D, by_slot(slot, q.Q, q1, q2, q3));

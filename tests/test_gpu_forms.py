@@ -90,3 +90,49 @@ def test_backward_graph_captured_at_a_smaller_frame():
         pairs.append(r.stats(1)["pairs"])
     assert pairs[0] == pairs[2] < 0.7 * pairs[1]
     r.close()
+
+
+# --------------------------------------------------------------------------- #
+# colours that overflow
+# --------------------------------------------------------------------------- #
+
+# An entry with an infinite colour that no pixel blends (opacity 0.006 between the pixel
+# centres: it passes the cull, whose rectangle it is over, and reaches 1/255 at none of them)
+# has no part in the gradients of the entries around it; the slotted backward takes it in the
+# same step as them.  Every gradient is finite and as the plain form's (which the view takes
+# beside a large one).
+@pytest.mark.parametrize("tile", [(16, 16), (8, 8), (32, 8)])
+@pytest.mark.parametrize("place", [0, 1, 3, 6])
+def test_infinite_colour_that_no_pixel_blends(tile, place):
+    n = 8
+    cam = scenes.Camera(16, 16, 16.0, 16.0, 8.0, 8.0, np.eye(3, dtype=np.float32), np.zeros(3, np.float32))
+    big = scenes.Camera(1600, 1060, 16.0, 16.0, 8.0, 8.0, cam.R, np.array([0, 0, -100], np.float32))     # sees nothing
+    z = 1.0 + torch.arange(n, device=DEV)
+    xy = torch.tensor([[0.5 if i % 2 else -2.5, -1.5 + 0.5 * i] for i in range(n)], device=DEV)     # pixels from the centre
+    xy[place] = -2.0                                       # inside a 4x4 block
+    sh = torch.zeros(n, 9, 3, device=DEV)
+    sh[:, 0] = torch.linspace(0.1, 0.8, n, device=DEV)[:, None]
+    sh[place, 0::2] = 3.3e38                               # (Y_0, Y_2 and Y_6 are positive along z)
+    sh[place, 4] = sh[place, 8] = 0.0
+    scale = (3.0 * z / 16.0)[:, None].repeat(1, 3)
+    scale[:, 1] *= 0.5
+    scale[place] = 1e-4
+    p = [torch.cat([xy * z[:, None] / 16.0, z[:, None]], 1).contiguous(), scale,
+         torch.tensor([[0.9, 0.1, 0.2, 0.3]], device=DEV).repeat(n, 1),
+         torch.full((n,), 0.3, device=DEV), sh]
+    p[3][place] = 0.006
+    opts = gsr.RasterOptions(tile=tile, sh_degree=2)
+    up = _upstream([cam])
+    r = gsr.Rasterizer(max_views=2)
+    out = r.forward(*p, [cam], opts)
+    assert np.isinf(r.inspect(gsr.BUF_RECORDS).reshape(n, 12)[place, 6:9]).all()
+    assert torch.isfinite(out["rgb"]).all() and r.stats(1)["tested_fwd"] > 0
+    got = r.backward(*p, [cam], opts, out, *up)
+    m = big.width * big.height
+    zeros = [torch.zeros(m, 3, device=DEV), torch.zeros(m, device=DEV), torch.zeros(1, device=DEV)]
+    want = r.backward(*p, [cam, big], opts, r.forward(*p, [cam, big], opts), *(torch.cat(x) for x in zip(up, zeros)))
+    for k in KEYS:
+        assert torch.isfinite(want[k]).all(), k
+        assert torch.isfinite(got[k]).all(), k
+    _near(got, want)
+    r.close()

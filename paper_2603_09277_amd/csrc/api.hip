@@ -366,8 +366,8 @@ gsr_status ensure_tiles(gsr_ctx* c, uint32_t tiles, uint32_t blocks)
     return GSR_OK;
 }
 
-// The whole forward.  Its cameras go up with the first kernel's arguments (more than fit
-// there by a copy); under capture the caller copies them from pinned memory instead.
+// The whole forward.  Its cameras go up in kernel arguments (no host copy to wait for or to
+// keep); under capture the caller copies them from pinned memory instead.
 // `plain` = read the pair count back and size the pair buffers for it (one host
 // synchronisation), with `headroom` at 1.5x the count + 4096 for later fixed-capacity frames;
 // with `bounded` a frame that cannot have more than kBoundPairs pairs is sized for that bound
@@ -382,11 +382,8 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
     // pair count and overflow cleared; a new stamp for the per-pair gradient rows of
     // this frame's backward (every backward of one forward writes the same rows: the
     // entries some pixel blended); the tile ranges and tile-order class counts cleared
-    const int packed = !c->capturing && V <= (uint32_t)kCamPack ? (int)V : 0;
-    if (!c->capturing && !packed)
-        HIP_TRY(c, hipMemcpyAsync(c->cams.p, L.cams.data(), sizeof(CamDev) * V, hipMemcpyHostToDevice, st));
     HIP_TRY(c, launch_frame_begin(counters, (uint32_t*)c->ranges.p, L.n_tiles, L.n_tiles * 2u + kTileHistWords,
-                                  L.cams.data(), packed, (CamDev*)c->cams.p, st));
+                                  L.cams.data(), c->capturing ? 0 : (int)V, (CamDev*)c->cams.p, st));
 
     ProjectFwdArgs pa;
     pa.means = g->means; pa.scales = g->scales; pa.quats = g->quats; pa.opac = g->opacities; pa.sh = g->sh;
@@ -599,8 +596,8 @@ gsr_status wait_replay(gsr_ctx* c)
 }
 
 // GSR_NO_SYNC forward: the capacity path of graph mode, launched eagerly.  The frame's
-// pair count comes back asynchronously into counters_host; ev_replay (waited for by the
-// next call that touches it or the cameras' host copy) covers both.
+// pair count comes back asynchronously into counters_host, covered by ev_replay (waited for
+// by the next call that touches it).
 gsr_status enqueue_nosync(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, const gsr_opts* o, gsr_fwd_out* out,
                           bool render_only)
 {

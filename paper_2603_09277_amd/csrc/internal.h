@@ -286,7 +286,8 @@ hipError_t launch_grad_reduce(const float* pair_grad, const uint32_t* pair_stamp
 
 // a forward's counters: pair total and overflow flag cleared, row stamp (counters[4]) advanced;
 // the n_tiles tile bounds in ranges set to (0xffffffff, 0), the words after them up to
-// ranges[n_words) cleared; n_cams (at most kCamPack) cameras stored to `cams`
+// ranges[n_words) cleared; n_cams cameras stored to `cams` from kernel arguments (a further
+// launch for every kCamPack past the first)
 hipError_t launch_frame_begin(uint32_t* counters, uint32_t* ranges, uint32_t n_tiles, uint32_t n_words,
                               const CamDev* host_cams, int n_cams, CamDev* cams, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t count, hipStream_t s);

@@ -1125,6 +1125,13 @@ __global__ __launch_bounds__(kThreads) void seg_fixup_kernel(const SegCarry* car
 }
 
 
+// `words` words of cameras, by one workgroup
+__device__ __forceinline__ void store_cams(const CamPack& pack, uint32_t words, uint32_t* cams)
+{
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(&pack);
+    for (uint32_t w = threadIdx.x; w < words; w += blockDim.x) cams[w] = src[w];
+}
+
 // a frame's first kernel: pair count and overflow cleared, the row stamp advanced,
 // the tile ranges (plus the tile-order class counts behind them) cleared, and the cameras
 // stored from the kernel's arguments (a copy from host memory of its own cost a small
@@ -1139,13 +1146,15 @@ __global__ void frame_begin_kernel(uint32_t* counters, uint32_t* ranges, uint32_
             counters[8] = 0u;                 // set when this frame's invariants are checked
             atomicAdd(&counters[4], 1u);
         }
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(&pack);
-        for (uint32_t w = threadIdx.x; w < cam_words; w += blockDim.x) cams[w] = src[w];
+        store_cams(pack, cam_words, cams);
     }
     // tile bounds (0xffffffff, 0), then the words after them zero
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n_words; i += gridDim.x * blockDim.x)
         ranges[i] = i < 2u * n_tiles && (i & 1u) == 0u ? 0xffffffffu : 0u;
 }
+
+// the cameras past a frame's first kCamPack
+__global__ void store_cams_kernel(CamPack pack, uint32_t words, uint32_t* cams) { store_cams(pack, words, cams); }
 
 __global__ void fill_u32_kernel(uint32_t* p, uint32_t value, size_t count)
 {
@@ -1407,9 +1416,19 @@ hipError_t launch_frame_begin(uint32_t* counters, uint32_t* ranges, uint32_t n_t
     uint32_t blocks = (n_words + 255u) / 256u;
     blocks = blocks < 1u ? 1u : (blocks > 1024u ? 1024u : blocks);
     CamPack pack;
-    if (n_cams > 0) memcpy(pack.c, host_cams, sizeof(CamDev) * (size_t)n_cams);
-    hipLaunchKernelGGL(frame_begin_kernel, dim3(blocks), dim3(256), 0, s, counters, ranges, n_tiles, n_words, pack,
-                       (uint32_t)n_cams * (uint32_t)(sizeof(CamDev) / 4), reinterpret_cast<uint32_t*>(cams));
+    uint32_t words = 0u;
+    auto fill = [&](int v0) {                                // cameras [v0, v0 + kCamPack)
+        const int nv = n_cams - v0 < kCamPack ? n_cams - v0 : kCamPack;
+        if (nv > 0) memcpy(pack.c, host_cams + v0, sizeof(CamDev) * (size_t)nv);
+        words = (uint32_t)nv * (uint32_t)(sizeof(CamDev) / 4);
+    };
+    fill(0);
+    hipLaunchKernelGGL(frame_begin_kernel, dim3(blocks), dim3(256), 0, s, counters, ranges, n_tiles, n_words, pack, words,
+                       reinterpret_cast<uint32_t*>(cams));
+    for (int v0 = kCamPack; v0 < n_cams; v0 += kCamPack) {
+        fill(v0);
+        hipLaunchKernelGGL(store_cams_kernel, dim3(1), dim3(256), 0, s, pack, words, reinterpret_cast<uint32_t*>(cams + v0));
+    }
     return hipGetLastError();
 }
 

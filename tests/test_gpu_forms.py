@@ -136,3 +136,40 @@ def test_infinite_colour_that_no_pixel_blends(tile, place):
         assert torch.isfinite(got[k]).all(), k
     _near(got, want)
     r.close()
+
+
+# --------------------------------------------------------------------------- #
+# frames without host synchronisation
+# --------------------------------------------------------------------------- #
+
+# GSR_NO_SYNC frames return while the stream is still busy with earlier work, however many
+# views they have (cameras that fit the first kernel's arguments, and more).
+@pytest.mark.parametrize("views", [1, 16, 17, 40, 64])
+def test_no_sync_returns_before_the_stream(views):
+    t, p = _scene(3000)
+    cams = _cams(*[(64 + v, 48) for v in range(views)])
+    opts = gsr.RasterOptions(sh_degree=0, flags=gsr.GSR_DEFAULT_FLAGS | gsr.GSR_NO_SYNC)
+    r = gsr.Rasterizer(max_views=views)
+    other = cams[1:] + cams[:1]
+    want, want2 = ({k: v.clone() for k, v in r.forward(*p, c, gsr.RasterOptions(sh_degree=0)).items() if k in IMAGES}
+                   for c in (cams, other))
+    out = r.forward(*p, cams, opts)                        # the mode's first frame sizes the buffers
+    a = torch.randn(8192, 8192, device=DEV)
+    b = torch.empty_like(a)
+    torch.mm(a, a, out=b)
+    for k in IMAGES:
+        out[k].zero_()
+    out2 = r.forward(*p, other, opts)
+    torch.cuda.synchronize()
+    end = torch.cuda.Event()
+    for _ in range(20):                                    # some 10 ms each
+        torch.mm(a, a, out=b)
+    end.record()
+    out = r.forward(*p, cams, opts, out)
+    busy = not end.query()
+    out2 = r.forward(*p, other, opts, out2)                # (waits for the frame before: its pair count)
+    torch.cuda.synchronize()
+    for k in IMAGES:
+        assert torch.equal(out[k], want[k]) and torch.equal(out2[k], want2[k]), k
+    assert busy
+    r.close()

@@ -84,7 +84,8 @@ typedef struct {
                                     (GSR_ERR_CAPACITY) a frame whose pairs did not fit */
 #define GSR_PERSISTENT     16u   /* persistent blend kernels: resident workgroups pull tiles from 8 device
                                     queues (one per XCD) of spatially contiguous tiles, stealing from the
-                                    others when their own is empty */
+                                    others when their own is empty.  No effect where the blend takes its
+                                    slotted form (see gsr_opts) */
 #define GSR_NO_SYNC        32u   /* eager launches with a fixed pair capacity and no host synchronisation:
                                     the first frame of a context sizes the capacity (1.5x its pairs + 4096),
                                     later frames read their pair count back asynchronously and the next
@@ -97,12 +98,20 @@ typedef struct {
                                     the pixels past the FP32 bound 4u (n_contrib + 1), u = 2^-24 */
 #define GSR_DEFAULT_FLAGS  (GSR_DILATE | GSR_JACOBIAN_CLAMP | GSR_COLOR_CLAMP)
 
+/* Frames of few 8x8 pixel blocks (over all views: at most 2,048, or at most 10,240 with at
+ * least two (view, Gaussian)s a block) are blended in the slotted form, four list entries a
+ * step; their backward too, up to 2^20 (view, Gaussian)s.  It has batches of 256 entries and windows
+ * of 64 of its own: lds_batch and GSR_PERSISTENT change nothing there.  Forward outputs are
+ * those of the other forms bit by bit; gradients sum the same terms over pixels in another
+ * order. */
 typedef struct {
     int32_t tile_w, tile_h;    /* {8,8}, {16,16} or {32,8} */
     int32_t lds_batch;         /* Gaussians staged per LDS batch of the forward: 32, 64, 128, 256; 0 = 64.
                                   The backward walks windows of min(lds_batch, 128) entries (its LDS
                                   holds per-wavefront partial sums of every window entry), or of
-                                  min(lds_batch, 64) when the frame's mean list length is 256 or more */
+                                  min(lds_batch, 64) when the frame's mean list length is 256 or more.
+                                  (Not the slotted form; up to 20,480 blocks the forward's longest tiles
+                                  may be staged 128 at a time.) */
     int32_t sh_degree;         /* 0 .. 3; K = (sh_degree + 1)^2 coefficients per channel */
     int32_t sh_dtype;          /* 0 = float32, 1 = bfloat16 (SH storage and SH gradients) */
     uint32_t flags;            /* GSR_* flags */
@@ -353,7 +362,8 @@ gsr_status gsr_stage_times(gsr_ctx* ctx, double* total_ms, int64_t* launches, in
  * GSR_PERSISTENT) on the given inputs, and write the fastest into
  * inout->tile_w/tile_h/lds_batch and the GSR_PERSISTENT bit of inout->flags
  * (the other flags are kept; the timing runs use plain mode; a candidate's time is the
- * fastest of five forward+backward iterations after one warm-up).  If cache_path is not NULL the result
+ * fastest of five forward+backward iterations after one warm-up).  A tile shape whose
+ * frames are slotted in both passes has one candidate, the batch and scheduling as given.  If cache_path is not NULL the result
  * is read from / appended to that text file, keyed by device and workload.
  * Synchronises `stream`.  Note the image depends on the tile shape. */
 gsr_status gsr_autotune(gsr_ctx* ctx, void* stream, const gsr_gaussians* g, const gsr_camera* cams,

@@ -453,7 +453,8 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
         HIP_TRY(c, launch_tile_sort(pk, pv, L.n_tiles, counters, cap, (uint2*)c->ranges.p, (uint32_t*)c->radix_tmp.p, st));
     }
     const int sb = tile_sort_passes(L.n_tiles) & 1;
-    const bool persist = (o->flags & GSR_PERSISTENT) != 0;
+    const bool slotted = slotted_blend(L.n_blocks, vn);
+    const bool persist = (o->flags & GSR_PERSISTENT) != 0 && !slotted;      // (the slotted form has no queues)
     {
         StageTimer tm(c, st, GSR_STAGE_RANGES, !c->capturing);
         // hardware dispatch visits the tiles longest list first (persistent kernels keep their queues)
@@ -461,8 +462,8 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
         else
             HIP_TRY(c, launch_tile_order((uint2*)c->ranges.p, L.n_tiles, (uint32_t*)c->ranges.p + 2 * (size_t)L.n_tiles,
                                          (uint32_t*)c->tile_order.p, st));
-        // the persistent blend kernels' queue heads (forward and backward sets)
-        if (persist) HIP_TRY(c, launch_fill_u32((uint32_t*)c->queues.p, 0u, 2 * kQueues * kQueueStride, st));
+        // the persistent forward's queue heads (the backward clears its own)
+        if (persist) HIP_TRY(c, launch_fill_u32((uint32_t*)c->queues.p, 0u, kQueues * kQueueStride, st));
     }
 
     BlendFwdArgs ba;
@@ -483,7 +484,7 @@ gsr_status enqueue_forward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, c
         ba.shared_batches = (L.n_tiles > 0 && p_est >= kSharedBatchMeanLen * (double)L.n_tiles) ? 1 : 0;
         c->long_lists = ba.shared_batches != 0;
     }
-    ba.slotted = slotted_blend(L.n_blocks, vn) ? 1 : 0;
+    ba.slotted = slotted ? 1 : 0;
     ba.mixed = mixed_blend(L.n_blocks, vn) ? 1 : 0;
     {
         StageTimer tm(c, st, GSR_STAGE_BLEND_FWD, !c->capturing);
@@ -529,11 +530,11 @@ gsr_status enqueue_backward(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, 
     bb.T_final = saved->t_final; bb.n_contrib = saved->n_contrib; bb.grad_rgb = grad_rgb; bb.grad_H = grad_H;
     bb.grad_LE = grad_LE; bb.pair_grad = (float*)c->pair_grad.p;
     bb.pair_stamp = (uint32_t*)c->pair_stamp.p; bb.stamp = (const uint32_t*)c->counters.p + 4;
-    const bool persist = (o->flags & GSR_PERSISTENT) != 0;
+    bb.slotted = slotted_backward(L.n_blocks, vn) ? 1 : 0;
+    const bool persist = (o->flags & GSR_PERSISTENT) != 0 && !bb.slotted;
     bb.queues = persist ? (uint32_t*)c->queues.p + kQueues * kQueueStride : nullptr;
     bb.tile_order = persist ? nullptr : (const uint32_t*)c->tile_order.p;
     bb.block_cnt = (uint4*)c->block_cnt.p;
-    bb.slotted = slotted_backward(L.n_blocks, vn) ? 1 : 0;
     if (persist) HIP_TRY(c, launch_fill_u32(bb.queues, 0u, kQueues * kQueueStride, st));
     // backward window: at most 128 entries; on long lists 64, whose smaller per-window LDS
     // (records and per-wavefront sums) lets more wavefronts stay resident (the walk of a long
@@ -1417,12 +1418,19 @@ gsr_status gsr_autotune(gsr_ctx* c, void* stream, const gsr_gaussians* g, const 
     hipEvent_t e0, e1;
     HIP_TRY(c, hipEventCreate(&e0));
     HIP_TRY(c, hipEventCreate(&e1));
+    // tile shapes whose frames are slotted in both passes have one candidate: neither the batch
+    // nor the scheduling changes a launch, so both stay as given
+    const int given_lds = inout->lds_batch == 0 ? 64 : inout->lds_batch;
+    const int given_pe = (inout->flags & GSR_PERSISTENT) ? 1 : 0;
     for (int pe = 0; pe < 2; ++pe)
     for (auto& sh : shapes)
         for (int lb : batches) {
             gsr_opts o = *inout;
             o.tile_w = sh[0]; o.tile_h = sh[1]; o.lds_batch = lb;
             o.flags = (o.flags & ~(uint32_t)(GSR_GRAPH | GSR_PERSISTENT | GSR_NO_SYNC)) | (pe ? GSR_PERSISTENT : 0u);
+            if ((lb != given_lds || pe != given_pe) &&
+                slotted_backward(make_layout(cams, n_views, &o).n_blocks, (uint32_t)(g->n * n_views)))
+                continue;
             // one warm-up iteration, then the fastest of five timed ones (the minimum is
             // robust to interference; candidates often differ by a few per cent)
             double t = 1e30;

@@ -179,7 +179,7 @@ struct BlendFwdArgs {
     int32_t render_only;                  // 1: colour only (no entropy, no saved state)
     const uint32_t* tile_order;           // [n_tiles] tiles, longest list first (hardware dispatch); or null
     int32_t shared_batches;               // 16x16 / 32x8 tiles: stage each batch once for the 4 blocks
-    int32_t slotted;                      // the slotted form (queues unused: a workgroup a tile)
+    int32_t slotted;                      // the slotted form (no queues: a workgroup an 8x8 block)
     int32_t mixed;                        // the mixed form may be taken (mixed_blend)
 };
 
@@ -205,7 +205,7 @@ struct BlendBwdArgs {
     const uint32_t* tile_order;           // [n_tiles] tiles, longest list first (hardware dispatch); or null
     uint4* block_cnt;                     // the forward's block counts: word 1 of [2 wb + 1] gets the
                                           //   backward's alpha tests of block wb
-    int32_t slotted;                      // the slotted form (queues unused: a workgroup a tile)
+    int32_t slotted;                      // the slotted form (no queues: a workgroup a tile)
 };
 
 // Debug check of Eq. 9 after a forward (GSR_DEBUG_INVARIANTS): per pixel, the sum of

@@ -173,3 +173,49 @@ def test_no_sync_returns_before_the_stream(views):
         assert torch.equal(out[k], want[k]) and torch.equal(out2[k], want2[k]), k
     assert busy
     r.close()
+
+
+# --------------------------------------------------------------------------- #
+# options that a form does not look at
+# --------------------------------------------------------------------------- #
+
+# Few blocks, more than 2^20 records: the forward is slotted, the backward is not and takes
+# persistent scheduling and lds_batch from the options.
+def test_persistent_backward_after_slotted_forward():
+    n, extra = 3000, 1 << 20
+    t, _ = _scene(n)
+    far = {k: v[:1].expand(extra, *v.shape[1:]) for k, v in t.items()}
+    far["means"] = far["means"] + 1e4
+    p = [torch.cat([t[k], far[k]]).contiguous() for k in KEYS]
+    cams = _cams((70, 50))
+    up = _upstream(cams)
+    r = gsr.Rasterizer(max_views=1)
+    res = []
+    for flags in (0, gsr.GSR_PERSISTENT, gsr.GSR_PERSISTENT | gsr.GSR_GRAPH):
+        opts = gsr.RasterOptions(sh_degree=0, flags=gsr.GSR_DEFAULT_FLAGS | flags)
+        out = r.forward(*p, cams, opts)
+        g = r.backward(*p, cams, opts, out, *up)
+        for _ in range(2):                                 # (queues start afresh for every backward)
+            g = r.backward(*p, cams, opts, out, *up, g)
+        torch.cuda.synchronize()
+        res.append(({k: out[k].clone() for k in IMAGES}, {k: v.clone() for k, v in g.items()}))
+    for img, g in res[1:]:
+        for k in IMAGES:
+            assert torch.equal(img[k], res[0][0][k]), k
+        for k in KEYS:
+            assert torch.equal(g[k], res[0][1][k]), k
+    r.close()
+
+
+# Where both passes are slotted, lds_batch and GSR_PERSISTENT change nothing: the autotuner
+# leaves them as given.
+@pytest.mark.parametrize("lds,flags", [(32, 0), (256, gsr.GSR_PERSISTENT), (128, gsr.GSR_GRAPH)])
+def test_autotune_leaves_what_changes_nothing(lds, flags, tmp_path):
+    t, p = _scene(2000)
+    cams = _cams((96, 64))
+    opts = gsr.RasterOptions(lds_batch=lds, sh_degree=0, flags=gsr.GSR_DEFAULT_FLAGS | flags)
+    r = gsr.Rasterizer(max_views=1)
+    best = r.autotune(*p, cams, opts, str(tmp_path / "tune.txt"))
+    assert best.tile in ((8, 8), (16, 16), (32, 8)) and best.lds_batch == lds and best.flags == opts.flags
+    assert r.autotune(*p, cams, opts, str(tmp_path / "tune.txt")) == best
+    r.close()

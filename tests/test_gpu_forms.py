@@ -3,9 +3,10 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import oracle as orc
 from paper_2603_09277_amd import gsr, scenes
 
-from gpu_helpers import DEV, KEYS, to_dev
+from gpu_helpers import DEV, KEYS, check_grad2d, gpu_records, oracle_stagewise, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -218,4 +219,103 @@ def test_autotune_leaves_what_changes_nothing(lds, flags, tmp_path):
     best = r.autotune(*p, cams, opts, str(tmp_path / "tune.txt"))
     assert best.tile in ((8, 8), (16, 16), (32, 8)) and best.lds_batch == lds and best.flags == opts.flags
     assert r.autotune(*p, cams, opts, str(tmp_path / "tune.txt")) == best
+    r.close()
+
+
+# --------------------------------------------------------------------------- #
+# the forms of frames past the slotted and mixed forms' limits
+# --------------------------------------------------------------------------- #
+
+def _form_scene(long):
+    scene, cams = scenes.tiny_scene(41, 8000)
+    scene.scales = (scene.scales * np.float32(2.0 if long else 0.5)).astype(np.float32)
+    c = cams[0]
+    f = 1600.0 / c.width
+    big = scenes.Camera(1600, 1060, c.fx * f, c.fy * f, 800.0, 530.0, c.R, c.t)     # 26,600 8x8 blocks
+    return scene, [c, big]
+
+
+# The per-block and the shared form of the blends at every batch, in hardware dispatch and
+# persistent, on a small view beside a large one: images and 2D gradients of the small view
+# against the oracle on the GPU's own records; the two schedulings bit by bit.
+@pytest.mark.parametrize("tile,lds", [((16, 16), 32), ((16, 16), 64), ((16, 16), 128), ((16, 16), 256), ((32, 8), 32),
+                                      ((32, 8), 64), ((32, 8), 256), ((8, 8), 32), ((8, 8), 128)])
+@pytest.mark.parametrize("long", [False, True])
+def test_plain_shared_and_persistent_forms_vs_oracle(tile, lds, long):
+    from test_gpu_parity import _cmp_image
+    scene, cams = _form_scene(long)
+    cam, t = cams[0], to_dev(scene)
+    p = [t[k] for k in KEYS]
+    m, M = cam.width * cam.height, sum(c.width * c.height for c in cams)
+    g_rgb = torch.zeros(M, 3, device=DEV)
+    g_rgb[:m] = torch.randn(m, 3, device=DEV, generator=torch.Generator(DEV).manual_seed(1)) / m
+    g_em = torch.tensor([0.3, 0.0], device=DEV)
+    r = gsr.Rasterizer(max_views=2)
+    res = []
+    for flags in (0, gsr.GSR_PERSISTENT):
+        opts = gsr.RasterOptions(tile=tile, lds_batch=lds, sh_degree=0, flags=gsr.GSR_DEFAULT_FLAGS | flags)
+        out = r.forward(*p, cams, opts)
+        grads = r.backward(*p, cams, opts, out, g_rgb, None, g_em)
+        st = r.stats(2)
+        assert (st["mean_len"] >= 256) == long, st["mean_len"]
+        res.append(({k: out[k].clone() for k in IMAGES + ("entropy_mean",)}, {k: v.clone() for k, v in grads.items()},
+                    r.inspect(gsr.BUF_GRAD2D), st, r.render_image(*p, cams, opts)))
+    out, grads, g2, st, image = res[0]
+    assert torch.equal(image, out["rgb"]) and torch.equal(res[1][4], out["rgb"])
+    for k in out:
+        assert torch.equal(res[1][0][k], out[k]), k
+    for k in KEYS:
+        assert torch.equal(res[1][1][k], grads[k]), k
+    assert np.array_equal(res[1][2], g2)
+    assert res[1][3] == st
+    r.forward(*p, cams, opts)
+    pg = gpu_records(r, scene.n, 2)[0]
+    img_o = oracle_stagewise(pg, cam, tile)
+    _cmp_image(out, img_o, cam, 0, cams)
+    g2o = orc.backward_render(cam.width, cam.height, tile[0], tile[1], pg["mean2d"], pg["conic"], pg["opacity"], pg["rgb"],
+                              img_o["ranges"], img_o["values"],
+                              g_rgb[:m].cpu().numpy().reshape(cam.height, cam.width, 3).astype(np.float64),
+                              np.full((cam.height, cam.width), np.float64(np.float32(0.3)) / m))
+    check_grad2d(g2.reshape(2, scene.n, 9)[0].astype(np.float64), g2o)
+    r.close()
+
+
+# The dense slotted backward (16x16 and 32x8 tiles, 6,145 to 10,240 blocks, two records a
+# block or more): images and work counts equal the plain form's, which the view takes beside a
+# large one, bit by bit; the 2D gradients of both are within the oracle's tolerance on the
+# GPU's own records (their sums over pixels are in another order).
+@pytest.mark.parametrize("tile,size", [((16, 16), (800, 513)), ((16, 16), (1011, 631)), ((32, 8), (803, 509))])
+@pytest.mark.parametrize("scale", [1.0, 4.0])
+def test_dense_slotted_backward(tile, size, scale):
+    n = 21_000
+    t, p = _scene(n, 1, scale)
+    (cam,), (big,) = _cams(size), scenes.orbit_cameras(np.random.default_rng(9), [(1600, 1060)])
+    blocks = -(-size[0] // tile[0]) * -(-size[1] // tile[1]) * 4
+    assert 6144 < blocks <= 10240 and n >= 2 * blocks
+    opts = gsr.RasterOptions(tile=tile, sh_degree=1)
+    up = _upstream([cam])
+    m, mb = cam.width * cam.height, big.width * big.height
+    zeros = [torch.zeros(mb, 3, device=DEV), torch.zeros(mb, device=DEV), torch.zeros(1, device=DEV)]
+    r = gsr.Rasterizer(max_views=2)
+    out = r.forward(*p, [cam], opts)
+    one = {k: out[k].clone() for k in IMAGES}
+    r.backward(*p, [cam], opts, out, *up)
+    st, g2 = r.stats(1), r.inspect(gsr.BUF_GRAD2D).reshape(n, 9)
+    out = r.forward(*p, [cam, big], opts)
+    r.backward(*p, [cam, big], opts, out, *(torch.cat(x) for x in zip(up, zeros)))
+    both, g2p = r.stats(2), r.inspect(gsr.BUF_GRAD2D).reshape(2, n, 9)[0]
+    pg = gpu_records(r, n, 2)[0]
+    r.backward(*p, [big], opts, r.forward(*p, [big], opts), *zeros)
+    alone = r.stats(1)
+    for k in IMAGES:
+        assert torch.equal(one[k], out[k][:m]), k
+    for k in ("pairs", "evals_fwd", "evals_bwd", "blended", "tested_fwd", "tested_bwd"):
+        assert st[k] == both[k] - alone[k], k
+    vals, ranges = orc.bin_lists(pg["mean2d"], pg["radius"], pg["depth32"], cam.width, cam.height, tile[0], tile[1])
+    shape = (cam.height, cam.width)
+    g2o = orc.backward_render(cam.width, cam.height, tile[0], tile[1], pg["mean2d"], pg["conic"], pg["opacity"], pg["rgb"],
+                              ranges, vals, up[0].cpu().numpy().reshape(*shape, 3).astype(np.float64),
+                              up[1].cpu().numpy().reshape(shape).astype(np.float64) + np.float64(np.float32(0.3)) / m)
+    for g in (g2p, g2):
+        check_grad2d(g.astype(np.float64), g2o)
     r.close()

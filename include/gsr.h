@@ -186,8 +186,9 @@ gsr_status gsr_forward(gsr_ctx* ctx, void* stream, const gsr_gaussians* g, const
  * without the entropy and without per-pixel saved state.  rgb: device, caller-
  * owned, float [P][3] with views packed as in gsr_fwd_out.  Eager launches
  * only (GSR_GRAPH -> GSR_ERR_UNSUPPORTED; GSR_PERSISTENT and GSR_NO_SYNC are
- * honoured); synchronises once on `stream` unless GSR_NO_SYNC.  It replaces the context's frame: a backward of an earlier
- * forward then fails with GSR_ERR_STALE_FRAME.  gsr_stats describes it. */
+ * honoured); synchronises on `stream` as gsr_forward does.  It replaces the
+ * context's frame: a backward of an earlier forward then fails with
+ * GSR_ERR_STALE_FRAME.  gsr_stats describes it. */
 gsr_status gsr_render(gsr_ctx* ctx, void* stream, const gsr_gaussians* g, const gsr_camera* cams,
                       int32_t n_views, const gsr_opts* opts, float* rgb);
 
@@ -249,8 +250,8 @@ gsr_status gsr_opacity_loss(gsr_ctx* ctx, void* stream, const float* opacities, 
  * with the 3DGS-lineage SSIM (11x11 Gaussian window, sigma 1.5, zero outside
  * the image, C1 = 0.01^2, C2 = 0.03^2, mean over pixels and channels).  rgb,
  * target: device [P][3] packed as in gsr_fwd_out; grad_rgb (device, may be
- * NULL) += dloss/drgb; loss (device, n_views floats, may be NULL).  Views are
- * processed one after another; asynchronous. */
+ * NULL) += dloss/drgb; loss (device, n_views floats, may be NULL).
+ * Asynchronous. */
 gsr_status gsr_dssim(gsr_ctx* ctx, void* stream, const gsr_camera* cams, int32_t n_views, const float* rgb,
                      const float* target, float weight, float* grad_rgb, float* loss);
 
@@ -336,8 +337,9 @@ gsr_status gsr_stats(gsr_ctx* ctx, void* stream, int64_t* pairs_per_view, gsr_fr
  * launches[GSR_N_STAGES] (host arrays), and resets if `reset` is non-zero. */
 typedef enum {
     GSR_STAGE_PROJECT = 0,     /* EWA projection, SH colour, tile rectangles */
-    GSR_STAGE_DEPTH_SORT = 1,  /* LSD radix passes over the depth keys of all (view, Gaussian) */
-    GSR_STAGE_SCAN = 2,        /* prefix sum of tiles touched, in depth order */
+    GSR_STAGE_DEPTH_SORT = 1,  /* LSD radix passes over the depth keys of all (view, Gaussian); up to
+                                  6,144 of them the scan too */
+    GSR_STAGE_SCAN = 2,        /* sums of the tiles touched, in depth order */
     GSR_STAGE_DUPLICATE = 3,   /* (tile, Gaussian) pair emission */
     GSR_STAGE_TILE_SORT = 4,   /* stable LSD radix passes over the tile digits of the pairs; the
                                   last pass also records each tile's [start, end) */

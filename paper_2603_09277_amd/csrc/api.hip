@@ -88,7 +88,8 @@ struct gsr_ctx {
     std::string err;
 
     // grow-only device buffers
-    // rect: per record (rectangle, tiles touched) as uint4
+    // rect: each record's tile rectangle, one 8-byte word, or (rect8) one 4-byte word in its
+    // first half, the second being the sort's scratch; rect_s: the same in depth order
     Dev cams, rec, dkey0, dkey1, ord0, ord1, rect, rect_s, radius, depth, grad2d, rec_stamp, scan_tmp, radix_tmp;
     Dev pk0, pk1, pv0, pv1, emit_vg, pair_grad, pair_stamp, seg_carry, ranges, tile_order, queues, block_H, block_cnt, hchunk, counters, l1_tmp, reg_tmp, ssim_tmp, counts;
     size_t vn_cap = 0, pair_cap = 0, tile_cap = 0, block_cap = 0;

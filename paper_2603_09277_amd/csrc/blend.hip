@@ -919,11 +919,11 @@ __global__ __launch_bounds__(256) void blend_fwd_slot_kernel(BlendFwdArgs a)
 }
 
 // A mid-sized launch of short lists ends with the walks of its longest tiles too: of 200k
-// Gaussians at 1296x840 the compute units were busy for 58 of the plain form's 92 us.  The
-// first workgroups take the 128 longest tiles in the slotted form, the others the
-// rest of the tile order in the plain one, in the same launch; the outputs are those of
-// either form.  76 us; its registers are the slotted form's (five wavefronts a SIMD instead
-// of seven), which larger launches would feel (mixed_blend).
+// Gaussians at 1296x840 VALU instructions were active for 0.79 of the plain form's busy cycles, of
+// 1M with longer lists for 1.00.  The first workgroups take the 128 longest tiles in the slotted
+// form, the others the rest of the tile order in the plain one, in the same launch; the outputs
+// are those of either form.  90 -> 78 us, active for 0.91; its registers are the slotted form's (five
+// wavefronts a SIMD instead of seven), which larger launches would feel (mixed_blend).
 constexpr int kMixedBatch = 128;
 template <int B, bool RENDER>
 __global__ __launch_bounds__(256) void blend_fwd_mixed_kernel(BlendFwdArgs a)
@@ -1327,8 +1327,8 @@ __global__ __launch_bounds__(256, (SHARED && B <= 64 && !PERSIST) ? 8 : 1) void 
 // order.  T and Q pass from slot to slot by DPP (T with the plain form's arithmetic); the 9
 // terms of the four entries are summed over the 16 pixels together, by lane swaps and row
 // rotations, into one row of LDS an entry and wavefront.
-// DENSE: held to 64 VGPRs (a few bytes spill), so that two workgroups of 16 wavefronts
-// share a CU.
+// DENSE: held to 64 VGPRs (19 of them spill, 80 bytes of scratch a lane), so that two
+// workgroups of 16 wavefronts share a CU.
 template <int SPT, bool DENSE>
 __global__ __launch_bounds__(256 * SPT, DENSE ? 8 : 1) void blend_bwd_slot_kernel(BlendBwdArgs a)
 {

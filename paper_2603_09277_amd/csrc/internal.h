@@ -52,29 +52,37 @@ constexpr int kL1Pix = 4 * kL1Block;   // pixels per L1 block (4 a thread)
 constexpr double kLog2e = 1.4426950408889634;
 constexpr int kRecF4 = 3;
 // mean per-tile list length from which the forward stages each batch once per
-// 16x16 / 32x8 tile instead of once per 8x8 block (measured: 200k Gaussians at
-// 1296x840, mean 211, per block 0.105 vs shared 0.116 ms; 1M at 1600x1060, mean
-// 1025, 0.232 vs 0.184 ms; its half-scale variant, mean 495, per block 0.244 ms)
+// 16x16 / 32x8 tile instead of once per 8x8 block, and the backward's window is 64
+// entries instead of 128.  Both sides, per block / shared in us, forward; backward, of 26,800
+// blocks at 1600x1060: mean 154 (150k Gaussians) 75 / 79; 155 / 150, 256 (250k) 89 / 91; 209 / 178,
+// 513 (500k) 125 / 112; 279 / 238, 1,025 (1M) 177 / 141; 342 / 298.  Up to 20,480 blocks the
+// per-block side is the mixed form (below) and the two meet later: 17,172 blocks at 1296x840, mean
+// 207 78 / 104; 176 / 188, 260 82 / 100; 161 / 173, 413 112 / 121; 205 / 209, 823 149 / 151; 259 /
+// 258: there the shared form is taken from 256 on although it is the slower one up to about 800.
 constexpr double kSharedBatchMeanLen = 256.0;
 // The blend's slotted form (four wavefronts an 8x8 block instead of one, see blend.hip): up
 // to kSlotBlocks blocks, ten plain wavefronts a SIMD, below which the plain walks of the
 // longest lists end on an idle chip; and, beyond 2,048 blocks, where lists are not so
 // short that starting four wavefronts a block costs more than their walks (from two
-// records a block).  Both sides, 16x16 tiles, forward / backward in us: 9,600 blocks,
-// 200k Gaussians 131 -> 96 / 243 -> 162, 1M 252 -> 247 / 377 -> 329; 17,010 blocks, 200k
-// 99 -> 137 / 179 -> 228 (plain); 6,600 blocks, 5k (0.8 records a block) 15 -> 25 / 19 -> 29
-// (plain); 2,688 blocks, 5k 17 -> 14 / 27 -> 18.  It depends on sizes alone, so that every
-// mode takes the same form for the same frame.
+// records a block).  Both sides, 16x16 tiles, plain -> slotted, forward / backward in us: 9,600
+// blocks, 200k Gaussians 127 -> 91 / 236 -> 156, 1M 252 -> 247 / 377 -> 329; 17,172 blocks, 200k
+// 90 -> 131 / 172 -> 224 (plain); 6,600 blocks, 5k (0.8 records a block) 12 -> 22 / 17 -> 27
+// (plain); 2,688 blocks, 5k 14 -> 13 / 25 -> 15 (plain, with the mixed forward 10: 1.9 records a
+// block).  It depends on sizes alone, so that every mode takes the same form for the same frame.
 constexpr uint32_t kSlotBlocks = 10240;
 constexpr uint32_t kSlotFewBlocks = 2048;
 inline bool slotted_blend(uint32_t n_blocks, uint32_t records)
 {
     return n_blocks <= kSlotFewBlocks || (n_blocks <= kSlotBlocks && records / 2u >= n_blocks);
 }
-// The backward takes it only up to 2^20 records: its sums over pixels are in another order
-// than the plain form's, and among more Gaussians than that there are scale and rotation
-// gradients that cancel so far that the order shows at 1e-3 of their size (500k and 1M
-// records: 3e-4 at most over 6 scenes each; 2M: up to 2.4e-3).
+// The backward takes it only up to 2^20 records.  Its sums over pixels are in another order
+// than the plain form's, and single scale and rotation gradients that cancel show the order: by
+// 3e-4 of their size at most at 500k and 1M records (6 scenes each), by up to 2.4e-3 at 2M.
+// Against 64 bits both forms are as far off: over 14 scenes of 2k to 2M Gaussians within kSlotBlocks
+// the relative L2 errors (2e-6 to 3.5e-4 by scene and attribute) and the median, 99 % point and
+// maximum of the Gaussians' own errors are the same to a few per cent, the forms 1e-7 to 3.4e-6
+// apart.  So the line is no bound on an error: it keeps frames of more records at the values of
+// the plain form.
 constexpr uint32_t kSlotBackward = 1u << 20;
 inline bool slotted_backward(uint32_t n_blocks, uint32_t records)
 {
@@ -83,10 +91,10 @@ inline bool slotted_backward(uint32_t n_blocks, uint32_t records)
 // The mixed forward (blend.hip): the kMixedTiles longest tiles slotted, the others plain, for
 // lists short enough that tiles do not share batches.  Up to 20 plain wavefronts a SIMD,
 // where the longest walks outlast the rest, and with half a record a block or more.  Both
-// sides, plain -> mixed in us: 17,010 blocks, 200k Gaussians 92 -> 76, 30k 29 -> 24, 3k 12 -> 15
-// (plain); 6,600 blocks, 5k 11 -> 9.5; 17,010 blocks of 8x8 tiles, 300k 124 -> 114, of 32x8, 100k
+// sides, plain -> mixed in us: 17,172 blocks, 200k Gaussians 90 -> 78, 30k 30 -> 26, 3k 12 -> 15
+// (plain); 6,600 blocks, 5k 12 -> 11; 17,010 blocks of 8x8 tiles, 300k 124 -> 114, of 32x8, 100k
 // 51 -> 34; 26,800 blocks, 200k 95 -> 89, of 8x8 tiles 74 -> 82 (plain); 39,400 blocks, 250k 109 ->
-// 127 (plain).  64 tiles took 80 us in the first, 192 74, 256 79.
+// 127 (plain).  The number of tiles rests on the first alone: 64 took 80 us, 192 74, 256 79.
 constexpr uint32_t kMixedTiles = 128;
 constexpr uint32_t kMixedBlocks = 20480;
 inline bool mixed_blend(uint32_t n_blocks, uint32_t records)
@@ -230,9 +238,9 @@ inline size_t project_count_words(uint32_t n, int n_views) { return 4 * (size_t)
 hipError_t launch_project_bwd(const ProjectBwdArgs& a, int sh_degree, bool sh_bf16, hipStream_t s);
 
 // The tile rectangles of large depth sorts travel with the sort as 32-bit words, from
-// `records` on, where the large passes begin, if every view has at most 256 x 256 tiles: sort
-// and scan of 24M records take 0.53 ms so (0.81 with the rectangles gathered at the end),
-// of 3.3M 114 us (136); the small passes are bound by latency, and 1M records gather in 15 us.
+// `records` on, where the large passes begin, if every view has at most 256 x 256 tiles: the four
+// downsweeps and the scan of 24M records take 0.52 ms so (0.88 with the rectangles gathered at the
+// end), with histograms and spines 0.65; of 3.3M 114 us (136); the small passes are bound by latency, and 1M records gather in 15 us.
 constexpr uint32_t kCarryFrom = 1u << 21;
 inline bool carry_rects(uint32_t records, int gx, int gy) { return records >= kCarryFrom && gx <= 256 && gy <= 256; }
 

@@ -58,8 +58,8 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* total)
 // depth order): tile counts summed a workgroup, then an exclusive scan of the sums.
 // Rectangles are 32-bit words in depth order where the depth sort carried them (large
 // sorts, carry_rects), else 64-bit words that the reduce step gathers: 8 bytes at 24M
-// random places take 0.48 ms, where carrying 4 bytes through the four passes (0.32 ->
-// 0.51 ms) and reading them in order takes 0.02.
+// random places take 0.48 ms, where carrying 4 bytes through the four passes (0.31 ->
+// 0.50 ms) and reading them in order takes 0.02.
 // ---------------------------------------------------------------------------
 
 // inclusive tile bounds: (x0 | x1 << 16, y0 | y1 << 16), or in one word x0, x1, y0, y1 of 8
@@ -375,8 +375,8 @@ struct PassKind {
 // counts itself and no spine kernel runs.  An item's key and rank share a register where
 // both are 16 bits, and LDS holds 16-bit keys and, for implicit values, 16-bit local
 // indices: three (implicit: four) workgroups of 8,192 items a CU instead of two, whose
-// loads, ranking and scatter overlap.  The 8-view workload's two tile passes take 0.59 ms
-// (32-bit keys and 180 registers a lane: 0.79), with their histograms 0.75 (1.06).
+// loads, ranking and scatter overlap.  The 8-view workload's two tile passes take 0.61 ms
+// (32-bit keys and 180 registers a lane: 0.79), with their histograms and spines 0.83 (1.10).
 template <int ITEMS, bool SELF, typename Kind>
 __global__ __launch_bounds__(kThreads) void radix_downsweep_kernel(
     const typename Kind::Key* keys_in, const uint32_t* vals_in, typename Kind::Out* keys_out, uint32_t* vals_out,

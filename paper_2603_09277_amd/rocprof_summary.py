@@ -81,6 +81,7 @@ def pick(d, pattern):
 
 # VALU issue rate: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, one FP32 lane-operation per lane per clock
 VALU_LANE_OPS_PEAK = 256 * 64 * 2.4e9
+N_SIMD, N_SE = 1024, 32
 
 
 def all_counters(paths):
@@ -113,6 +114,11 @@ def counters_table(paths, stats_path, patterns):
         if "SQ_THREAD_CYCLES_VALU" in avg and avg.get("SQ_ACTIVE_INST_VALU"):
             out.append(f"| VALU lane utilisation (active lanes / 64) | "
                        f"{avg['SQ_THREAD_CYCLES_VALU'] / (avg['SQ_ACTIVE_INST_VALU'] * 64):.3f} |")
+        if avg.get("SQ_BUSY_CYCLES") and "SQ_ACTIVE_INST_VALU" in avg:
+            # quad-cycles over the SIMDs against the cycles that the shader engines were busy; launches
+            # bound by VALU issue read 1.1 (a transcendental is active for longer than it blocks others)
+            v = avg["SQ_ACTIVE_INST_VALU"] * 4 / N_SIMD / (avg["SQ_BUSY_CYCLES"] / N_SE)
+            out.append(f"| VALU active cycles a SIMD / busy cycles | {v:.3f} |")
         if "SQ_INSTS_VALU" in avg and d_ns:
             rate = avg["SQ_INSTS_VALU"] * 64 / (d_ns * 1e-9)
             out.append(f"| issued VALU lane-slots / s | {rate / 1e12:.2f} T ({rate / VALU_LANE_OPS_PEAK:.3f} of "

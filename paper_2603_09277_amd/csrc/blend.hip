@@ -1649,9 +1649,10 @@ __global__ __launch_bounds__(256) void entropy_mean_kernel(const double* chunk_s
     if (threadIdx.x == 0) out[v] = (float)(tot / ((double)c.W * (double)c.H));
 }
 
-// views of at most kOneBlocks blocks: one workgroup a view, one launch instead of two (8.5 us
-// of a small frame)
-constexpr uint32_t kOneThreads = 1024, kOneBlocks = 32u * kOneThreads;
+// views of at most kOneBlocks blocks: one workgroup a view, one launch instead of two.  Both sides
+// as a step's time in us, one launch / two: 4,000 blocks 114 / 120, 10,240 124 / 127, 17,172 136.5 /
+// 136.8, 20,520 143.0 / 142.4, 22,800 147 / 146, 26,800 155 / 152, 32,640 166 / 162.
+constexpr uint32_t kOneThreads = 1024, kOneBlocks = 20u * kOneThreads;
 
 __global__ __launch_bounds__(kOneThreads) void entropy_one_kernel(const float* block_H, const CamDev* cams, float* out)
 {

@@ -1468,8 +1468,9 @@ __device__ __forceinline__ uint2 finish_range(uint2* ranges, uint32_t t, uint2 r
 }
 
 // up to kOrderThreads * kOrderPer tiles: the whole counting sort in one workgroup, one launch
-// instead of three (4,293 tiles 6 us for 9 and two gaps between launches, 6,767 8; 15.4k 17 for 10)
-constexpr uint32_t kOrderThreads = 1024, kOrderPer = 8;
+// instead of two.  Both sides as a step's time in us, one launch / two: 1,000 tiles 114 / 120, 2,560
+// 124 / 127, 4,293 136.5 / 137.2, 5,130 143.0 / 142.5, 5,700 147 / 146, 6,700 155 / 152, 8,160 166 / 161.
+constexpr uint32_t kOrderThreads = 1024, kOrderPer = 5;
 
 __global__ __launch_bounds__(kOrderThreads) void tile_order_one_kernel(uint2* ranges, uint32_t n_tiles, uint32_t* order)
 {

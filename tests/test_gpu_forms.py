@@ -319,3 +319,26 @@ def test_dense_slotted_backward(tile, size, scale):
     for g in (g2p, g2):
         check_grad2d(g.astype(np.float64), g2o)
     r.close()
+
+
+# Tile order and mean entropy in one kernel or in two (from 5,121 tiles and from a view of 20,481 8x8
+# blocks on): every tile is served, as without an order (persistent scheduling, bit by bit),
+# and L_E is the FP64 mean of the entropy map to FP32 rounding.
+@pytest.mark.parametrize("tile,sizes", [((16, 16), [(1280, 1024)]), ((16, 16), [(1296, 1024)]), ((16, 16), [(1920, 1080)]),
+                                        ((8, 8), [(1280, 1024)]), ((8, 8), [(1281, 1024)]), ((32, 8), [(1280, 1024), (1281, 1025)])])
+def test_one_and_two_kernel_forms(tile, sizes):
+    t, p = _scene(7000, scale=2.0)
+    cams = _cams(*sizes)
+    r = gsr.Rasterizer(max_views=2)
+    res = []
+    for flags in (0, gsr.GSR_PERSISTENT):
+        out = r.forward(*p, cams, gsr.RasterOptions(tile=tile, sh_degree=0, flags=gsr.GSR_DEFAULT_FLAGS | flags), None)
+        res.append({k: out[k].clone() for k in IMAGES + ("entropy_mean",)})
+    for k in res[0]:
+        assert torch.equal(res[0][k], res[1][k]), k
+    at = 0
+    for v, c in enumerate(cams):
+        h = res[0]["entropy"][at:at + c.width * c.height].double().mean().item()
+        assert h > 0 and abs(res[0]["entropy_mean"][v].item() - h) <= 2e-6 * h
+        at += c.width * c.height
+    r.close()

@@ -398,8 +398,10 @@ uint32_t ssim_groups(int32_t W, int32_t H, int seg)
 }
 
 // rows a workgroup, of those whose marched rows (the segment and its halo) are whole
-// steps: the one with the least rounds of workgroups (3 a CU, by LDS) times steps.  (Small
-// images end with one workgroup's steps: 148x96 with four of them 31 us, with three 23.)
+// steps: the one of the least time, rounds of workgroups (3 a CU, by LDS) times steps, where
+// a step takes 5.9 us with one workgroup a CU, 7.9 with two and 10.3 with three: 3, 4 and 5 units for
+// the last round.  (Counted as equal, 320x480 took three steps at 600 workgroups, 37 us, instead of
+// four at 200, 30; 148x96 takes three at 72, 23, and four would take 31.)
 int ssim_segment(const SsimSizes& z, int v0, int n, bool with_grad, uint64_t* groups)
 {
     constexpr uint64_t kResident = 768;
@@ -410,8 +412,9 @@ int ssim_segment(const SsimSizes& z, int v0, int n, bool with_grad, uint64_t* gr
         const int seg = steps * kStep - halo;
         uint64_t wgs = 0;
         for (int v = v0; v < v0 + n; ++v) wgs += ssim_groups(z.w(v), z.h(v), seg);
-        const uint64_t cost = (wgs + kResident - 1) / kResident * (uint64_t)steps;
-        if (best == 0 || cost < best_cost) { best = seg; best_cost = cost; *groups = wgs; }
+        const uint64_t rest = wgs % kResident;
+        const uint64_t cost = (5 * (wgs / kResident) + (rest == 0 ? 0 : rest <= 256 ? 3 : rest <= 512 ? 4 : 5)) * (uint64_t)steps;
+        if (best == 0 || cost <= best_cost) { best = seg; best_cost = cost; *groups = wgs; }
     }
     return best;
 }

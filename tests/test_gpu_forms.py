@@ -342,3 +342,25 @@ def test_one_and_two_kernel_forms(tile, sizes):
         assert h > 0 and abs(res[0]["entropy_mean"][v].item() - h) <= 2e-6 * h
         at += c.width * c.height
     r.close()
+
+
+# D-SSIM at sizes between those of one round of short segments and several rounds of long ones;
+# tolerances as for the parity test of its bands (FP32 window sums against FP64).
+@pytest.mark.parametrize("sizes", [[(320, 480)], [(65, 700)], [(486, 324), (97, 65)], [(20, 2000)]])
+def test_dssim_segments_of_mid_sized_images(sizes):
+    rng = np.random.default_rng(sizes[0][1])
+    xs = [rng.uniform(0, 1, (h, w, 3)).astype(np.float32) for w, h in sizes]
+    ys = [np.clip(x + rng.normal(0, 0.1, x.shape), 0, 1).astype(np.float32) for x in xs]
+    x, y = (torch.from_numpy(np.concatenate([a.reshape(-1, 3) for a in s])).to(DEV) for s in (xs, ys))
+    cams = _cams(*sizes)
+    grad = torch.zeros_like(x)
+    r = gsr.Rasterizer(max_views=2)
+    loss = r.dssim(cams, x, y, 0.2, grad).cpu().numpy()
+    at = 0
+    for v, (w, h) in enumerate(sizes):
+        s, gs = orc.ssim(xs[v], ys[v])
+        g = grad[at:at + w * h].cpu().numpy().reshape(h, w, 3).astype(np.float64)
+        assert abs(loss[v] - 0.2 * (1.0 - s)) <= 2e-5, (v, w, h)
+        assert np.linalg.norm(g + 0.2 * gs) <= 1e-4 * np.linalg.norm(0.2 * gs), (v, w, h)
+        at += w * h
+    r.close()

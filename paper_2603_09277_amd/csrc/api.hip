@@ -322,6 +322,7 @@ gsr_status ensure_vn(gsr_ctx* c, uint32_t vn)
     size_t v = std::max<size_t>(vn, 1);
     if (v <= c->vn_cap) return GSR_OK;
     v = std::max(v, c->vn_cap + c->vn_cap / 4);
+    c->vn_cap = 0;                         // (a failure below leaves some of the buffers without memory)
     gsr_status s;
     if ((s = grow(c, c->rec, v * 48)) || (s = grow(c, c->dkey0, v * 4)) || (s = grow(c, c->dkey1, v * 4)) ||
         (s = grow(c, c->ord0, v * 4)) || (s = grow(c, c->ord1, v * 4)) || (s = grow(c, c->rect, v * 8)) ||
@@ -339,6 +340,7 @@ gsr_status ensure_pairs(gsr_ctx* c, size_t p)
     p = std::max<size_t>(p, 1);
     if (p <= c->pair_cap) return GSR_OK;
     if (p >= 0xfffffff0ull) return fail(c, GSR_ERR_CAPACITY, "pair count exceeds 2^32");
+    c->pair_cap = 0;                       // (as in ensure_vn)
     gsr_status s;
     if ((s = grow(c, c->pk0, p * 4)) || (s = grow(c, c->pk1, p * 4)) || (s = grow(c, c->pv0, p * 4)) ||
         (s = grow(c, c->pv1, p * 4)) || (s = grow(c, c->emit_vg, p * 4)) || (s = grow(c, c->pair_grad, p * 4 * kRowF + 64, true)) ||
@@ -604,7 +606,7 @@ gsr_status enqueue_nosync(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g, co
                           bool render_only)
 {
     gsr_status s;
-    if (!c->nosync_ready) {                          // first such frame: exact sizing, then head room
+    if (!c->nosync_ready || c->pair_cap == 0) {      // first such frame: exact sizing, then head room
         // (the buffers grow before the pairs are written, so this frame's state stays valid)
         if ((s = enqueue_forward(c, st, g, o, out, true, render_only, true))) return s;
         c->nosync_count = false;
@@ -725,6 +727,7 @@ gsr_status gsr_forward(gsr_ctx* c, void* stream, const gsr_gaussians* g, const g
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
     if ((s = wait_replay(c))) return s;
+    c->have_frame = c->have_records = false;       // until this frame is enqueued whole
     Layout L = make_layout(cams, n_views, o);
     const uint32_t n = (uint32_t)g->n, vn = n * (uint32_t)n_views;
     if ((s = ensure_vn(c, vn)) || (s = ensure_tiles(c, L.n_tiles, L.n_blocks)) ||
@@ -815,6 +818,7 @@ gsr_status gsr_render(gsr_ctx* c, void* stream, const gsr_gaussians* g, const gs
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(c, hipSetDevice(c->device));
     if ((s = wait_replay(c))) return s;
+    c->have_frame = c->have_records = false;       // until this frame is enqueued whole
     Layout L = make_layout(cams, n_views, o);
     const uint32_t n = (uint32_t)g->n, vn = n * (uint32_t)n_views;
     if ((s = ensure_vn(c, vn)) || (s = ensure_tiles(c, L.n_tiles, L.n_blocks)) ||
@@ -1057,6 +1061,7 @@ static gsr_status count_pairs(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g
 {
     gsr_status s;
     if ((s = wait_replay(c))) return s;
+    c->have_frame = c->have_records = false;
     const gsr_camera* kept = cams + store_from;
     const int32_t n_kept = n_views - store_from;
     Layout L = make_layout(kept, n_kept, o);
@@ -1069,7 +1074,6 @@ static gsr_status count_pairs(gsr_ctx* c, hipStream_t st, const gsr_gaussians* g
     c->n = n;
     c->vn = vn;
     c->n_views = n_kept;
-    c->have_frame = false;
     c->have_records = true;
     c->frame += 1;
     const Layout all = make_layout(cams, n_views, o);

@@ -37,7 +37,9 @@
  *
  * Errors: argument errors return before any GPU work is enqueued and leave
  * outputs untouched.  GSR_ERR_HIP wraps a HIP runtime failure (text in
- * gsr_last_error).  No C++ exception crosses this interface.
+ * gsr_last_error).  A forward, render or pair count that fails later (GSR_ERR_OOM,
+ * GSR_ERR_HIP, GSR_ERR_CAPACITY) leaves the context without a frame; the next
+ * forward starts afresh.  No C++ exception crosses this interface.
  *
  * Streams: all work is enqueued on the given stream (NULL = default stream);
  * calls return without synchronising except where stated.  A context is not

@@ -8,12 +8,14 @@
 // of 4 wavefronts (its 4 blocks), an 8x8 tile is one wavefront.  The tile
 // shape sets the sort granularity; the wavefront sets the blend granularity.
 //
-// Forward, two forms.  Per block: each wavefront stages its list in LDS in
+// Forward, four forms with the same outputs.  Per block: each wavefront stages its list in LDS in
 // batches of B records (its own LDS region: no workgroup barrier, and a
 // wavefront whose 64 pixels have all stopped leaves at the next batch
 // boundary).  Shared (16x16 and 32x8 tiles, long lists): the 4 wavefronts of a
 // tile stage each batch once, one entry per thread, and the tile's batch loop
-// ends when none of its pixels is open.
+// ends when none of its pixels is open.  Slotted (few blocks): four wavefronts a
+// block, four list entries a step.  Mixed (mid-sized launches of short lists): the
+// longest tiles slotted, the others per block.
 //
 // Culling: while staging, every wavefront drops the Gaussians that cannot
 // reach alpha >= 1/255 at any pixel centre of its 8x8 block: the exact maximum
@@ -22,7 +24,8 @@
 // entries would be skipped by every lane anyway, so results are unchanged;
 // the list walk only visits the survivors, compacted in list order.
 //
-// Backward: list windows of B entries are walked from the back.  In a 16x16
+// Backward: list windows of B entries are walked from the back (in the slotted form
+// too, with 4x4 blocks and four entries a step).  In a 16x16
 // or 32x8 tile the 4 wavefronts share each window's records.  An entry that
 // no lane of a wavefront blended is skipped by that wavefront.  Per Gaussian,
 // every wavefront sums its 9 partial gradients over its 64 lanes (half and

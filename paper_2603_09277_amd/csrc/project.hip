@@ -1,8 +1,9 @@
 // EWA projection of 3D Gaussians (Sec. 3, Eq. 1-2) and its backward.
 //
-// One thread per Gaussian; the thread loops over the views of the launch so
+// Forward: one thread per Gaussian, which loops over the views of the launch so
 // that parameters and SH coefficients are read from HBM once per Gaussian,
-// not once per (view, Gaussian).  Everything is FP32 except the 2x2
+// not once per (view, Gaussian).  Backward: a workgroup owns 256 Gaussians and
+// works on those of their views that blended them.  Everything is FP32 except the 2x2
 // determinant / inverse / eigenvalue step, which runs in FP64: near-degenerate
 // 2D covariances lose all significant digits of det = ac - b^2 in FP32.
 #include "internal.h"
